@@ -10,7 +10,7 @@
 //                     (run-deduplicated), batched: each id's slot tagged with
 //                     its shard, an id met in two shards flagged;
 //   2. k_dict_compact distinct ids -> list; radix sort of the list (signed order);
-//   3. k_dict_meta    journey count J, rank bits, time bits, key bits, passes;
+//   3. (its last block) journey count J, rank bits, time bits, key bits, passes;
 //   4. k_dict_rank    dense order-preserving rank of each distinct id; batched:
 //                     k_dict_shardkey + a stable sort by shard + k_dict_final,
 //                     ranks in (shard, id) order (the shard then needs no
@@ -60,6 +60,7 @@ struct SortMeta {
     u32 ib;   // index bits of a packed key word
     u32 p0;   // first pass whose input words are packed (ib and p0 adjacent: the radix passes read both)
     u32 w0;   // bits of the first radix digit: 9 where that saves a pass (a key of 8k + 1 bits), else 8
+    u32 blocks_done;  // blocks of the compaction that have ended
     u32 n_runs;  // runs of equal ids in input order (counted by the dictionary insert)
     u32 unordered;  // a timestamp below its predecessor's (same shard) in input order
     u32 ts_dropped; // key = (shard, rank) only: the input is time-ordered within every shard
@@ -73,14 +74,30 @@ struct SortMeta {
 
 __device__ __forceinline__ u32 bit_width64(u64 x) { return x ? 64u - (u32)__clzll((long long)x) : 0u; }
 
-__global__ void k_sort_init(SortMeta* m)
+// What one block of the dictionary insert found in its records, stored by the
+// block and joined by the last block of the compaction.  Adding it to one
+// shared word instead serialised some 36 000 atomics on a few addresses:
+// about 250 us of every sort, whatever its size.
+struct InsPart {
+    u64 lo, hi;  // least and largest time stamp (ordered image)
+    u64 tor;     // OR of every |ts - ts[0]|
+    u32 nd5, runs, down, multi;
+};
+
+// The sort's scratch in one launch: the meta words, the dictionary's empty
+// slots and the region cleared to zero.
+__global__ void __launch_bounds__(256) k_sort_begin(SortMeta* m, u64* __restrict__ table, u64 words,
+                                                    u32* __restrict__ zero, u64 zwords)
 {
-    if (threadIdx.x == 0) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
         SortMeta z = {};
-        z.tmin_ord = ~0ull;
-        z.tmax_ord = 0;
         *m = z;
     }
+    const u64 i0 = (u64)blockIdx.x * blockDim.x + threadIdx.x;
+    const u64 stride = (u64)gridDim.x * blockDim.x;
+    ulonglong2* t2 = (ulonglong2*)table;  // slots are 16-byte pairs
+    for (u64 i = i0; i < words / 2; i += stride) t2[i] = make_ulonglong2(EMPTY, EMPTY);
+    for (u64 i = i0; i < zwords; i += stride) zero[i] = 0u;
 }
 
 // The dictionary is an open-addressing table of 16-byte slots {id, rank}:
@@ -214,6 +231,29 @@ __device__ __forceinline__ u64 time_offset(u64 toff, u32 sh, u32 p5)
     return q;
 }
 
+__device__ __forceinline__ void part_join(InsPart& a, const InsPart& b)
+{
+    a.lo = b.lo < a.lo ? b.lo : a.lo;
+    a.hi = b.hi > a.hi ? b.hi : a.hi;
+    a.tor |= b.tor;
+    a.nd5 |= b.nd5;
+    a.runs += b.runs;
+    a.down |= b.down;
+    a.multi |= b.multi;
+}
+
+// the join of a wave's lanes, in every lane
+__device__ __forceinline__ void part_wave_join(InsPart& p)
+{
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) {
+        const InsPart o{(u64)__shfl_xor(p.lo, d, WAVE), (u64)__shfl_xor(p.hi, d, WAVE), (u64)__shfl_xor(p.tor, d, WAVE),
+                        (u32)__shfl_xor(p.nd5, d, WAVE), (u32)__shfl_xor(p.runs, d, WAVE),
+                        (u32)__shfl_xor(p.down, d, WAVE), (u32)__shfl_xor(p.multi, d, WAVE)};
+        part_join(p, o);
+    }
+}
+
 // Also checks whether the timestamps never decrease within a shard in input
 // order: then every journey's records already come in time order, and a
 // stable sort by (shard, journey) alone gives the (journey, time) order.
@@ -225,12 +265,13 @@ __device__ __forceinline__ u64 time_offset(u64 toff, u32 sh, u32 p5)
 template <bool SHARDS>
 __global__ void __launch_bounds__(256) k_dict_insert(const i64* __restrict__ jid, const i64* __restrict__ ts, u32 n,
                                                      u64* __restrict__ table, u64 mask, SortMeta* m,
-                                                     const u64* __restrict__ soff, u32 S)
+                                                     InsPart* __restrict__ parts, const u64* __restrict__ soff,
+                                                     u32 S)
 {
     // (the batched form's 16-byte probes and shard checks take it to 4 waves
     // per SIMD, with 3 windows per round as with 4)
     constexpr int DP = DPW;
-    __shared__ u64 s_min[4], s_max[4];
+    __shared__ InsPart s_part[4];
     __shared__ u64 c_key[4][DC];
     __shared__ u32 c_own[4][DC];
     const int w = threadIdx.x / WAVE;
@@ -367,79 +408,23 @@ __global__ void __launch_bounds__(256) k_dict_insert(const i64* __restrict__ jid
             csh = last;
         }
     }
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) {
-        u64 a = __shfl_xor(lo, d, WAVE), b = __shfl_xor(hi, d, WAVE);
-        lo = a < lo ? a : lo;
-        hi = b > hi ? b : hi;
-    }
-    if (l == 0) {
-        s_min[w] = lo;
-        s_max[w] = hi;
-    }
     if (has_min) atomicOr(&m->has_min, 1u);
     if (full) atomicOr(&m->overflow, 1u);
-    if (SHARDS && __ballot(multi) && l == 0) atomicOr(&m->multi_shard, 1u);
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) {
-        tor |= __shfl_xor(tor, d, WAVE);
-        nd5 |= __shfl_xor(nd5, d, WAVE);
-    }
-    if (l == 0) {
-        if (tor) atomicOr((unsigned long long*)&m->t_or, (unsigned long long)tor);
-        if (nd5) atomicOr(&m->t_nd5, nd5);
-    }
-    if (__ballot(down) && l == 0) atomicOr(&m->unordered, 1u);
-    if (runs && l == 0) atomicAdd(&m->n_runs, runs);
+    // (runs is wave-uniform)
+    InsPart wp{lo, hi, tor, nd5, l == 0 ? runs : 0u, down ? 1u : 0u, SHARDS && multi ? 1u : 0u};
+    part_wave_join(wp);
+    if (l == 0) s_part[w] = wp;
     __syncthreads();
     if (threadIdx.x == 0) {
-        for (int k = 1; k < (int)(blockDim.x / WAVE); ++k) {
-            lo = s_min[k] < lo ? s_min[k] : lo;
-            hi = s_max[k] > hi ? s_max[k] : hi;
-        }
-        if (lo != ~0ull) atomicMin((unsigned long long*)&m->tmin_ord, (unsigned long long)lo);
-        if (hi != 0) atomicMax((unsigned long long*)&m->tmax_ord, (unsigned long long)hi);
+        InsPart p = s_part[0];
+        for (int k = 1; k < (int)(blockDim.x / WAVE); ++k) part_join(p, s_part[k]);
+        parts[blockIdx.x] = p;
     }
 }
 
-__global__ void __launch_bounds__(256) k_dict_compact(const u64* __restrict__ table, u64 slots, u32 max_j,
-                                                      SortMeta* m, u64* __restrict__ list)
+// The key's layout from the distinct ids (J) and the insert's findings (one thread).
+__device__ __forceinline__ void dict_meta(SortMeta* m, u32 J, u32 max_j, u32 n, u32 n_shards, u32 allow_wide)
 {
-    // one counter claim per workgroup and round (the list is sorted afterwards,
-    // so the order of the claims does not matter)
-    __shared__ u32 s_wc[256 / WAVE];
-    __shared__ u32 s_base;
-    u32 hm = m->has_min;
-    if (blockIdx.x == 0 && threadIdx.x == 0 && hm && max_j > 0) list[0] = EMPTY ^ SIGN;
-    const int w = threadIdx.x / WAVE;
-    const u64 stride = (u64)gridDim.x * blockDim.x;
-    for (u64 b = (u64)blockIdx.x * blockDim.x; b < slots; b += stride) {
-        const u64 s = b + threadIdx.x;
-        const u64 k = s < slots ? table[2 * s] : EMPTY;
-        const bool occ = k != EMPTY;
-        const u64 msk = __ballot(occ);
-        if (lane_id() == 0) s_wc[w] = (u32)__popcll(msk);
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            u32 t = 0;
-            for (int x = 0; x < 256 / WAVE; ++x) t += s_wc[x];
-            s_base = t ? atomicAdd(&m->list_count, t) : 0u;
-        }
-        __syncthreads();
-        u32 base = s_base;
-        for (int x = 0; x < w; ++x) base += s_wc[x];
-        if (occ) {
-            const u32 pos = base + popc_below(msk) + hm;
-            if (pos < max_j) list[pos] = k ^ SIGN;
-        }
-        __syncthreads();
-    }
-}
-
-__global__ void k_dict_meta(SortMeta* m, u32 max_j, u32 n, u32 n_shards, u32 allow_wide)
-{
-    if (threadIdx.x != 0) return;
-    u32 J = m->list_count + m->has_min;  // distinct ids counted by the compaction
     m->J = J;
     if (J > max_j) m->overflow = 1;
     m->dict_n = J < max_j ? J : max_j;
@@ -481,6 +466,67 @@ __global__ void k_dict_meta(SortMeta* m, u32 max_j, u32 n, u32 n_shards, u32 all
     const u32 w0 = (allow_wide && p0 == 0 && kb > RADIX_BITS && kb % RADIX_BITS == 1) ? RADIX_BITS + 1 : RADIX_BITS;
     m->w0 = w0;
     m->passes = kb == 0 ? 0u : (kb <= w0 ? 1u : 1u + (kb - w0 + RADIX_BITS - 1) / RADIX_BITS);
+}
+
+__global__ void __launch_bounds__(256) k_dict_compact(const u64* __restrict__ table, u64 slots, u32 max_j,
+                                                      SortMeta* m, u64* __restrict__ list,
+                                                      const InsPart* __restrict__ parts, u32 nparts, u32 n,
+                                                      u32 n_shards, u32 allow_wide)
+{
+    // one counter claim per workgroup and round (the list is sorted afterwards,
+    // so the order of the claims does not matter)
+    __shared__ u32 s_wc[256 / WAVE];
+    __shared__ u32 s_base;
+    u32 hm = m->has_min;
+    if (blockIdx.x == 0 && threadIdx.x == 0 && hm && max_j > 0) list[0] = EMPTY ^ SIGN;
+    const int w = threadIdx.x / WAVE;
+    const u64 stride = (u64)gridDim.x * blockDim.x;
+    for (u64 b = (u64)blockIdx.x * blockDim.x; b < slots; b += stride) {
+        const u64 s = b + threadIdx.x;
+        const u64 k = s < slots ? table[2 * s] : EMPTY;
+        const bool occ = k != EMPTY;
+        const u64 msk = __ballot(occ);
+        if (lane_id() == 0) s_wc[w] = (u32)__popcll(msk);
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            u32 t = 0;
+            for (int x = 0; x < 256 / WAVE; ++x) t += s_wc[x];
+            s_base = t ? atomicAdd(&m->list_count, t) : 0u;
+        }
+        __syncthreads();
+        u32 base = s_base;
+        for (int x = 0; x < w; ++x) base += s_wc[x];
+        if (occ) {
+            const u32 pos = base + popc_below(msk) + hm;
+            if (pos < max_j) list[pos] = k ^ SIGN;
+        }
+        __syncthreads();
+    }
+    // the last block to end joins the insert's per-block parts and fixes the
+    // key (a launch less than a kernel of its own)
+    if (threadIdx.x == 0) {
+        __threadfence();
+        s_base = atomicAdd(&m->blocks_done, 1u);
+    }
+    __syncthreads();
+    if (s_base != gridDim.x - 1) return;
+    __shared__ InsPart s_part[256 / WAVE];
+    InsPart p{~0ull, 0, 0, 0, 0, 0, 0};
+    for (u32 i = threadIdx.x; i < nparts; i += 256) part_join(p, parts[i]);
+    part_wave_join(p);
+    if (lane_id() == 0) s_part[w] = p;
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    for (int k = 1; k < 256 / WAVE; ++k) part_join(p, s_part[k]);
+    __threadfence();
+    m->tmin_ord = p.lo;
+    m->tmax_ord = p.hi;
+    m->t_or = p.tor;
+    m->t_nd5 = p.nd5;
+    m->n_runs = p.runs;
+    m->unordered = p.down;
+    m->multi_shard = p.multi;
+    dict_meta(m, atomicAdd(&m->list_count, 0u) + hm, max_j, n, n_shards, allow_wide);
 }
 
 // Batched form, after the distinct ids are sorted: each id's shard (its slot's
@@ -1392,14 +1438,18 @@ static cv_status sort_impl(const cv_records* in, const uint64_t* soff, uint32_t 
     const int gs = cvh::grid_for(n, 256, 2048);
     {
         cvh::TimedScope ts_("sort_prep", s);
-        hipLaunchKernelGGL(k_sort_init, dim3(1), dim3(64), 0, s, L.meta);
-        cvh::fill_u64(L.table, EMPTY, 2 * L.slots, s);
-        cvh::fill_u32(L.zero_begin, 0u, L.zero_bytes / 4, s);
+        // the insert's per-block parts lie in the second key buffer, which the
+        // passes write later (a block for at least 256 of its 8-byte words, and
+        // every buffer holds at least 256 bytes)
+        InsPart* parts = (InsPart*)L.K1;
+        static_assert(sizeof(InsPart) <= 256, "one part fits the smallest buffer");
+        const u64 fill_words = L.slots > L.zero_bytes / 4 ? L.slots : L.zero_bytes / 4;
+        hipLaunchKernelGGL(k_sort_begin, dim3(cvh::grid_for(fill_words, 256, 4096)), dim3(256), 0, s, L.meta, L.table,
+                           2 * L.slots, L.zero_begin, (u64)(L.zero_bytes / 4));
         hipLaunchKernelGGL(S > 1 ? k_dict_insert<true> : k_dict_insert<false>, dim3(gs), dim3(256), 0, s,
-                           in->journey_id, in->ts_ms, nn, L.table, mask, L.meta, soff, S);
+                           in->journey_id, in->ts_ms, nn, L.table, mask, L.meta, parts, soff, S);
         hipLaunchKernelGGL(k_dict_compact, dim3(cvh::grid_for(L.slots, 256, 2048)), dim3(256), 0, s, L.table,
-                           L.slots, mj, L.meta, L.dl0);
-        hipLaunchKernelGGL(k_dict_meta, dim3(1), dim3(64), 0, s, L.meta, mj, nn, S, sort_wide_first() ? 1u : 0u);
+                           L.slots, mj, L.meta, L.dl0, parts, (u32)gs, nn, S, sort_wide_first() ? 1u : 0u);
         // sort the distinct ids (64-bit, signed order via the flipped sign bit)
         const u32* dn = &L.meta->dict_n;
         radix_hist(L.dl0, mj, dn, MAX_PASSES, nullptr, L.dhist, cvh::grid_for(max_journeys, 256, 512), s);
