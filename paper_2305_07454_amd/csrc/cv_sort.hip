@@ -9,12 +9,14 @@
 //                     journey ids into an open-addressing hash set
 //                     (run-deduplicated), batched: each id's slot tagged with
 //                     its shard, an id met in two shards flagged;
-//   2. k_dict_compact distinct ids -> list; radix sort of the list (signed order);
-//   3. (its last block) journey count J, rank bits, time bits, key bits, passes;
-//   4. k_dict_rank    dense order-preserving rank of each distinct id; batched:
-//                     k_dict_shardkey + a stable sort by shard + k_dict_final,
-//                     ranks in (shard, id) order (the shard then needs no
-//                     bits of its own in the key unless an id spans shards);
+//   2. k_dict_compact distinct ids -> list; its last block settles the journey
+//                     count J, rank bits, time bits, key bits and passes;
+//   3. launch_dict_order
+//                     the list in signed order, batched: by (shard, id): one
+//                     block, sorted chunks and their join, or radix passes
+//                     (cv_dictsort.h);
+//   4.                and each id's dense rank in that order (the shard needs
+//                     no bits of its own in the key unless an id spans shards);
 //   5. k_pack_hist / k_pack_il
 //                     key = rank << t_bits | (ts - t_min) / factor (or the
 //                     rank alone for time-ordered input) and the digit
@@ -31,6 +33,7 @@
 #include <hip/hip_runtime.h>
 
 #include "cv_device.h"
+#include "cv_dictsort.h"
 #include "cv_host.h"
 #include "cv_kin.h"
 #include "cv_radix.h"
@@ -60,6 +63,7 @@ struct SortMeta {
     u32 ib;   // index bits of a packed key word
     u32 p0;   // first pass whose input words are packed (ib and p0 adjacent: the radix passes read both)
     u32 w0;   // bits of the first radix digit: 9 where that saves a pass (a key of 8k + 1 bits), else 8
+    u32 big_n;   // dict_n when the radix passes are to sort the distinct ids, else 0
     u32 blocks_done;  // blocks of the compaction that have ended
     u32 n_runs;  // runs of equal ids in input order (counted by the dictionary insert)
     u32 unordered;  // a timestamp below its predecessor's (same shard) in input order
@@ -428,6 +432,7 @@ __device__ __forceinline__ void dict_meta(SortMeta* m, u32 J, u32 max_j, u32 n, 
     m->J = J;
     if (J > max_j) m->overflow = 1;
     m->dict_n = J < max_j ? J : max_j;
+    m->big_n = m->dict_n > DS_ONE ? m->dict_n : 0u;
     u32 rb = J > 1 ? bit_width64((u64)J - 1) : 0;
     u64 span = n ? (unord_i64(m->tmax_ord) - (u64)unord_i64(m->tmin_ord)) : 0;
     // the offsets' common factor 2^a 5^b (1 when the time stamps are all equal)
@@ -468,57 +473,20 @@ __device__ __forceinline__ void dict_meta(SortMeta* m, u32 J, u32 max_j, u32 n, 
     m->passes = kb == 0 ? 0u : (kb <= w0 ? 1u : 1u + (kb - w0 + RADIX_BITS - 1) / RADIX_BITS);
 }
 
-__global__ void __launch_bounds__(256) k_dict_compact(const u64* __restrict__ table, u64 slots, u32 max_j,
-                                                      SortMeta* m, u64* __restrict__ list,
-                                                      const InsPart* __restrict__ parts, u32 nparts, u32 n,
-                                                      u32 n_shards, u32 allow_wide)
+// The insert's per-block parts joined, then the key's layout from `ids` distinct
+// ids (a whole block of B threads).
+template <int B>
+__device__ __forceinline__ void dict_settle(SortMeta* m, const InsPart* __restrict__ parts, u32 nparts, u32 ids,
+                                            u32 max_j, u32 n, u32 n_shards, u32 allow_wide)
 {
-    // one counter claim per workgroup and round (the list is sorted afterwards,
-    // so the order of the claims does not matter)
-    __shared__ u32 s_wc[256 / WAVE];
-    __shared__ u32 s_base;
-    u32 hm = m->has_min;
-    if (blockIdx.x == 0 && threadIdx.x == 0 && hm && max_j > 0) list[0] = EMPTY ^ SIGN;
-    const int w = threadIdx.x / WAVE;
-    const u64 stride = (u64)gridDim.x * blockDim.x;
-    for (u64 b = (u64)blockIdx.x * blockDim.x; b < slots; b += stride) {
-        const u64 s = b + threadIdx.x;
-        const u64 k = s < slots ? table[2 * s] : EMPTY;
-        const bool occ = k != EMPTY;
-        const u64 msk = __ballot(occ);
-        if (lane_id() == 0) s_wc[w] = (u32)__popcll(msk);
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            u32 t = 0;
-            for (int x = 0; x < 256 / WAVE; ++x) t += s_wc[x];
-            s_base = t ? atomicAdd(&m->list_count, t) : 0u;
-        }
-        __syncthreads();
-        u32 base = s_base;
-        for (int x = 0; x < w; ++x) base += s_wc[x];
-        if (occ) {
-            const u32 pos = base + popc_below(msk) + hm;
-            if (pos < max_j) list[pos] = k ^ SIGN;
-        }
-        __syncthreads();
-    }
-    // the last block to end joins the insert's per-block parts and fixes the
-    // key (a launch less than a kernel of its own)
-    if (threadIdx.x == 0) {
-        __threadfence();
-        s_base = atomicAdd(&m->blocks_done, 1u);
-    }
-    __syncthreads();
-    if (s_base != gridDim.x - 1) return;
-    __shared__ InsPart s_part[256 / WAVE];
+    __shared__ InsPart s_part[B / WAVE];
     InsPart p{~0ull, 0, 0, 0, 0, 0, 0};
-    for (u32 i = threadIdx.x; i < nparts; i += 256) part_join(p, parts[i]);
+    for (u32 i = threadIdx.x; i < nparts; i += B) part_join(p, parts[i]);
     part_wave_join(p);
-    if (lane_id() == 0) s_part[w] = p;
+    if (lane_id() == 0) s_part[threadIdx.x / WAVE] = p;
     __syncthreads();
     if (threadIdx.x != 0) return;
-    for (int k = 1; k < 256 / WAVE; ++k) part_join(p, s_part[k]);
-    __threadfence();
+    for (int k = 1; k < B / WAVE; ++k) part_join(p, s_part[k]);
     m->tmin_ord = p.lo;
     m->tmax_ord = p.hi;
     m->t_or = p.tor;
@@ -526,7 +494,140 @@ __global__ void __launch_bounds__(256) k_dict_compact(const u64* __restrict__ ta
     m->n_runs = p.runs;
     m->unordered = p.down;
     m->multi_shard = p.multi;
-    dict_meta(m, atomicAdd(&m->list_count, 0u) + hm, max_j, n, n_shards, allow_wide);
+    dict_meta(m, ids, max_j, n, n_shards, allow_wide);
+}
+
+// The dictionary's ids to a list (any order), batched: with their shards.  Each
+// thread takes CPT_D slots per round, so that a round's one claim of list
+// places (atomics on one word, which serialise) covers 1 024 slots.
+constexpr int CPT_D = 4;
+__global__ void __launch_bounds__(256) k_dict_compact(const u64* __restrict__ table, u64 slots, u32 max_j,
+                                                      SortMeta* m, u64* __restrict__ list, u64* __restrict__ tag,
+                                                      const InsPart* __restrict__ parts, u32 nparts, u32 n,
+                                                      u32 n_shards, u32 allow_wide)
+{
+    __shared__ u32 s_t[256 / WAVE];
+    __shared__ u32 s_base;
+    const u32 hm = m->has_min;
+    if (blockIdx.x == 0 && threadIdx.x == 0 && hm && max_j > 0) {
+        list[0] = EMPTY ^ SIGN;
+        if (tag) tag[0] = 0;
+    }
+    const ulonglong2* t2 = (const ulonglong2*)table;
+    const u64 stride = (u64)gridDim.x * 256 * CPT_D;
+    for (u64 b = (u64)blockIdx.x * 256 * CPT_D; b < slots; b += stride) {
+        ulonglong2 e[CPT_D];
+        u32 c = 0;
+#pragma unroll
+        for (int q = 0; q < CPT_D; ++q) {
+            const u64 sl = b + q * 256 + threadIdx.x;
+            e[q].x = EMPTY;
+            if (sl < slots) {
+                if (tag) e[q] = t2[sl];
+                else e[q].x = table[2 * sl];
+            }
+            c += e[q].x != EMPTY;
+        }
+        u32 tot;
+        const u32 ex = block_exclusive_sum<256>(c, s_t, tot);
+        if (threadIdx.x == 0) s_base = tot ? atomicAdd(&m->list_count, tot) : 0u;
+        __syncthreads();
+        u32 pos = s_base + ex + hm;
+#pragma unroll
+        for (int q = 0; q < CPT_D; ++q) {
+            if (e[q].x == EMPTY) continue;
+            if (pos < max_j) {
+                list[pos] = e[q].x ^ SIGN;
+                if (tag) tag[pos] = e[q].y;
+            }
+            ++pos;
+        }
+        __syncthreads();
+    }
+    // the last block to end settles the key (a launch less than a kernel of its own)
+    if (threadIdx.x == 0) {
+        __threadfence();
+        s_base = atomicAdd(&m->blocks_done, 1u);
+    }
+    __syncthreads();
+    if (s_base != gridDim.x - 1) return;
+    __threadfence();
+    dict_settle<256>(m, parts, nparts, atomicAdd(&m->list_count, 0u) + hm, max_j, n, n_shards, allow_wide);
+}
+
+// writes rank r of the id (image) into its slot
+__device__ __forceinline__ void dict_set_rank(u64* __restrict__ table, u64 mask, u64 image, u32 r)
+{
+    const u64 k = image ^ SIGN;
+    if (k == EMPTY) return;  // INT64_MIN has no slot
+    const u64 slot = dict_find(table, mask, k);
+    if (slot != ~0ull) table[2 * slot + 1] = r;
+}
+
+// Up to DS_ONE distinct ids, by one block: their order into out, their ranks
+// into the table.  ALL: the caller's capacity allows no more, and the block
+// also does the compaction's work (the table then has at most 2 DS_ONE slots).
+template <bool SH, bool ALL>
+__global__ void __launch_bounds__(DS_B) k_dict_one(SortMeta* m, u64* __restrict__ table, u64 mask,
+                                                   const u64* __restrict__ list, const u64* __restrict__ tag,
+                                                   u64* __restrict__ out, const InsPart* __restrict__ parts, u32 nparts,
+                                                   u32 max_j, u32 n, u32 n_shards, u32 allow_wide)
+{
+    __shared__ u64 s_k[DS_ONE];
+    __shared__ u32 s_s[SH ? DS_ONE : 1];
+    __shared__ u32 s_t[DS_B / WAVE];
+    if (ALL) {
+        const u32 hm = m->has_min;
+        u32 base = hm;
+        if (threadIdx.x == 0 && hm) {
+            s_k[0] = EMPTY ^ SIGN;
+            if (SH) s_s[0] = 0;
+        }
+        const ulonglong2* t2 = (const ulonglong2*)table;
+        for (u64 b = 0; b <= mask; b += DS_B) {  // slots are a multiple of DS_B
+            const ulonglong2 e = t2[b + threadIdx.x];
+            const bool occ = e.x != EMPTY;
+            u32 tot;
+            const u32 pos = base + block_exclusive_sum<DS_B>(occ ? 1u : 0u, s_t, tot);
+            if (occ && pos < max_j) {
+                s_k[pos] = e.x ^ SIGN;
+                if (SH) s_s[pos] = (u32)e.y;
+            }
+            base += tot;
+        }
+        dict_settle<DS_B>(m, parts, nparts, base, max_j, n, n_shards, allow_wide);
+        __syncthreads();
+        if (SH && m->multi_shard)
+            for (u32 i = threadIdx.x; i < DS_ONE; i += DS_B) s_s[i] = 0;
+        __syncthreads();
+    }
+    const u32 c = m->dict_n;
+    if (c > DS_ONE) return;
+    if (!ALL) {
+        const bool one = SH && m->multi_shard;
+        for (u32 i = threadIdx.x; i < c; i += DS_B) {
+            s_k[i] = list[i];
+            if (SH) s_s[i] = one ? 0u : (u32)tag[i];
+        }
+        __syncthreads();
+    }
+    ds_block_sort<SH>(s_k, s_s, c);
+    for (u32 r = threadIdx.x; r < c; r += DS_B) {
+        out[r] = s_k[r];
+        dict_set_rank(table, mask, s_k[r], r);
+    }
+}
+
+// A step of the chunks' join (cv_dictsort.h); the last one also writes the ranks.
+template <bool SH, bool LAST>
+__global__ void __launch_bounds__(256) k_dict_join(const SortMeta* m, u64* __restrict__ table, u64 mask,
+                                                   const u64* __restrict__ in, const u64* __restrict__ tin, u32 run,
+                                                   u64* __restrict__ out, u64* __restrict__ tout)
+{
+    const u32 n = m->big_n;
+    ds_join<SH>(in, tin, n, run, out, tout, [&](u32 r, u64 id) {
+        if (LAST) dict_set_rank(table, mask, id, r);
+    });
 }
 
 // Batched form, after the distinct ids are sorted: each id's shard (its slot's
@@ -536,7 +637,7 @@ __global__ void __launch_bounds__(256) k_dict_compact(const u64* __restrict__ ta
 __global__ void __launch_bounds__(256) k_dict_shardkey(const u64* __restrict__ sorted_list, const SortMeta* m,
                                                        const u64* __restrict__ table, u64 mask, u64* __restrict__ skey)
 {
-    const u32 dn = m->dict_n;
+    const u32 dn = m->big_n;
     const bool multi = m->multi_shard != 0;
     for (u32 r = blockIdx.x * blockDim.x + threadIdx.x; r < dn; r += gridDim.x * blockDim.x) {
         const u64 k = sorted_list[r] ^ SIGN;
@@ -555,26 +656,20 @@ __global__ void __launch_bounds__(256) k_dict_final(const u64* __restrict__ sort
                                                     const SortMeta* m, u64* __restrict__ table, u64 mask,
                                                     u64* __restrict__ final_list)
 {
-    const u32 dn = m->dict_n;
+    const u32 dn = m->big_n;
     for (u32 r = blockIdx.x * blockDim.x + threadIdx.x; r < dn; r += gridDim.x * blockDim.x) {
         const u64 v = sorted_list[perm[r]];
         final_list[r] = v;
-        const u64 k = v ^ SIGN;
-        if (k == EMPTY) continue;
-        const u64 slot = dict_find(table, mask, k);
-        if (slot != ~0ull) table[2 * slot + 1] = r;
+        dict_set_rank(table, mask, v, r);
     }
 }
 
 __global__ void __launch_bounds__(256) k_dict_rank(const u64* __restrict__ sorted_list, const SortMeta* m,
                                                    u64* __restrict__ table, u64 mask)
 {
-    u32 dn = m->dict_n;
+    u32 dn = m->big_n;
     for (u32 r = blockIdx.x * blockDim.x + threadIdx.x; r < dn; r += gridDim.x * blockDim.x) {
-        u64 k = sorted_list[r] ^ SIGN;
-        if (k == EMPTY) continue;
-        u64 s = dict_find(table, mask, k);
-        if (s != ~0ull) table[2 * s + 1] = r;
+        dict_set_rank(table, mask, sorted_list[r], r);
     }
 }
 
@@ -1404,6 +1499,74 @@ __global__ void __launch_bounds__(256) k_gather_feat(u32 n, const SortMeta* m, c
     }
 }
 
+// The distinct ids in order (with several shards: by shard, then id) and their
+// ranks in the table.  See cv_dictsort.h for where the lines between the three
+// ways lie; the ids' count is known on the device alone, so a kernel of a way
+// that it does not choose leaves at once.
+template <bool SH>
+void launch_dict_order_as(const SortLayout& L, u32 mj, u32 n, u32 S, u64 mask, const InsPart* parts, u32 nparts,
+                          hipStream_t s)
+{
+    const u32 wide = sort_wide_first() ? 1u : 0u;
+    u64* out = SH ? L.dlf : L.dl0;
+    u64* tag = SH ? L.dsk0 : nullptr;
+    if (mj <= DS_ONE) {
+        hipLaunchKernelGGL((k_dict_one<SH, true>), dim3(1), dim3(DS_B), 0, s, L.meta, L.table, mask, L.dl0, tag, out,
+                           parts, nparts, mj, n, S, wide);
+        return;
+    }
+    hipLaunchKernelGGL(k_dict_compact, dim3(cvh::grid_for(L.slots, 256 * CPT_D, 2048)), dim3(256), 0, s, L.table,
+                       L.slots, mj, L.meta, L.dl0, tag, parts, nparts, n, S, wide);
+    hipLaunchKernelGGL((k_dict_one<SH, false>), dim3(1), dim3(DS_B), 0, s, L.meta, L.table, mask, L.dl0, tag, out,
+                       parts, nparts, mj, n, S, wide);
+    const u32* big = &L.meta->big_n;
+    if (mj <= DS_MERGE) {
+        const dim3 jg((unsigned)cvh::grid_for(mj, 256, 2048));
+        const u32 group = DS_ONE * DS_FAN;
+        // the last step writes `out`, so one step alone starts from another buffer
+        u64* chunks = (!SH && mj <= group) ? L.dl1 : L.dl0;
+        hipLaunchKernelGGL(k_ds_chunks<SH>, dim3((mj + DS_ONE - 1) / DS_ONE), dim3(DS_B), 0, s, L.dl0, chunks, tag, big,
+                           &L.meta->multi_shard);
+        static_assert(DS_MERGE <= (u64)DS_ONE * DS_FAN * DS_FAN, "two steps join every chunk");
+        if (mj <= group) {
+            hipLaunchKernelGGL((k_dict_join<SH, true>), jg, dim3(256), 0, s, L.meta, L.table, mask, chunks, tag,
+                               DS_ONE, out, (u64*)nullptr);
+            return;
+        }
+        hipLaunchKernelGGL((k_dict_join<SH, false>), jg, dim3(256), 0, s, L.meta, L.table, mask, chunks, tag, DS_ONE,
+                           L.dl1, SH ? L.dsk1 : nullptr);
+        hipLaunchKernelGGL((k_dict_join<SH, true>), jg, dim3(256), 0, s, L.meta, L.table, mask, L.dl1,
+                           SH ? L.dsk1 : nullptr, group, out, (u64*)nullptr);
+        return;
+    }
+    // radix passes over the ids (64-bit, signed order via the flipped sign bit)
+    radix_hist(L.dl0, mj, big, MAX_PASSES, nullptr, L.dhist, cvh::grid_for(mj, 256, 512), s);
+    radix_scan(L.dhist, L.doffs, MAX_PASSES, s);
+    radix_passes(L.dl0, L.dl1, nullptr, L.dv0, L.dv1, mj, big, nullptr, MAX_PASSES, L.doffs, L.dstatus,
+                 L.meta->tickets + MAX_PASSES, s);
+    const int dg = cvh::grid_for(mj, 256, 1024);
+    if (SH) {
+        // the id-sorted list, stably by shard: (shard, id) order, and ranks in it
+        const int sp = (int)((bit_width_host((u64)S - 1) + RADIX_BITS - 1) / RADIX_BITS);
+        hipLaunchKernelGGL(k_dict_shardkey, dim3(dg), dim3(256), 0, s, L.dl0, L.meta, L.table, mask, L.dsk0);
+        radix_hist(L.dsk0, mj, big, sp, nullptr, L.shist, cvh::grid_for(mj, 256, 512), s);
+        radix_scan(L.shist, L.soffs, sp, s);
+        radix_passes(L.dsk0, L.dsk1, nullptr, L.dv0, L.dv1, mj, big, nullptr, sp, L.soffs, L.sstatus,
+                     L.meta->tickets + 2 * MAX_PASSES, s);
+        hipLaunchKernelGGL(k_dict_final, dim3(dg), dim3(256), 0, s, L.dl0, (sp & 1) ? L.dv1 : L.dv0, L.meta, L.table,
+                           mask, L.dlf);
+    } else {
+        hipLaunchKernelGGL(k_dict_rank, dim3(dg), dim3(256), 0, s, L.dl0, L.meta, L.table, mask);
+    }
+}
+
+void launch_dict_order(const SortLayout& L, u32 mj, u32 n, u32 S, u64 mask, const InsPart* parts, u32 nparts,
+                       hipStream_t s)
+{
+    if (S > 1) launch_dict_order_as<true>(L, mj, n, S, mask, parts, nparts, s);
+    else launch_dict_order_as<false>(L, mj, n, S, mask, parts, nparts, s);
+}
+
 }  // namespace
 
 static cv_status sort_impl(const cv_records* in, const uint64_t* soff, uint32_t S, uint64_t max_journeys, uint32_t* perm,
@@ -1448,29 +1611,7 @@ static cv_status sort_impl(const cv_records* in, const uint64_t* soff, uint32_t 
                            2 * L.slots, L.zero_begin, (u64)(L.zero_bytes / 4));
         hipLaunchKernelGGL(S > 1 ? k_dict_insert<true> : k_dict_insert<false>, dim3(gs), dim3(256), 0, s,
                            in->journey_id, in->ts_ms, nn, L.table, mask, L.meta, parts, soff, S);
-        hipLaunchKernelGGL(k_dict_compact, dim3(cvh::grid_for(L.slots, 256, 2048)), dim3(256), 0, s, L.table,
-                           L.slots, mj, L.meta, L.dl0, parts, (u32)gs, nn, S, sort_wide_first() ? 1u : 0u);
-        // sort the distinct ids (64-bit, signed order via the flipped sign bit)
-        const u32* dn = &L.meta->dict_n;
-        radix_hist(L.dl0, mj, dn, MAX_PASSES, nullptr, L.dhist, cvh::grid_for(max_journeys, 256, 512), s);
-        radix_scan(L.dhist, L.doffs, MAX_PASSES, s);
-        radix_passes(L.dl0, L.dl1, nullptr, L.dv0, L.dv1, mj, dn, nullptr, MAX_PASSES, L.doffs, L.dstatus,
-                     L.meta->tickets + MAX_PASSES, s);
-        if (S > 1) {
-            // the id-sorted list, stably by shard: (shard, id) order, and ranks in it
-            const int sp = (int)((bit_width_host((u64)S - 1) + RADIX_BITS - 1) / RADIX_BITS);
-            const int dg = cvh::grid_for(max_journeys, 256, 1024);
-            hipLaunchKernelGGL(k_dict_shardkey, dim3(dg), dim3(256), 0, s, L.dl0, L.meta, L.table, mask, L.dsk0);
-            radix_hist(L.dsk0, mj, dn, sp, nullptr, L.shist, cvh::grid_for(max_journeys, 256, 512), s);
-            radix_scan(L.shist, L.soffs, sp, s);
-            radix_passes(L.dsk0, L.dsk1, nullptr, L.dv0, L.dv1, mj, dn, nullptr, sp, L.soffs, L.sstatus,
-                         L.meta->tickets + 2 * MAX_PASSES, s);
-            hipLaunchKernelGGL(k_dict_final, dim3(dg), dim3(256), 0, s, L.dl0, (sp & 1) ? L.dv1 : L.dv0, L.meta,
-                               L.table, mask, L.dlf);
-        } else {
-            hipLaunchKernelGGL(k_dict_rank, dim3(cvh::grid_for(max_journeys, 256, 1024)), dim3(256), 0, s, L.dl0,
-                               L.meta, L.table, mask);
-        }
+        launch_dict_order(L, mj, nn, S, mask, parts, (u32)gs, s);
         // interleaved input (short runs of equal ids): the payload packed per
         // record for the fused gather, in the same pass
         hipLaunchKernelGGL(S > 1 ? k_pack_hist<true> : k_pack_hist<false>, dim3(gs), dim3(256), 0, s, in->journey_id,
