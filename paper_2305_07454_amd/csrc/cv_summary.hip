@@ -26,8 +26,21 @@ using namespace cv;
 namespace {
 
 constexpr int SB = 256;
-constexpr int SI = 64;
-constexpr int ST = SB * SI;
+// Windows of 64 records that a wave walks, by the record count.  A wave goes
+// through its windows one after the other, so a small call is bound by one
+// wave's walk unless the records are split finer; a large one pays for finer
+// chunks with more journeys that cross a chunk edge (merged by atomics).
+//   SI_S  up to N_S records: 2 048 per block; every block sums the (at most
+//         2 048) journey counts before its own itself, and both reductions
+//         run in one launch, which saves two launches as well;
+//   SI_M  up to N_M records;
+//   SI_L  above.
+// Whole summary, SI_S / SI_M / SI_L: 33 k records 26 / 48 / 105 us, 1 M 34 / 56 /
+// 124, 4 M 82 / 80 / 140, 8 M 162 / 143 / 162, 32 M 368 / 358 / 367, a 30 M batch
+// of shards 639 / 366 / 393; 100 M records 948 / 931 / 933 and a 200 M batch
+// - / 2 238 / 1 960.
+constexpr int SI_S = 8, SI_M = 16, SI_L = 64;
+constexpr u64 N_S = 4ull << 20, N_M = 32ull << 20;
 constexpr int FX_DIST = SUM_FX_DIST;  // distance: 2^-128 m resolution (exact for steps >= 2^-75 m)
 constexpr int FX_SPD = SUM_FX_SPD;    // speed: exact for every float32
 
@@ -36,9 +49,8 @@ struct SumMeta {
 };
 
 constexpr int NW = SB / WAVE;  // waves per block
-constexpr int WI = SI;         // windows of 64 records per wave
-constexpr int WCH = WAVE * WI; // records per wave
-static_assert(ST == NW * WCH, "tile = waves x wave chunk");
+// a tile is NW wave chunks of WAVE * SI records
+constexpr u64 sum_tiles(u64 n, int si) { return (n + (u64)SB * si - 1) / ((u64)SB * si); }
 
 // Journey starts among the records of window [a, a + 64) of a wave that walks
 // consecutive windows, from this lane's id jv (already loaded): jprev is the
@@ -61,9 +73,11 @@ __device__ __forceinline__ u64 heads_of(i64 jv, u64 a, u64 end, i64& jprev, cons
 
 // journey starts per wave chunk of WCH records: wcnt[tile * NW + wave], and
 // per tile: tcnt[tile]
+template <int SI>
 __global__ void __launch_bounds__(SB) k_sum_count(const i64* __restrict__ jid, u32 n, u32* __restrict__ wcnt,
                                                   u32* __restrict__ tcnt, const u64* __restrict__ soff, u32 S)
 {
+    constexpr int WCH = WAVE * SI, ST = SB * SI;
     __shared__ u32 s_w[NW];
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);  // wave-uniform
     const u64 cs = (u64)blockIdx.x * ST + (u64)w * WCH;
@@ -95,21 +109,24 @@ __global__ void __launch_bounds__(SB) k_sum_count(const i64* __restrict__ jid, u
 
 // The same counts from the features' FIRST flags (set exactly at journey and
 // shard starts): one byte per record instead of an id and its predecessor.
+template <int SI>
 __global__ void __launch_bounds__(SB) k_sum_count_flags(const uint8_t* __restrict__ flags, u32 n,
                                                         u32* __restrict__ wcnt, u32* __restrict__ tcnt)
 {
+    constexpr int WCH = WAVE * SI, ST = SB * SI;
     __shared__ u32 s_w[NW];
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
     const u64 cs = (u64)blockIdx.x * ST + (u64)w * WCH;
     const u64 ce = cs + WCH < n ? cs + WCH : (u64)n;
     constexpr int FB = WCH / WAVE;  // flag bytes per lane
-    static_assert(FB % 16 == 0 && CV_FLAG_FIRST == 1u, "whole 16-byte loads per lane; FIRST is bit 0");
+    static_assert((FB == 8 || FB % 16 == 0) && CV_FLAG_FIRST == 1u, "whole 8- or 16-byte loads per lane; FIRST is bit 0");
     u32 c = 0;
     if (cs < ce) {
-        // lane l counts the chunk's bytes [FB l, FB l + FB): 16-byte loads
-        // when the chunk is whole and the column 16-byte aligned
+        // lane l counts the chunk's bytes [FB l, FB l + FB): 16-byte (8-byte)
+        // loads when the chunk is whole and the column 16-byte aligned
         const u64 b0 = cs + (u64)lane_id() * FB;
         if (ce - cs == (u64)WCH && ((uintptr_t)flags & 15u) == 0) {
+            if (FB == 8) c = (u32)__popcll(*reinterpret_cast<const u64*>(flags + b0) & 0x0101010101010101ull);
 #pragma unroll
             for (int q = 0; q < FB / 16; ++q) {
                 const uint4 v = *reinterpret_cast<const uint4*>(flags + b0 + 16 * q);
@@ -172,10 +189,29 @@ __device__ __forceinline__ void jacc_identity(JAcc& a)
     a.gfirst = 0;
 }
 
-__global__ void __launch_bounds__(256) k_sum_init(JAcc* __restrict__ acc, AccX* __restrict__ accx, const SumMeta* meta,
-                                                 u32 cap)
+// sum of c[0, tiles) over the block (SB threads), in every thread
+__device__ __forceinline__ u32 block_count_sum(const u32* __restrict__ c, u32 tiles, u32* s_t)
 {
-    u32 J = meta->J;
+    u32 v = 0;
+    for (u32 i = threadIdx.x; i < tiles; i += SB) v += c[i];
+    u32 total;
+    block_exclusive_sum<SB>(v, s_t, total);
+    return total;
+}
+
+// tcnt (nullable): the tiles' journey counts, whose sum is J (the small form);
+// else meta holds it
+__global__ void __launch_bounds__(SB) k_sum_init(JAcc* __restrict__ acc, AccX* __restrict__ accx, SumMeta* meta,
+                                                u32 cap, const u32* __restrict__ tcnt, u32 tiles)
+{
+    __shared__ u32 s_t[NW];
+    u32 J;
+    if (tcnt) {
+        J = block_count_sum(tcnt, tiles, s_t);
+        if (blockIdx.x == 0 && threadIdx.x == 0) meta->J = J;
+    } else {
+        J = meta->J;
+    }
     u32 m = J < cap ? J : cap;
     for (u32 j = blockIdx.x * blockDim.x + threadIdx.x; j < m; j += gridDim.x * blockDim.x) {
         JAcc a;
@@ -458,22 +494,24 @@ __device__ __forceinline__ void flush_part(JAcc* acc, u32 cap, u32 j, const Part
 // FL = true: journey starts are read from the features' FIRST flags instead
 // of comparing ids (the box pass then loads an id only at a journey start,
 // to write it out).
-template <bool BOX, bool SHARDS, bool FL = false>
-__global__ void __launch_bounds__(SB) k_sum_reduce(u32 n, const i64* __restrict__ jid, const double* __restrict__ lat,
-                                                   const double* __restrict__ lon, const float* __restrict__ spd, const double* __restrict__ step,
-                                                   const double* __restrict__ dspd, const uint8_t* __restrict__ flags,
-                                                   const u32* __restrict__ tile_prefix, const u32* __restrict__ wcnt,
-                                                   u32 cap, Out o, JAcc* __restrict__ acc, AccX* __restrict__ accx,
-                                                   const u64* __restrict__ soff, u32 S, u64* __restrict__ jo)
+// seen: journey starts before the block's tile.
+template <bool BOX, bool SHARDS, bool FL, int SI>
+__device__ __forceinline__ void sum_reduce(u32 n, const i64* __restrict__ jid, const double* __restrict__ lat,
+                                           const double* __restrict__ lon, const float* __restrict__ spd,
+                                           const double* __restrict__ step, const double* __restrict__ dspd,
+                                           const uint8_t* __restrict__ flags, u32 seen, const u32* __restrict__ wcnt,
+                                           u32 cap, Out o, JAcc* __restrict__ acc, AccX* __restrict__ accx,
+                                           const u64* __restrict__ soff, u32 S, u64* __restrict__ jo)
 {
     using P = typename std::conditional<BOX, PartBox, PartSum>::type;
+    constexpr int WI = SI, WCH = WAVE * SI, ST = SB * SI;
     if (!SHARDS) S = 0;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);  // wave-uniform
     const int l = lane_id();
     const u64 cs = (u64)blockIdx.x * ST + (u64)w * WCH;  // wave chunk start
     const u64 ce = cs + WCH < n ? cs + WCH : (u64)n;      // wave chunk end (may be <= cs)
     if (cs >= ce) return;
-    u32 seen = tile_prefix[blockIdx.x];  // journey starts before the current window
+    // (from here on: journey starts before the current window)
     for (int k = 0; k < w; ++k) seen += wcnt[(u64)blockIdx.x * NW + k];
 
     P p;
@@ -607,6 +645,40 @@ __global__ void __launch_bounds__(SB) k_sum_reduce(u32 n, const i64* __restrict_
     }
 }
 
+template <bool BOX, bool SHARDS, bool FL, int SI>
+__global__ void __launch_bounds__(SB) k_sum_reduce(u32 n, const i64* __restrict__ jid, const double* __restrict__ lat,
+                                                   const double* __restrict__ lon, const float* __restrict__ spd,
+                                                   const double* __restrict__ step, const double* __restrict__ dspd,
+                                                   const uint8_t* __restrict__ flags,
+                                                   const u32* __restrict__ tile_prefix, const u32* __restrict__ wcnt,
+                                                   u32 cap, Out o, JAcc* __restrict__ acc, AccX* __restrict__ accx,
+                                                   const u64* __restrict__ soff, u32 S, u64* __restrict__ jo)
+{
+    sum_reduce<BOX, SHARDS, FL, SI>(n, jid, lat, lon, spd, step, dspd, flags, tile_prefix[blockIdx.x], wcnt, cap, o, acc,
+                                    accx, soff, S, jo);
+}
+
+// The small form: both reductions in one launch (grid row 0 the box, row 1 the
+// sums), the journeys before the tile counted here.
+template <bool SHARDS, bool FL>
+__global__ void __launch_bounds__(SB) k_sum_both(u32 n, const i64* __restrict__ jid, const double* __restrict__ lat,
+                                                 const double* __restrict__ lon, const float* __restrict__ spd,
+                                                 const double* __restrict__ step, const double* __restrict__ dspd,
+                                                 const uint8_t* __restrict__ flags, const u32* __restrict__ tcnt,
+                                                 const u32* __restrict__ wcnt, u32 cap, Out o, JAcc* __restrict__ acc,
+                                                 AccX* __restrict__ accx, const u64* __restrict__ soff, u32 S,
+                                                 u64* __restrict__ jo)
+{
+    __shared__ u32 s_t[NW];
+    const u32 seen = block_count_sum(tcnt, blockIdx.x, s_t);
+    if (blockIdx.y == 0)
+        sum_reduce<true, SHARDS, FL, SI_S>(n, jid, lat, lon, spd, step, dspd, flags, seen, wcnt, cap, o, acc, accx,
+                                           soff, S, jo);
+    else
+        sum_reduce<false, SHARDS, FL, SI_S>(n, jid, lat, lon, spd, step, dspd, flags, seen, wcnt, cap, o, acc, accx,
+                                            soff, S, jo);
+}
+
 __global__ void __launch_bounds__(256) k_sum_finalize(const JAcc* __restrict__ acc, const AccX* __restrict__ accx,
                                                       const SumMeta* meta, u32 cap,
                                                       Out o, const i64* __restrict__ ts, cv_result* res,
@@ -670,10 +742,10 @@ struct SumLayout {
     AccX* accx;
     u64 tiles;
     size_t bytes;
-    SumLayout(void* ws, u64 n, u64 cap)
+    SumLayout(void* ws, u64 n, u64 cap, int si = SI_L)
     {
         cvh::Carver c(ws);
-        tiles = (n + ST - 1) / ST;
+        tiles = sum_tiles(n, si);
         meta = c.take<SumMeta>(1);
         wcnt = c.take<u32>(tiles * NW);
         tcnt = c.take<u32>(tiles + 1);
@@ -683,6 +755,76 @@ struct SumLayout {
         bytes = c.size();
     }
 };
+
+// windows per wave for n records (see SI_S); a workspace that holds only the
+// coarsest form's tile counts gets that form
+int sum_windows(u64 n, u64 cap, size_t ws_bytes)
+{
+    const int si = n <= N_S ? SI_S : (n <= N_M ? SI_M : SI_L);
+    return SumLayout(nullptr, n, cap, si).bytes <= ws_bytes ? si : SI_L;
+}
+
+// bytes that hold every form for every record count up to n
+size_t sum_bytes(u64 n, u64 cap)
+{
+    const size_t l = SumLayout(nullptr, n, cap).bytes;
+    const size_t small = SumLayout(nullptr, n < N_S ? n : N_S, 0, SI_S).bytes;
+    const size_t mid = SumLayout(nullptr, n < N_M ? n : N_M, 0, SI_M).bytes;
+    return l + (small > mid ? small : mid);
+}
+
+struct SumArgs {
+    const cv_records* r;
+    const cv_features* f;
+    const SumLayout* L;
+    u32 cap;
+    Out o;
+    JAcc* acc;
+    AccX* accx;
+    const u64* soff;
+    u32 S;
+    u64* jo;
+    hipStream_t s;
+};
+
+// tile counts, J, the rows' identities and both reductions, SI windows per wave.
+// FL: journey starts from the FIRST flags, else from the ids.
+template <bool SHARDS, bool FL, int SI>
+void sum_launch_as(const SumArgs& a)
+{
+    const u32 n = (u32)a.r->n, tiles = (u32)a.L->tiles;
+    const SumLayout& L = *a.L;
+    if (FL)
+        hipLaunchKernelGGL((k_sum_count_flags<SI>), dim3(tiles), dim3(SB), 0, a.s, a.f->flags, n, L.wcnt, L.tcnt);
+    else
+        hipLaunchKernelGGL((k_sum_count<SI>), dim3(tiles), dim3(SB), 0, a.s, a.r->journey_id, n, L.wcnt, L.tcnt, a.soff,
+                           a.S);
+    constexpr bool small = SI == SI_S;
+    if (!small)
+        hipLaunchKernelGGL(k_tile_scan, dim3(1), dim3(SCAN_B), 0, a.s, L.tcnt, L.tile_prefix, tiles, L.meta);
+    hipLaunchKernelGGL(k_sum_init, dim3(cvh::grid_for(a.cap, SB, small ? 256 : 2048)), dim3(SB), 0, a.s, a.acc, a.accx,
+                       L.meta, a.cap, small ? L.tcnt : (const u32*)nullptr, tiles);
+    if (small) {
+        hipLaunchKernelGGL((k_sum_both<SHARDS, FL>), dim3(tiles, 2), dim3(SB), 0, a.s, n, a.r->journey_id, a.r->lat_deg,
+                           a.r->lon_deg, a.r->speed_mps, a.f->step_m, a.f->speed_mps, a.f->flags, L.tcnt, L.wcnt, a.cap,
+                           a.o, a.acc, a.accx, a.soff, a.S, a.jo);
+        return;
+    }
+    hipLaunchKernelGGL((k_sum_reduce<true, SHARDS, FL, SI>), dim3(tiles), dim3(SB), 0, a.s, n, a.r->journey_id,
+                       a.r->lat_deg, a.r->lon_deg, a.r->speed_mps, a.f->step_m, a.f->speed_mps, a.f->flags,
+                       L.tile_prefix, L.wcnt, a.cap, a.o, a.acc, a.accx, a.soff, a.S, a.jo);
+    hipLaunchKernelGGL((k_sum_reduce<false, SHARDS, FL, SI>), dim3(tiles), dim3(SB), 0, a.s, n, a.r->journey_id,
+                       a.r->lat_deg, a.r->lon_deg, a.r->speed_mps, a.f->step_m, a.f->speed_mps, a.f->flags,
+                       L.tile_prefix, L.wcnt, a.cap, a.o, a.acc, a.accx, a.soff, a.S, a.jo);
+}
+
+template <bool SHARDS, bool FL>
+void sum_launch(const SumArgs& a, int si)
+{
+    if (si == SI_S) sum_launch_as<SHARDS, FL, SI_S>(a);
+    else if (si == SI_M) sum_launch_as<SHARDS, FL, SI_M>(a);
+    else sum_launch_as<SHARDS, FL, SI_L>(a);
+}
 
 }  // namespace
 
@@ -708,7 +850,8 @@ static cv_status summary_impl(const cv_records* sorted, const cv_features* feat,
                          !out->distance_m || !out->sum_speed || !out->max_speed || !out->max_derived_speed ||
                          !out->n_dt_zero || !out->lat_min || !out->lat_max || !out->lon_min || !out->lon_max))
         return CV_ERR_INVALID_ARGUMENT;
-    SumLayout L(ws, n, capacity);
+    const int si = sum_windows(n, capacity, ws_bytes);
+    SumLayout L(ws, n, capacity, si);
     Out o{out->journey_id, out->first, out->n_points, out->t_start_ms, out->t_end_ms, out->distance_m,
           out->sum_speed, out->max_speed, out->max_derived_speed, out->n_dt_zero, out->lat_min, out->lat_max,
           out->lon_min, out->lon_max};
@@ -717,16 +860,9 @@ static cv_status summary_impl(const cv_records* sorted, const cv_features* feat,
     cvh::TimedScope ts_("summary", s);
     // journey starts come from the features' FIRST flags here (the features
     // of these records mark exactly the journey and shard starts)
-    hipLaunchKernelGGL(k_sum_count_flags, dim3((unsigned)L.tiles), dim3(SB), 0, s, feat->flags, nn, L.wcnt, L.tcnt);
-    hipLaunchKernelGGL(k_tile_scan, dim3(1), dim3(SCAN_B), 0, s, L.tcnt, L.tile_prefix, (u32)L.tiles, L.meta);
-    hipLaunchKernelGGL(k_sum_init, dim3(cvh::grid_for(cap, 256, 2048)), dim3(256), 0, s, L.acc, L.accx, L.meta, cap);
-    for (const bool box : {true, false}) {
-        auto kern = box ? (S > 1 ? k_sum_reduce<true, true, true> : k_sum_reduce<true, false, true>)
-                        : (S > 1 ? k_sum_reduce<false, true, true> : k_sum_reduce<false, false, true>);
-        hipLaunchKernelGGL(kern, dim3((unsigned)L.tiles), dim3(SB), 0, s, nn, sorted->journey_id, sorted->lat_deg,
-                           sorted->lon_deg, sorted->speed_mps, feat->step_m, feat->speed_mps, feat->flags,
-                           L.tile_prefix, L.wcnt, cap, o, L.acc, L.accx, soff, S, jo);
-    }
+    const SumArgs a{sorted, feat, &L, cap, o, L.acc, L.accx, soff, S, jo, s};
+    if (S > 1) sum_launch<true, true>(a, si);
+    else sum_launch<false, true>(a, si);
     hipLaunchKernelGGL(k_sum_finalize, dim3(cvh::grid_for(cap, 256, 2048)), dim3(256), 0, s, L.acc, L.accx, L.meta, cap, o,
                        sorted->ts_ms, res, soff, S, jo, nn);
     cvh::debug_rows(out->journey_id, nullptr, nullptr, res, cap, jo, S, CV_DEBUG_JOURNEY_ORDER, s);
@@ -767,30 +903,16 @@ void* noalloc_scratch()
 
 namespace cv {
 
-size_t sum_partials_bytes(u64 n)
-{
-    SumLayout L(nullptr, n, 0);
-    return L.bytes;
-}
+size_t sum_partials_bytes(u64 n) { return sum_bytes(n, 0); }
 
 cv_status sum_partials(const cv_records* sorted, const cv_features* feat, u32 rows, JAcc* acc, AccX* accx, void* ws,
                        hipStream_t s)
 {
     const u64 n = sorted->n;
     if (n == 0) return CV_OK;
-    SumLayout L(ws, n, 0);
-    Out o{};
-    const u32 nn = (u32)n;
-    hipLaunchKernelGGL(k_sum_count, dim3((unsigned)L.tiles), dim3(SB), 0, s, sorted->journey_id, nn, L.wcnt, L.tcnt,
-                       nullptr, 0u);
-    hipLaunchKernelGGL(k_tile_scan, dim3(1), dim3(SCAN_B), 0, s, L.tcnt, L.tile_prefix, (u32)L.tiles, L.meta);
-    hipLaunchKernelGGL(k_sum_init, dim3(cvh::grid_for(rows, 256, 2048)), dim3(256), 0, s, acc, accx, L.meta, rows);
-    hipLaunchKernelGGL((k_sum_reduce<true, false>), dim3((unsigned)L.tiles), dim3(SB), 0, s, nn, sorted->journey_id,
-                       sorted->lat_deg, sorted->lon_deg, sorted->speed_mps, feat->step_m, feat->speed_mps,
-                       feat->flags, L.tile_prefix, L.wcnt, rows, o, acc, accx, nullptr, 0u, nullptr);
-    hipLaunchKernelGGL((k_sum_reduce<false, false>), dim3((unsigned)L.tiles), dim3(SB), 0, s, nn, sorted->journey_id,
-                       sorted->lat_deg, sorted->lon_deg, sorted->speed_mps, feat->step_m, feat->speed_mps,
-                       feat->flags, L.tile_prefix, L.wcnt, rows, o, acc, accx, nullptr, 0u, nullptr);
+    const int si = sum_windows(n, 0, ~(size_t)0);
+    SumLayout L(ws, n, 0, si);
+    sum_launch<false, false>(SumArgs{sorted, feat, &L, rows, Out{}, acc, accx, nullptr, 0u, nullptr, s}, si);
     return cvh::last_launch_status();
 }
 
@@ -801,8 +923,7 @@ extern "C" {
 cv_status cv_summary_workspace_size(uint64_t n, uint64_t capacity, size_t* bytes)
 {
     if (!bytes || n >= (1ull << 32)) return CV_ERR_INVALID_ARGUMENT;
-    SumLayout L(nullptr, n, capacity);
-    *bytes = L.bytes;
+    *bytes = sum_bytes(n, capacity);
     return CV_OK;
 }
 
