@@ -4,20 +4,20 @@
 // before any record's key, so what it costs is launches and latency, not
 // bytes: eight radix passes with their histogram and scan took 11 launches and
 // about 110 us of every sort.  Here:
-//   up to DS_ONE ids     one block sorts them in LDS (a bitonic network over the
-//                        next power of two) and writes their ranks;
+//   up to DS_COUNT ids   an id's rank is the count of smaller ids, each id
+//                        compared with all: one launch without a barrier
+//                        chain (a block's bitonic network over 2 048 ids took
+//                        35 us, this takes 10, and 18 with shards or 5 000 ids);
 //   more, when the caller's capacity allows at most DS_MERGE ids
-//                        every chunk of DS_ONE ids is sorted by a block, then
+//                        every chunk of DS_CHUNK ids is sorted by a block, then
 //                        each id's rank among DS_FAN sorted chunks is its place
 //                        in its own plus a binary search in every other one;
 //                        a second such step joins the groups of chunks.
-// With 400 to 50 000 ids a sort takes 60 to 110 us less than with the radix
-// passes (1 M shuffled records of 2 000 journeys 685 -> 614 us per pass of the
-// whole path, 12.3 M records of 5 000 journeys 1 283 -> 1 214 us, a batch of
-// 2 M records 963 -> 775 us).
-// Above DS_MERGE ids the searches (DS_FAN x 12 reads per id and step) cost more
-// than the radix passes, which keep that range (the caller launches them for
-// such capacities; they leave at once when the ids turn out to be few).
+// The counts grow with the square of the ids (16 384: 20 us; at 32 768 they
+// would take as long as the chunks, 80 us), the searches with their number:
+// above DS_MERGE ids they (DS_FAN x 12 reads per id and step) cost more than the
+// radix passes, which keep that range (the caller launches them for such
+// capacities; they leave at once when the ids turn out to be few).
 // Ids are ordered by (shard, id image); without shards the shard words are
 // absent.
 #pragma once
@@ -27,11 +27,12 @@ namespace cv {
 namespace {
 
 constexpr int DS_B = 1024;             // threads of a sorting block
-constexpr u32 DS_ONE = 4096;           // ids per block (48 KB of LDS with shards)
+constexpr u32 DS_COUNT = 16384;        // ids ranked by counting
+constexpr u32 DS_CHUNK = 4096;         // ids per sorted chunk (48 KB of LDS with shards)
 constexpr u32 DS_FAN = 16;             // sorted chunks joined by one step
 constexpr u64 DS_MERGE = 512 * 1024;   // capacity up to which chunks are sorted and joined
 
-// Sorts n <= DS_ONE (shard, id) pairs of LDS in place (all DS_B threads).
+// Sorts n <= DS_CHUNK (shard, id) pairs of LDS in place (all DS_B threads).
 template <bool SH>
 __device__ __forceinline__ void ds_block_sort(u64* k, u32* sh, u32 n)
 {
@@ -69,17 +70,17 @@ __device__ __forceinline__ void ds_block_sort(u64* k, u32* sh, u32 n)
     }
 }
 
-// Chunk blockIdx.x of the list (DS_ONE ids), sorted into out (which may be the
+// Chunk blockIdx.x of the list (DS_CHUNK ids), sorted into out (which may be the
 // list); tag: the ids' shards (SH), sorted in place, all taken as 0 when *multi.
 template <bool SH>
 __global__ void __launch_bounds__(DS_B) k_ds_chunks(const u64* list, u64* out, u64* __restrict__ tag,
                                                     const u32* __restrict__ n_dev, const u32* __restrict__ multi)
 {
-    __shared__ u64 s_k[DS_ONE];
-    __shared__ u32 s_s[SH ? DS_ONE : 1];
-    const u32 n = *n_dev, a = blockIdx.x * DS_ONE;
+    __shared__ u64 s_k[DS_CHUNK];
+    __shared__ u32 s_s[SH ? DS_CHUNK : 1];
+    const u32 n = *n_dev, a = blockIdx.x * DS_CHUNK;
     if (a >= n) return;
-    const u32 c = n - a < DS_ONE ? n - a : DS_ONE;
+    const u32 c = n - a < DS_CHUNK ? n - a : DS_CHUNK;
     const bool one = SH && *multi;
     for (u32 i = threadIdx.x; i < c; i += DS_B) {
         s_k[i] = list[a + i];
@@ -91,6 +92,44 @@ __global__ void __launch_bounds__(DS_B) k_ds_chunks(const u64* list, u64* out, u
         out[a + i] = s_k[i];
         if (SH) tag[a + i] = s_s[i];
     }
+}
+
+// Ranks by counting, for the WAVE ids from blockIdx.x * WAVE on: lane l of every
+// wave holds id l, each wave goes through its share of the list with uniform
+// (scalar) reads, and wave 0 adds the waves' counts and calls done(r, id).
+template <bool SH, class Done>
+__device__ __forceinline__ void ds_count(const u64* __restrict__ list, const u64* __restrict__ tag, u32 n, bool multi,
+                                         Done done)
+{
+    constexpr int NWD = DS_B / WAVE;
+    __shared__ u32 s_c[NWD][WAVE];
+    const u32 i0 = blockIdx.x * WAVE;
+    if (i0 >= n) return;
+    const int l = lane_id();
+    const u32 w = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
+    const u32 i = i0 + l < n ? i0 + l : n - 1;
+    const bool sh = SH && !multi;  // (one id in several shards: the order is by id alone)
+    const u64 key = list[i], own = sh ? tag[i] : 0ull;
+    const u32 per = (n + NWD - 1) / NWD;
+    const u32 a = w * per, b = a + per < n ? a + per : n;
+    u32 c = 0;
+    if (sh) {
+#pragma unroll 8
+        for (u32 j = a; j < b; ++j) {
+            const u64 t = tag[j];
+            c += (t < own || (t == own && list[j] < key)) ? 1u : 0u;
+        }
+    } else {
+#pragma unroll 8
+        for (u32 j = a; j < b; ++j) c += list[j] < key ? 1u : 0u;
+    }
+    s_c[w][l] = c;
+    __syncthreads();
+    if (w != 0 || i0 + l >= n) return;
+    u32 r = 0;
+#pragma unroll
+    for (int k = 0; k < NWD; ++k) r += s_c[k][l];
+    done(r, key);
 }
 
 // One step of the join: runs of `run` sorted ids, DS_FAN of them to a group.

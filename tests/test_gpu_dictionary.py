@@ -1,7 +1,7 @@
-"""The order of the distinct journey ids inside the record sort: one block
-(up to 4 096 ids), sorted chunks joined in one step (up to 65 536) or two
-(capacities up to 524 288), radix passes (capacities above), each at the edges
-of its range.  The order is compared with numpy's stable sort."""
+"""The order of the distinct journey ids inside the record sort: by counting (up
+to 16 384 ids), sorted chunks of 4 096 joined in one step (capacities up to
+65 536) or two (up to 524 288), radix passes (capacities above), each at the
+edges of its range.  The order is compared with numpy's stable sort."""
 import numpy as np
 import pytest
 
@@ -38,8 +38,9 @@ def _columns(seed, J, extra):
 
 
 @pytest.mark.parametrize("J,capacity", [
-    (1, 1), (2, 4096), (63, 4096), (4095, 4096), (4096, 4096), (4096, 4097), (4097, 4097), (8193, 65536),
-    (65536, 65536), (65537, 65537), (140_001, 524_288), (3, 600_000), (4097, 600_000)])
+    (1, 1), (2, 4096), (63, 4096), (64, 64), (65, 4097), (16_384, 16_384), (16_384, 20_000), (16_385, 16_385),
+    (20_480, 65_536), (65_536, 65_536), (65_537, 65_537), (20_000, 524_288), (140_001, 524_288), (3, 600_000),
+    (16_385, 600_000)])
 def test_order_of_distinct_ids(cv, J, capacity):
     print(f"[dictionary] J={J} capacity={capacity}", flush=True)
     cols = _columns(J, J, J + 37)
@@ -52,7 +53,7 @@ def test_order_of_distinct_ids(cv, J, capacity):
 
 
 @pytest.mark.parametrize("spans", [False, True])
-@pytest.mark.parametrize("J,capacity", [(40, 4096), (4096, 4097), (4100, 5000), (70_000, 90_000), (5000, 600_000)])
+@pytest.mark.parametrize("J,capacity", [(40, 4096), (16_384, 16_384), (16_400, 20_000), (70_000, 90_000), (300, 600_000), (17_000, 600_000)])
 def test_order_of_distinct_ids_with_shards(cv, J, capacity, spans):
     """Shards of uneven size (one empty); `spans`: an id in two of them."""
     print(f"[dictionary] shards J={J} capacity={capacity} spans={spans}", flush=True)
