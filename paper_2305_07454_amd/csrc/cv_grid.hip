@@ -10,11 +10,11 @@
 //     * the runs of one (journey, key) inside the tile add into one partial
 //       row, and the tile writes its partial rows in record order into its
 //       own region (at most GT rows: each holds >= 1 record);
-//   partials of all tiles -> compacted (key, row) pairs (scan of the counts),
-//     in tile order;
+//   k_gpart_compact  partials of all tiles -> (key, row) pairs in tile order,
+//     with the digit counts of their keys;
 //   radix sort of the pairs by key (the same stable LSD sort as the record
 //     order), so a key's partials stay in record order;
-//   k_gpart_heads / k_gpart_emit: groups are runs of equal key in the sorted
+//   k_gpart_emit: groups are runs of equal key in the sorted
 //     pairs; each group's first pair sums its partials exactly (integer adds
 //     and min / max, so the order of the partials changes nothing), counts a
 //     journey once per run of equal journey ids among them (the partials of
@@ -34,34 +34,40 @@ using namespace cv;
 
 namespace {
 
-// scans of per-tile / per-chunk counts: SCH counts per block
-constexpr int SCB = 256;
-constexpr int SCP = 8;
-constexpr int SCH = SCB * SCP;
+// blocks of the compaction and of the emit at most: a block takes a contiguous
+// range of tiles (chunks), so that the look-back between them stays short and
+// its tickets few (they are atomics on one word, some 8 ns each)
+constexpr u32 CMP_BLOCKS = 512;
+constexpr u32 CMP_TILES = 4;     // tiles per block at least (one per wave)
+constexpr u32 CMP_FULL = 48;     // tiles per block from which twice as many blocks pay
+constexpr u32 EMIT_BLOCKS = 2048;
+constexpr u32 EMIT_CHUNKS = 2;   // chunks of the bound per block at least
 // sorted partial pairs per chunk of the head count and the emit
 constexpr int ECB = 256;
 constexpr int ECP = 4;  // (4: 118 VGPRs in the emit, 4 waves per SIMD)
 constexpr int ECH = ECB * ECP;
 
+struct PartMeta : GridMeta {
+    u32 t_compact, t_emit;  // tickets of the compaction's and the emit's ranges
+};
+
 struct GridLayout {
-    GridMeta* meta;
+    PartMeta* meta;
     GPart* part;  // [pmax] partial rows, GT per tile
     u64* K0;      // [pmax] compacted keys; the sort's first key buffer
     u64* K1;      // [pmax] the tiles' partial keys; then the sort's second key buffer
     u32* V0;      // [pmax] compacted partial rows (the sort's pass-0 values); then its first value buffer
     u32* V1;      // [pmax]
     u32* tcnt;    // [tiles] partial rows per tile
-    u32* toff;    // [tiles] their first compacted position
     u64* tmax;    // [tiles] largest key per tile
-    u32* bsum;    // [nb] per-block sums of a scan
-    u64* bmax;    // [nb]
-    u32* hcnt;    // [chunks] group heads per chunk of sorted pairs, then their exclusive scan
     u32* zero_begin;
     size_t zero_bytes;
     u32* hist;
+    u64* lb1;     // look-back words of the compaction's ranges
+    u64* lb2;     // and of the emit's
     u64* status;
-    u32* offs;
-    u64 pmax, stiles, tiles, chunks, nb;
+    u64 pmax, stiles, tiles, chunks;
+    u32 cblocks, eblocks;
     size_t bytes;
     GridLayout(void* ws, u64 n)
     {
@@ -70,218 +76,215 @@ struct GridLayout {
         pmax = tiles * GT;
         stiles = (pmax + sort_min_tile() - 1) / sort_min_tile();
         chunks = (pmax + ECH - 1) / ECH;
-        const u64 big = tiles > chunks ? tiles : chunks;
-        nb = (big + SCH - 1) / SCH;
-        meta = c.take<GridMeta>(1);
+        cblocks = (u32)cvh::grid_for(tiles, CMP_TILES, tiles > CMP_BLOCKS * CMP_FULL ? 2 * CMP_BLOCKS : CMP_BLOCKS);
+        eblocks = (u32)cvh::grid_for(chunks, EMIT_CHUNKS, EMIT_BLOCKS);
+        meta = c.take<PartMeta>(1);
         part = c.take<GPart>(pmax);
         K0 = c.take<u64>(pmax);
         K1 = c.take<u64>(pmax);
         V0 = c.take<u32>(pmax);
         V1 = c.take<u32>(pmax);
         tcnt = c.take<u32>(tiles);
-        toff = c.take<u32>(tiles + 1);
         tmax = c.take<u64>(tiles);
-        bsum = c.take<u32>(nb + 1);
-        bmax = c.take<u64>(nb + 1);
-        hcnt = c.take<u32>(chunks + 1);
         size_t z0 = cvh::align_up(c.off);
         hist = c.take<u32>(MAX_PASSES * RADIX);
+        lb1 = c.take<u64>(cblocks);
+        lb2 = c.take<u64>(eblocks);
+        // last in the cleared range: a call clears what its tile shape uses
         status = c.take<u64>(stiles * RADIX + 1);
-        size_t z1 = cvh::align_up(c.off);
         zero_begin = (u32*)(c.base ? c.base + z0 : nullptr);
-        zero_bytes = z1 - z0;
-        offs = c.take<u32>(MAX_PASSES * RADIX);
+        const u64 tile = (u64)sort_tile(sort_shape());
+        const size_t used = c.base ? (size_t)((char*)(status + ((pmax + tile - 1) / tile) * RADIX) - c.base) : 0;
+        zero_bytes = c.base ? cvh::align_up(used) - z0 : 0;
         bytes = c.size();
     }
 };
 
-__global__ void k_gmeta_init(GridMeta* meta)
+// The call's scratch words in one launch: meta, the cleared region and the
+// shards' counts of records outside the grid (sout, nullable).
+__global__ void __launch_bounds__(256) k_gpart_begin(PartMeta* meta, u32* __restrict__ zero, u64 words,
+                                                     u64* __restrict__ sout, u32 S)
 {
-    if (threadIdx.x == 0) {
-        GridMeta z = {};
+    const u64 i0 = (u64)blockIdx.x * 256 + threadIdx.x;
+    const u64 stride = (u64)gridDim.x * 256;
+    if (i0 == 0) {
+        PartMeta z = {};
         *meta = z;
     }
+    for (u64 i = i0; i < words; i += stride) zero[i] = 0u;
+    if (sout)
+        for (u64 i = i0; i < S; i += stride) sout[i] = 0ull;
 }
 
-// Block b of a scan: the sum of v[b * SCH, (b + 1) * SCH) (and the largest of
-// vmax there when given), n = *n_dev when given, else n_max.
-__global__ void __launch_bounds__(SCB) k_scan_up(const u32* __restrict__ v, u32 n_max, const u32* __restrict__ n_dev,
-                                                 const u64* __restrict__ vmax, u32* __restrict__ bsum,
-                                                 u64* __restrict__ bmax)
+// The tiles' partial rows packed into (key, row) pairs, in tile order, with
+// the digit counts of the key sort.  Block `range` (taken by ticket, so that
+// every range it looks back on is held by a block already running) sums its
+// tiles' row counts, gets its first position by decoupled look-back, and
+// copies; one wave per tile.
+__global__ void __launch_bounds__(256) k_gpart_compact(const u64* __restrict__ pkey, const u32* __restrict__ tcnt,
+                                                       const u64* __restrict__ tmax, u32 tiles, u64* __restrict__ K0,
+                                                       u32* __restrict__ V0, PartMeta* meta, u64* __restrict__ lb,
+                                                       int passes, u32* __restrict__ hist)
 {
-    __shared__ u32 s_t[SCB / WAVE];
-    __shared__ u64 s_m[SCB / WAVE];
-    const u32 n = n_dev ? *n_dev : n_max;
-    const u64 i0 = (u64)blockIdx.x * SCH + (u64)threadIdx.x * SCP;
+    constexpr int NWC = 256 / WAVE, CU = 4;
+    __shared__ u32 s_h[MAX_PASSES * RADIX];
+    __shared__ u32 s_off[256], s_cnt[256];
+    __shared__ u32 s_t[NWC];
+    __shared__ u32 s_bits[NWC];
+    __shared__ u32 s_range;
+    __shared__ u64 s_base;
+    const int l = lane_id(), w = threadIdx.x / WAVE;
+    const u32 per = (tiles + gridDim.x - 1) / gridDim.x;
+    if ((u64)blockIdx.x * per >= tiles) return;  // exactly the blocks before take the tickets
+    if (threadIdx.x == 0) s_range = atomicAdd(&meta->t_compact, 1u);
+    for (int i = threadIdx.x; i < passes * RADIX; i += 256) s_h[i] = 0;
+    __syncthreads();
+    const u32 a = s_range * per;
+    const u32 b = a + per < tiles ? a + per : tiles;
     u32 c = 0;
-    u64 m = 0;
-#pragma unroll
-    for (int k = 0; k < SCP; ++k) {
-        const u64 i = i0 + k;
-        if (i < n) {
-            c += v[i];
-            if (vmax) m = vmax[i] > m ? vmax[i] : m;
-        }
+    u64 km = 0;
+    for (u32 t = a + threadIdx.x; t < b; t += 256) {
+        c += tcnt[t];
+        km = tmax[t] > km ? tmax[t] : km;
     }
     u32 tot;
-    block_exclusive_sum<SCB>(c, s_t, tot);
+    block_exclusive_sum<256>(c, s_t, tot);
+    u32 bits = km ? 64u - (u32)__clzll((long long)km) : 0u;
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) {
-        const u64 o = __shfl_xor(m, d, WAVE);
-        m = o > m ? o : m;
+        const u32 o = (u32)__shfl_xor((int)bits, d, WAVE);
+        bits = o > bits ? o : bits;
     }
-    if (lane_id() == 0) s_m[threadIdx.x / WAVE] = m;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        bsum[blockIdx.x] = tot;
-        u64 mm = 0;
-        for (int w = 0; w < SCB / WAVE; ++w) mm = s_m[w] > mm ? s_m[w] : mm;
-        bmax[blockIdx.x] = mm;
-    }
-}
-
-// One block: exclusive scan of the nb block sums in place.  mode 0 (the
-// tiles' partial counts): total = partial rows, the largest key gives the
-// sort's key width and passes, and the chunk count of the sorted pairs;
-// mode 1 (group heads per chunk): total = groups.
-__global__ void __launch_bounds__(SCB) k_scan_top(u32* __restrict__ bsum, u32 nb, const u64* __restrict__ bmax,
-                                                  GridMeta* meta, int mode)
-{
-    __shared__ u32 s_t[SCB / WAVE];
-    __shared__ u32 carry;
-    __shared__ u64 s_m;
-    if (threadIdx.x == 0) {
-        carry = 0;
-        s_m = 0;
+    if (l == 0) s_bits[w] = bits;
+    if (w == 0) {
+        const u64 e = wave_lookback_exclusive(lb, s_range, tot);
+        if (l == 0) s_base = e;
     }
     __syncthreads();
-    for (u32 b = 0; b < nb; b += SCB) {
-        const u32 i = b + threadIdx.x;
-        const u32 v = i < nb ? bsum[i] : 0u;
-        if (mode == 0 && i < nb && bmax[i]) atomicMax((unsigned long long*)&s_m, (unsigned long long)bmax[i]);
-        u32 tot;
-        const u32 e = block_exclusive_sum<SCB>(v, s_t, tot);
-        if (i < nb) bsum[i] = carry + e;
-        __syncthreads();
-        if (threadIdx.x == 0) carry += tot;
-        __syncthreads();
-    }
     if (threadIdx.x == 0) {
-        if (mode == 0) {
-            meta->compact_n = carry;
-            meta->max_key = s_m;
-            const u32 bits = s_m ? 64u - (u32)__clzll((long long)s_m) : 0u;
-            meta->key_bits = bits;
-            meta->passes = (bits + RADIX_BITS - 1) / RADIX_BITS;
-            meta->chunks = (u32)(((u64)carry + ECH - 1) / ECH);
-        } else {
-            meta->groups = carry;
-        }
+        for (int k = 1; k < NWC; ++k) bits = s_bits[k] > bits ? s_bits[k] : bits;
+        if (bits > meta->key_bits) atomicMax(&meta->key_bits, bits);  // most ranges have keys of one width
+        if (b == tiles) meta->compact_n = (u32)(s_base + tot);
     }
-}
-
-// Block b: exclusive offsets of v[b * SCH, (b + 1) * SCH) from bsum[b], into out.
-__global__ void __launch_bounds__(SCB) k_scan_down(const u32* __restrict__ v, u32 n_max, const u32* __restrict__ n_dev,
-                                                   const u32* __restrict__ bsum, u32* __restrict__ out)
-{
-    __shared__ u32 s_t[SCB / WAVE];
-    const u32 n = n_dev ? *n_dev : n_max;
-    const u64 i0 = (u64)blockIdx.x * SCH + (u64)threadIdx.x * SCP;
-    u32 x[SCP];
-    u32 c = 0;
+    u32 base = (u32)s_base;
+    for (u32 t0 = a; t0 < b; t0 += 256) {
+        const u32 t = t0 + threadIdx.x;
+        u32 sum;
+        const u32 ct = t < b ? tcnt[t] : 0u;
+        const u32 ex = block_exclusive_sum<256>(ct, s_t, sum);
+        s_off[threadIdx.x] = base + ex;
+        s_cnt[threadIdx.x] = ct;
+        base += sum;
+        __syncthreads();
+        const u32 m = b - t0 < 256 ? b - t0 : 256;
+        // a wave takes CU of its tiles together, so that their reads are in flight at once
+        for (u32 k0 = w; k0 < m; k0 += NWC * CU) {
+            u32 cn[CU], o[CU], top = 0;
 #pragma unroll
-    for (int k = 0; k < SCP; ++k) {
-        const u64 i = i0 + k;
-        x[k] = i < n ? v[i] : 0u;
-        c += x[k];
-    }
-    u32 tot;
-    u32 e = block_exclusive_sum<SCB>(c, s_t, tot) + bsum[blockIdx.x];
+            for (int u = 0; u < CU; ++u) {
+                const u32 k = k0 + u * NWC;
+                cn[u] = k < m ? s_cnt[k] : 0u;
+                o[u] = k < m ? s_off[k] : 0u;
+                top = cn[u] > top ? cn[u] : top;
+            }
+            for (u32 j = 0; j < top; j += WAVE) {
+                u64 key[CU];
 #pragma unroll
-    for (int k = 0; k < SCP; ++k) {
-        const u64 i = i0 + k;
-        if (i < n) out[i] = e;
-        e += x[k];
-    }
-}
-
-// One wave per tile: its partial keys to their compacted positions, with the
-// partial's row (tile * GT + j) as the sort's value.
-__global__ void __launch_bounds__(256) k_gpart_compact(const u64* __restrict__ pkey, const u32* __restrict__ tcnt,
-                                                       const u32* __restrict__ toff, u32 tiles, u64* __restrict__ K0,
-                                                       u32* __restrict__ V0)
-{
-    const u32 wv = (blockIdx.x * 256 + threadIdx.x) / WAVE;
-    const u32 nw = gridDim.x * 256 / WAVE;
-    const int l = lane_id();
-    for (u32 t = wv; t < tiles; t += nw) {
-        const u32 c = tcnt[t], o = toff[t];
-        const u64 b = (u64)t * GT;
-        for (u32 j = l; j < c; j += WAVE) {
-            K0[o + j] = pkey[b + j];
-            V0[o + j] = (u32)(b + j);
-        }
-    }
-}
-
-// the sorted pairs after meta->passes passes (ping-pong buffers)
-__device__ __forceinline__ const u64* sorted_keys(const GridMeta* m, const u64* K0, const u64* K1)
-{
-    return (m->passes & 1) ? K1 : K0;
-}
-__device__ __forceinline__ const u32* sorted_vals(const GridMeta* m, const u32* V0, const u32* V1)
-{
-    return (m->passes & 1) ? V1 : V0;
-}
-
-// group heads (first pair of each key) per chunk of ECH sorted pairs
-__global__ void __launch_bounds__(ECB) k_gpart_heads(const GridMeta* meta, const u64* __restrict__ K0,
-                                                     const u64* __restrict__ K1, u32* __restrict__ hcnt)
-{
-    __shared__ u32 s_t[ECB / WAVE];
-    const u32 P = meta->compact_n;
-    const u32 chunks = meta->chunks;
-    const u64* K = sorted_keys(meta, K0, K1);
-    for (u32 c = blockIdx.x; c < chunks; c += gridDim.x) {
-        const u64 i0 = (u64)c * ECH + (u64)threadIdx.x * ECP;
-        u32 h = 0;
-        u64 prev = (i0 > 0 && i0 < P) ? K[i0 - 1] : ~0ull;
+                for (int u = 0; u < CU; ++u)
+                    key[u] = j + l < cn[u] ? pkey[(u64)(t0 + k0 + u * NWC) * GT + j + l] : 0ull;
 #pragma unroll
-        for (int k = 0; k < ECP; ++k) {
-            const u64 i = i0 + k;
-            if (i < P) {
-                const u64 key = K[i];
-                h += (i == 0 || key != prev) ? 1u : 0u;
-                prev = key;
+                for (int u = 0; u < CU; ++u) {
+                    if (j >= cn[u]) continue;  // wave-uniform
+                    const bool ok = j + l < cn[u];
+                    if (ok) {
+                        K0[o[u] + j + l] = key[u];
+                        V0[o[u] + j + l] = (u32)((u64)(t0 + k0 + u * NWC) * GT + j + l);
+                    }
+                    const u64 vm = __ballot(ok);
+                    for (int p = 0; p < passes; ++p) {
+                        // (a digit shared by every row adds once)
+                        const u32 d = (u32)(key[u] >> (p * RADIX_BITS)) & (RADIX - 1);
+                        const u32 d0 = __builtin_amdgcn_readfirstlane(d);
+                        if (__ballot(ok && d != d0) == 0) {
+                            if (l == 0) atomicAdd(&s_h[p * RADIX + d0], (u32)__popcll(vm));
+                        } else if (ok) {
+                            atomicAdd(&s_h[p * RADIX + d], 1u);
+                        }
+                    }
+                }
             }
         }
-        u32 tot;
-        block_exclusive_sum<ECB>(h, s_t, tot);
-        if (threadIdx.x == 0) hcnt[c] = tot;
         __syncthreads();
     }
+    for (int i = threadIdx.x; i < passes * RADIX; i += 256)
+        if (s_h[i]) atomicAdd(&hist[i], s_h[i]);
 }
+
+// the passes of the key sort, and the sorted pairs after them (ping-pong buffers)
+__device__ __forceinline__ u32 key_passes(const PartMeta* m) { return (m->key_bits + RADIX_BITS - 1) / RADIX_BITS; }
 
 // Rows in ascending key: the first pair of each key sums the partials of its
 // group (the pairs that follow with the same key) and writes the row.  In the
 // batched form, group_offsets[s] = first row of shard s (keys carry the shard
-// above bit kb).
-__global__ void __launch_bounds__(ECB) k_gpart_emit(const GridMeta* meta, const u64* __restrict__ K0,
+// above bit kb).  A block takes a contiguous range of chunks by ticket, counts
+// their group heads, gets its first row by decoupled look-back and then reads
+// its keys again (from cache) for the rows; counts, their scan in three
+// launches and the rows apart took 4 launches more.
+__global__ void __launch_bounds__(ECB) k_gpart_emit(PartMeta* meta, const u64* __restrict__ K0,
                                                     const u64* __restrict__ K1, const u32* __restrict__ V0,
                                                     const u32* __restrict__ V1, const GPart* __restrict__ part,
-                                                    const u32* __restrict__ hoff, u32 cap, i64* __restrict__ o_key,
+                                                    u64* __restrict__ lb, u32 cap, i64* __restrict__ o_key,
                                                     u32* __restrict__ o_cnt, u32* __restrict__ o_nj,
                                                     double* __restrict__ o_sum, float* __restrict__ o_min,
                                                     float* __restrict__ o_max, u64* __restrict__ go, u32 S, u32 kb,
                                                     u64 kmask, cv_result* res)
 {
+    __shared__ u32 s_rw[ECP][ECB / WAVE];
+    __shared__ u32 s_t[ECB / WAVE];
+    __shared__ u32 s_range;
+    __shared__ u64 s_base;
     const u32 P = meta->compact_n;
-    const u32 G = meta->groups;
-    const u32 chunks = meta->chunks;
-    const u64* K = sorted_keys(meta, K0, K1);
-    const u32* V = sorted_vals(meta, V0, V1);
+    const u32 chunks = (u32)(((u64)P + ECH - 1) / ECH);
+    const bool odd = key_passes(meta) & 1;
+    const u64* K = odd ? K1 : K0;
+    const u32* V = odd ? V1 : V0;
     const bool sharded = go && S > 1;
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
+    const int t = threadIdx.x, lane = lane_id(), w = t / WAVE;
+    // exactly the first ceil(chunks / per) blocks take the tickets (one when there are no pairs)
+    const u32 per = (chunks + gridDim.x - 1) / gridDim.x;
+    if (blockIdx.x > 0 && (u64)blockIdx.x * per >= chunks) return;
+    if (t == 0) s_range = atomicAdd(&meta->t_emit, 1u);
+    __syncthreads();
+    const u32 range = s_range;
+    const u32 c0 = range * per;
+    const u32 c1 = c0 + per < chunks ? c0 + per : chunks;
+    u32 heads = 0;
+    for (u32 c = c0; c < c1; c += 2) {  // two chunks' keys in flight
+        u64 x[2 * ECP], y[2 * ECP];
+#pragma unroll
+        for (int k = 0; k < 2 * ECP; ++k) {
+            const u64 i = (u64)c * ECH + (u64)k * ECB + t;
+            const u64 j = i < P ? i : (u64)P - 1;
+            x[k] = K[j];
+            y[k] = K[j > 0 ? j - 1 : 0];
+        }
+        const u64 end = (u64)c1 * ECH < P ? (u64)c1 * ECH : (u64)P;
+#pragma unroll
+        for (int k = 0; k < 2 * ECP; ++k) {
+            const u64 i = (u64)c * ECH + (u64)k * ECB + t;
+            heads += (i < end && (i == 0 || x[k] != y[k])) ? 1u : 0u;
+        }
+    }
+    u32 mine;
+    block_exclusive_sum<ECB>(heads, s_t, mine);
+    if (w == 0) {
+        const u64 e = wave_lookback_exclusive(lb, range, mine);
+        if (lane == 0) s_base = e;
+    }
+    __syncthreads();
+    u32 rbase = (u32)s_base;
+    const u32 G = rbase + mine;  // the groups, in the block of the last range
+    if (c1 == chunks && t == 0) {
         if (res) {
             cv_result r = {};
             r.status = meta->overflow ? CV_ERR_DEVICE : (G > cap ? CV_ERR_CAPACITY : CV_OK);
@@ -298,9 +301,7 @@ __global__ void __launch_bounds__(ECB) k_gpart_emit(const GridMeta* meta, const 
     // c * ECH + k * ECB + t, so the heads of a row write consecutive output
     // rows (coalesced stores), and each thread still issues its ECP gathers
     // of first partials together.
-    __shared__ u32 s_rw[ECP][ECB / WAVE];
-    const int t = threadIdx.x, lane = lane_id(), w = t / WAVE;
-    for (u32 c = blockIdx.x; c < chunks; c += gridDim.x) {
+    for (u32 c = c0; c < c1; ++c) {
         const u64 ic = (u64)c * ECH;
         u64 key[ECP], kprev[ECP];
         u32 hb = 0;
@@ -327,7 +328,6 @@ __global__ void __launch_bounds__(ECB) k_gpart_emit(const GridMeta* meta, const 
         for (int k = 0; k < ECP; ++k)
             if ((hb >> k) & 1u) pf[k] = part[vv[k]];
         __syncthreads();
-        u32 rbase = hoff[c];
 #pragma unroll
         for (int k = 0; k < ECP; ++k) {
             const u64 i = ic + (u64)k * ECB + t;
@@ -438,18 +438,6 @@ static void launch_parts(dim3 gg, hipStream_t s, u32 nn, const cv_records* sorte
                        sorted->lat_deg, sorted->lon_deg, sorted->speed_mps, g, sk, meta, first);
 }
 
-// exclusive scan of v[0, n) into out (n = *n_dev when given, at most n_max);
-// mode as in k_scan_top
-static void scan_counts(const u32* v, u32 n_max, const u32* n_dev, const u64* vmax, u32* out, const GridLayout& L,
-                        int mode, hipStream_t s)
-{
-    const u32 nb = (u32)((n_max + SCH - 1) / SCH);
-    const dim3 g(nb ? nb : 1);
-    hipLaunchKernelGGL(k_scan_up, g, dim3(SCB), 0, s, v, n_max, n_dev, vmax, L.bsum, L.bmax);
-    hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(SCB), 0, s, L.bsum, nb, L.bmax, L.meta, mode);
-    hipLaunchKernelGGL(k_scan_down, g, dim3(SCB), 0, s, v, n_max, n_dev, L.bsum, out);
-}
-
 // nd > 0: a direction dimension of nd sectors (plus one for records without a
 // direction) from the sorted heading column hdg, else from feat's bearing
 static cv_status grid_impl(const cv_records* sorted, const u64* soff, u32 S, const cv_grid_spec* grid,
@@ -525,8 +513,9 @@ static cv_status grid_impl(const cv_records* sorted, const u64* soff, u32 S, con
     const u32 pmax = (u32)(L.pmax - 1 < 0xFFFFFFFFull ? L.pmax : 0xFFFFFFFFull);
     {
         cvh::TimedScope ts_("grid_agg", s);
-        hipLaunchKernelGGL(k_gmeta_init, dim3(1), dim3(64), 0, s, L.meta);
-        if (sout) cvh::fill_u64(sout, 0ull, S ? S : 1, s);
+        const u64 words = L.zero_bytes / 4;
+        hipLaunchKernelGGL(k_gpart_begin, dim3(cvh::grid_for(words, 256, 4096)), dim3(256), 0, s, L.meta, L.zero_begin,
+                           words, sout, S ? S : 1u);
         PartSink sk{L.K1, L.part, L.tcnt, L.tmax};
         const dim3 gg(tiles);
         if (nd == 0 && first) launch_parts<0, true>(gg, s, nn, sorted, g, sk, L.meta, first);
@@ -536,23 +525,15 @@ static cv_status grid_impl(const cv_records* sorted, const u64* soff, u32 S, con
     }
     {
         cvh::TimedScope ts_("grid_tail", s);
-        // partial rows -> compacted (key, row) pairs
-        cvh::fill_u32(L.zero_begin, 0u, L.zero_bytes / 4, s);
-        scan_counts(L.tcnt, tiles, nullptr, L.tmax, L.toff, L, 0, s);
-        hipLaunchKernelGGL(k_gpart_compact, dim3(cvh::grid_for((u64)tiles * WAVE, 256, 8192)), dim3(256), 0, s,
-                           L.K1, L.tcnt, L.toff, tiles, L.K0, L.V0);
+        // partial rows -> compacted (key, row) pairs, with the key sort's digit counts
+        hipLaunchKernelGGL(k_gpart_compact, dim3(L.cblocks), dim3(256), 0, s, L.K1, L.tcnt, L.tmax, tiles, L.K0, L.V0,
+                           L.meta, L.lb1, mpasses, L.hist);
         // key sort of the pairs
-        const u32* cnt = &L.meta->compact_n;
-        const u32* bits = &L.meta->key_bits;
-        radix_hist(L.K0, pmax, cnt, mpasses, bits, L.hist, cvh::grid_for(L.pmax, 256, 1024), s);
-        radix_scan(L.hist, L.offs, mpasses, s);
-        radix_passes(L.K0, L.K1, L.V0, L.V0, L.V1, pmax, cnt, bits, mpasses, L.offs, L.status, L.meta->tickets, s);
-        // groups: heads of equal-key runs, their rows, the merge
-        const unsigned eg = (unsigned)cvh::grid_for(L.chunks, 1, 4096);
-        hipLaunchKernelGGL(k_gpart_heads, dim3(eg), dim3(ECB), 0, s, L.meta, L.K0, L.K1, L.hcnt);
-        scan_counts(L.hcnt, (u32)L.chunks, &L.meta->chunks, nullptr, L.hcnt, L, 1, s);
-        hipLaunchKernelGGL(k_gpart_emit, dim3(eg), dim3(ECB), 0, s, L.meta, L.K0, L.K1, L.V0, L.V1, L.part, L.hcnt,
-                           (u32)capacity, out->key, out->count, out->n_journeys, out->sum_speed, out->min_speed,
+        radix_passes(L.K0, L.K1, L.V0, L.V0, L.V1, pmax, &L.meta->compact_n, &L.meta->key_bits, mpasses, L.hist,
+                     L.status, L.meta->tickets, s);
+        // groups: runs of equal keys, their rows
+        hipLaunchKernelGGL(k_gpart_emit, dim3(L.eblocks), dim3(ECB), 0, s, L.meta, L.K0, L.K1, L.V0, L.V1, L.part,
+                           L.lb2, (u32)capacity, out->key, out->count, out->n_journeys, out->sum_speed, out->min_speed,
                            out->max_speed, go, S, g.kb, kmask, res);
         cvh::debug_rows(out->key, out->count, out->n_journeys, res, capacity, go, S, CV_DEBUG_GROUP_ORDER, s);
     }

@@ -49,24 +49,22 @@ bool sort_wide_first();
 // Host launchers (defined in cv_radix.hip).
 //   radix_hist : digit histograms of `passes` passes (limited on device by
 //                ceil(*bits_dev / 8) when bits_dev is given) added into hist.
-//   radix_scan : per-pass exclusive scan hist -> offs.
-//   radix_passes: up to `passes` stable scatter passes, ping-pong k0 -> k1 -> k0
+//   radix_passes: (hist: the digit counts, each pass scans its own) up to `passes` stable scatter passes, ping-pong k0 -> k1 -> k0
 //                ...; pass p is skipped on device when 8p >= *bits_dev.  vals of
 //                pass 0 come from v_first (nullptr = identity).  After p passes
 //                the data sits in (k1, v1) when p is odd, in (k0, v0) when even.
 void radix_hist(const u64* keys, u32 n_max, const u32* n_dev, int passes, const u32* bits_dev, u32* hist,
                 int grid, hipStream_t s);
-void radix_scan(const u32* hist, u32* offs, int passes, hipStream_t s, const u32* w0_dev = nullptr);
 //                When `timed`, pass p is bracketed as timing family "sort_pass<p>".
 //                pack [device, 3] (nullable): {ib, p0, w0}: from pass p0 on,
 //                key words hold (key >> 8 p0) << ib | index and no value
 //                arrays are used (p0 = 0: the input keys are packed
 //                already); w0 is the first digit's width (8 or 9).
 //                w0_dev [device] (nullable): bits of the first digit (8 or
-//                9; 9 only with p0 = 0), the word after pack's two; offs then
+//                9; 9 only with p0 = 0), the word after pack's two; hist then
 //                use the wide layout and status holds 512 words per tile.
 void radix_passes(u64* k0, u64* k1, const u32* v_first, u32* v0, u32* v1, u32 n_max, const u32* n_dev,
-                  const u32* bits_dev, int passes, const u32* offs, u64* status, u32* tickets, hipStream_t s,
+                  const u32* bits_dev, int passes, const u32* hist, u64* status, u32* tickets, hipStream_t s,
                   bool timed = false, const u32* pack = nullptr, const u32* w0_dev = nullptr);
 
 }  // namespace cv

@@ -55,24 +55,6 @@ __global__ void __launch_bounds__(256) k_radix_hist(const u64* __restrict__ keys
         if (s_h[i]) atomicAdd(&hist[i], s_h[i]);
 }
 
-// Exclusive scan of each pass's digit counts (one block, a thread per digit).
-// With w0 (device, nullable) the counts use the wide layout: the first digit
-// has w0 bits (8 or 9) and 512 counters.
-__global__ void __launch_bounds__(2 * RADIX) k_radix_scan(const u32* __restrict__ hist, u32* __restrict__ offs,
-                                                          int passes, const u32* __restrict__ w0_dev)
-{
-    __shared__ u32 tmp[2 * RADIX / WAVE];
-    const u32 w0 = first_digit_bits(w0_dev);
-    for (int p = 0; p < passes; ++p) {
-        const u32 bins = 1u << (p == 0 ? w0 : (u32)RADIX_BITS);
-        const int base = w0_dev ? hist_wide_off(p) : p * RADIX;
-        u32 total;
-        const u32 v = threadIdx.x < bins ? hist[base + threadIdx.x] : 0u;
-        const u32 e = block_exclusive_sum<2 * RADIX>(v, tmp, total);
-        if (threadIdx.x < bins) offs[base + threadIdx.x] = e;
-    }
-}
-
 // One stable scatter pass on digit `pass`: bits [8*pass, 8*pass+8), or, with
 // a first digit of w0 = pack[2] bits (9): [0, w0) for pass 0 and
 // [w0 + 8 (pass - 1), w0 + 8 pass) after it.  DB: bits of the digit this
@@ -84,7 +66,7 @@ template <int SORT_BLOCK, int SORT_ITEMS, bool LOOP, int DB = RADIX_BITS>
 __global__ void __launch_bounds__(SORT_BLOCK)
 k_radix_pass(const u64* __restrict__ keys_in, const u32* __restrict__ vals_in, u64* __restrict__ keys_out,
              u32* __restrict__ vals_out, u32 n_max, const u32* __restrict__ n_dev, int pass,
-             const u32* __restrict__ bits_dev, const u32* __restrict__ digit_offs, u64* __restrict__ status,
+             const u32* __restrict__ bits_dev, const u32* __restrict__ hist, u64* __restrict__ status,
              u32* __restrict__ ticket, const u32* __restrict__ pack)
 {
     constexpr int NW = SORT_BLOCK / WAVE;
@@ -99,7 +81,7 @@ k_radix_pass(const u64* __restrict__ keys_in, const u32* __restrict__ vals_in, u
     // staging: keys in digit order; then, in passes that carry index values,
     // the values in the same order (the buffer reused as 32-bit words)
     __shared__ u64 s_keys[SORT_TILE];
-    __shared__ u32 s_tmp[NW];
+    __shared__ u64 s_tmp[NW];
     __shared__ u32 s_tile;
 
     // the launch's scalars from device memory, all loaded before any is used.
@@ -121,8 +103,8 @@ k_radix_pass(const u64* __restrict__ keys_in, const u32* __restrict__ vals_in, u
     const bool pin = pass >= p0;           // input words are packed
     const bool pout = pass + 1 >= p0;      // output words are packed
     const int shift = pin ? (int)ib + lo - p0 * RADIX_BITS : lo;
-    // this pass's global start of digit threadIdx.x, read before it is needed
-    const u32 doff = threadIdx.x < RK ? digit_offs[threadIdx.x] : 0u;
+    // this pass's global count of digit threadIdx.x, read before it is needed
+    const u32 dcnt = threadIdx.x < RK ? hist[threadIdx.x] : 0u;
     // Tiles are taken by ticket (with LOOP, until the tickets pass the last
     // tile, so a grid smaller than the tile count covers every tile); a tile
     // waits only on tiles whose tickets were taken before, by blocks already
@@ -180,8 +162,11 @@ k_radix_pass(const u64* __restrict__ keys_in, const u32* __restrict__ vals_in, u
             tcount += c;
         }
     }
-    u32 total;
-    u32 start = block_exclusive_sum<SORT_BLOCK>(threadIdx.x < RK ? tcount : 0u, s_tmp, total);
+    // one scan for the tile's digit starts and (high word) the pass's global
+    // ones: a scan kernel between the histogram and the passes cost a launch
+    u64 total;
+    const u64 ex = block_exclusive_sum<SORT_BLOCK>(((u64)dcnt << 32) | (threadIdx.x < RK ? tcount : 0u), s_tmp, total);
+    const u32 start = (u32)ex, doff = (u32)(ex >> 32);
     const u32 tag = (u32)pass + 1;
     if (threadIdx.x < RK) {
         s_start[threadIdx.x] = start;
@@ -292,11 +277,6 @@ void radix_hist(const u64* keys, u32 n_max, const u32* n_dev, int passes, const 
     hipLaunchKernelGGL(k_radix_hist, dim3(grid), dim3(256), 0, s, keys, n_max, n_dev, passes, bits_dev, hist);
 }
 
-void radix_scan(const u32* hist, u32* offs, int passes, hipStream_t s, const u32* w0_dev)
-{
-    hipLaunchKernelGGL(k_radix_scan, dim3(1), dim3(2 * RADIX), 0, s, hist, offs, passes, w0_dev);
-}
-
 namespace {
 
 // A pass whose record count is read on the device launches one block per
@@ -318,17 +298,17 @@ bool g_wide_first = true;  // tuning "radix_wide_first"
 
 template <int B, int I, int DB = RADIX_BITS>
 void launch_pass(u64 tiles, hipStream_t s, const u64* kin, const u32* vin, u64* kout, u32* vout, u32 n_max,
-                 const u32* n_dev, int p, const u32* bits_dev, const u32* offs, u64* status, u32* ticket,
+                 const u32* n_dev, int p, const u32* bits_dev, const u32* hist, u64* status, u32* ticket,
                  const u32* pack)
 {
     // a count known only on the device and a very large bound: a grid that
     // fills the GPU, whose blocks take tiles until the count is covered
     if (n_dev && tiles > DEVICE_COUNT_MAX_TILES)
         hipLaunchKernelGGL((k_radix_pass<B, I, true, DB>), dim3((unsigned)DEVICE_COUNT_GRID), dim3(B), 0, s, kin,
-                           vin, kout, vout, n_max, n_dev, p, bits_dev, offs, status, ticket, pack);
+                           vin, kout, vout, n_max, n_dev, p, bits_dev, hist, status, ticket, pack);
     else
         hipLaunchKernelGGL((k_radix_pass<B, I, false, DB>), dim3((unsigned)(tiles ? tiles : 1)), dim3(B), 0, s, kin,
-                           vin, kout, vout, n_max, n_dev, p, bits_dev, offs, status, ticket, pack);
+                           vin, kout, vout, n_max, n_dev, p, bits_dev, hist, status, ticket, pack);
 }
 
 }  // namespace
@@ -352,7 +332,7 @@ int sort_min_tile()
 }
 
 void radix_passes(u64* k0, u64* k1, const u32* v_first, u32* v0, u32* v1, u32 n_max, const u32* n_dev,
-                  const u32* bits_dev, int passes, const u32* offs, u64* status, u32* tickets, hipStream_t s,
+                  const u32* bits_dev, int passes, const u32* hist, u64* status, u32* tickets, hipStream_t s,
                   bool timed, const u32* pack, const u32* w0_dev)
 {
     static const char* const names[MAX_PASSES] = {"sort_pass0", "sort_pass1", "sort_pass2", "sort_pass3",
@@ -368,9 +348,9 @@ void radix_passes(u64* k0, u64* k1, const u32* v_first, u32* v0, u32* v1, u32 n_
         u64* kout = (p & 1) ? k0 : k1;
         u32* vout = (p & 1) ? v0 : v1;
         cvh::TimedScope ts_(timed ? names[p] : nullptr, s);
-        const u32* o = offs + (w0_dev ? hist_wide_off(p) : p * RADIX);
+        const u32* h = hist + (w0_dev ? hist_wide_off(p) : p * RADIX);
         auto go = [&](auto launch) {
-            launch(tiles, s, kin, vin, kout, vout, n_max, n_dev, p, bits_dev, o, status, tickets + p, pack);
+            launch(tiles, s, kin, vin, kout, vout, n_max, n_dev, p, bits_dev, h, status, tickets + p, pack);
         };
         // the first pass of a sort that may take a 9-bit first digit: both
         // widths are launched, and the one that is not the pass's leaves at once

@@ -438,7 +438,9 @@ __global__ void __launch_bounds__(256) k_dict_insert(const i64* __restrict__ jid
 }
 
 // The key's layout from the distinct ids (J) and the insert's findings (one thread).
-__device__ __forceinline__ void dict_meta(SortMeta* m, u32 J, u32 max_j, u32 n, u32 n_shards, u32 allow_wide)
+// res (nullable): the call's result, which is known from here on.
+__device__ __forceinline__ void dict_meta(SortMeta* m, u32 J, u32 max_j, u32 n, u32 n_shards, u32 allow_wide,
+                                          cv_result* res)
 {
     m->J = J;
     if (J > max_j) m->overflow = 1;
@@ -482,13 +484,22 @@ __device__ __forceinline__ void dict_meta(SortMeta* m, u32 J, u32 max_j, u32 n, 
     const u32 w0 = (allow_wide && p0 == 0 && kb > RADIX_BITS && kb % RADIX_BITS == 1) ? RADIX_BITS + 1 : RADIX_BITS;
     m->w0 = w0;
     m->passes = kb == 0 ? 0u : (kb <= w0 ? 1u : 1u + (kb - w0 + RADIX_BITS - 1) / RADIX_BITS);
+    if (!res) return;
+    cv_result r = {};
+    r.status = m->range_err ? CV_ERR_RANGE : (m->overflow ? CV_ERR_CAPACITY : CV_OK);
+    r.count = J;
+    r.required = m->overflow ? J : 0;
+    r.key_bits = kb;
+    r.packed_pass = p0;
+    r.flags = w0;  // bits of the first radix digit
+    *res = r;
 }
 
 // The insert's per-block parts joined, then the key's layout from `ids` distinct
 // ids (a whole block of B threads).
 template <int B>
 __device__ __forceinline__ void dict_settle(SortMeta* m, const InsPart* __restrict__ parts, u32 nparts, u32 ids,
-                                            u32 max_j, u32 n, u32 n_shards, u32 allow_wide)
+                                            u32 max_j, u32 n, u32 n_shards, u32 allow_wide, cv_result* res)
 {
     __shared__ InsPart s_part[B / WAVE];
     InsPart p{~0ull, 0, 0, 0, 0, 0, 0};
@@ -505,7 +516,7 @@ __device__ __forceinline__ void dict_settle(SortMeta* m, const InsPart* __restri
     m->n_runs = p.runs;
     m->unordered = p.down;
     m->multi_shard = p.multi;
-    dict_meta(m, ids, max_j, n, n_shards, allow_wide);
+    dict_meta(m, ids, max_j, n, n_shards, allow_wide, res);
 }
 
 // The dictionary's ids to a list (any order), batched: with their shards.  Each
@@ -515,7 +526,7 @@ constexpr int CPT_D = 4;
 __global__ void __launch_bounds__(256) k_dict_compact(const u64* __restrict__ table, u64 slots, u32 max_j,
                                                       SortMeta* m, u64* __restrict__ list, u64* __restrict__ tag,
                                                       const InsPart* __restrict__ parts, u32 nparts, u32 n,
-                                                      u32 n_shards, u32 allow_wide)
+                                                      u32 n_shards, u32 allow_wide, cv_result* res)
 {
     __shared__ u32 s_t[256 / WAVE];
     __shared__ u32 s_base;
@@ -563,7 +574,8 @@ __global__ void __launch_bounds__(256) k_dict_compact(const u64* __restrict__ ta
     __syncthreads();
     if (s_base != gridDim.x - 1) return;
     __threadfence();
-    dict_settle<256>(m, parts, nparts, atomicAdd(&m->list_count, 0u) + hm, max_j, n, n_shards, allow_wide);
+    dict_settle<256>(m, parts, nparts, atomicAdd(&m->list_count, 0u) + hm, max_j, n, n_shards, allow_wide,
+                     res);
 }
 
 // writes rank r of the id (image) into its slot
@@ -1115,19 +1127,6 @@ __global__ void __launch_bounds__(256) k_gather(u32 n, const SortMeta* m, const 
     }
 }
 
-__global__ void k_sort_finish(const SortMeta* m, cv_result* res)
-{
-    if (threadIdx.x != 0) return;
-    cv_result r = {};
-    r.status = m->range_err ? CV_ERR_RANGE : (m->overflow ? CV_ERR_CAPACITY : CV_OK);
-    r.count = m->J;
-    r.required = m->overflow ? m->J : 0;
-    r.key_bits = m->key_bits;
-    r.packed_pass = m->p0;
-    r.flags = m->w0;  // bits of the first radix digit
-    *res = r;
-}
-
 __global__ void k_empty_result(cv_result* res)
 {
     if (threadIdx.x == 0) {
@@ -1148,15 +1147,12 @@ struct SortLayout {
     u64* dlf;   // batched: the distinct ids in (shard, id) order
     u32* shist;
     u64* sstatus;
-    u32* soffs;
     u32* zero_begin;  // start of the region cleared to zero
     u32* hist;
     u32* dhist;
     u64* status;
     u64* dstatus;
     size_t zero_bytes;
-    u32* offs;
-    u32* doffs;
     u64* K0;
     u64* K1;
     PayRec* pay;  // packed payload (interleaved input, fused gather)
@@ -1199,9 +1195,6 @@ struct SortLayout {
             const size_t zu = cvh::align_up((size_t)((char*)(status + used) - (char*)c.base));
             zero_bytes = (zu < z1 ? zu : z1) - z0;
         }
-        offs = c.take<u32>(HIST_WIDE_WORDS);
-        doffs = c.take<u32>(MAX_PASSES * RADIX);
-        soffs = c.take<u32>(MAX_PASSES * RADIX);
         K0 = c.take<u64>(n);
         K1 = c.take<u64>(n);
         pay = c.take<PayRec>(n);
@@ -1477,13 +1470,13 @@ __global__ void __launch_bounds__(256) k_gather_feat(u32 n, const SortMeta* m, c
 // that it does not choose leaves at once.
 template <bool SH>
 void launch_dict_order_as(const SortLayout& L, u32 mj, u32 n, u32 S, u64 mask, const InsPart* parts, u32 nparts,
-                          hipStream_t s)
+                          cv_result* res, hipStream_t s)
 {
     // the counted ids may not be written over the list they are counted in
     u64* out = SH ? L.dlf : L.dl1;
     u64* tag = SH ? L.dsk0 : nullptr;
     hipLaunchKernelGGL(k_dict_compact, dim3(cvh::grid_for(L.slots, 256 * CPT_D, 2048)), dim3(256), 0, s, L.table,
-                       L.slots, mj, L.meta, L.dl0, tag, parts, nparts, n, S, sort_wide_first() ? 1u : 0u);
+                       L.slots, mj, L.meta, L.dl0, tag, parts, nparts, n, S, sort_wide_first() ? 1u : 0u, res);
     hipLaunchKernelGGL(k_dict_count<SH>, dim3(cvh::grid_for(mj < DS_COUNT ? mj : DS_COUNT, WAVE)), dim3(DS_B), 0, s,
                        L.meta, L.table, mask, L.dl0, tag, out);
     if (mj <= DS_COUNT) return;
@@ -1509,8 +1502,7 @@ void launch_dict_order_as(const SortLayout& L, u32 mj, u32 n, u32 S, u64 mask, c
     }
     // radix passes over the ids (64-bit, signed order via the flipped sign bit)
     radix_hist(L.dl0, mj, big, MAX_PASSES, nullptr, L.dhist, cvh::grid_for(mj, 256, 512), s);
-    radix_scan(L.dhist, L.doffs, MAX_PASSES, s);
-    radix_passes(L.dl0, L.dl1, nullptr, L.dv0, L.dv1, mj, big, nullptr, MAX_PASSES, L.doffs, L.dstatus,
+    radix_passes(L.dl0, L.dl1, nullptr, L.dv0, L.dv1, mj, big, nullptr, MAX_PASSES, L.dhist, L.dstatus,
                  L.meta->tickets + MAX_PASSES, s);
     const int dg = cvh::grid_for(mj, 256, 1024);
     if (SH) {
@@ -1518,8 +1510,7 @@ void launch_dict_order_as(const SortLayout& L, u32 mj, u32 n, u32 S, u64 mask, c
         const int sp = (int)((bit_width_host((u64)S - 1) + RADIX_BITS - 1) / RADIX_BITS);
         hipLaunchKernelGGL(k_dict_shardkey, dim3(dg), dim3(256), 0, s, L.dl0, L.meta, L.table, mask, L.dsk0);
         radix_hist(L.dsk0, mj, big, sp, nullptr, L.shist, cvh::grid_for(mj, 256, 512), s);
-        radix_scan(L.shist, L.soffs, sp, s);
-        radix_passes(L.dsk0, L.dsk1, nullptr, L.dv0, L.dv1, mj, big, nullptr, sp, L.soffs, L.sstatus,
+        radix_passes(L.dsk0, L.dsk1, nullptr, L.dv0, L.dv1, mj, big, nullptr, sp, L.shist, L.sstatus,
                      L.meta->tickets + 2 * MAX_PASSES, s);
         hipLaunchKernelGGL(k_dict_final, dim3(dg), dim3(256), 0, s, L.dl0, (sp & 1) ? L.dv1 : L.dv0, L.meta, L.table,
                            mask, L.dlf);
@@ -1529,10 +1520,10 @@ void launch_dict_order_as(const SortLayout& L, u32 mj, u32 n, u32 S, u64 mask, c
 }
 
 void launch_dict_order(const SortLayout& L, u32 mj, u32 n, u32 S, u64 mask, const InsPart* parts, u32 nparts,
-                       hipStream_t s)
+                       cv_result* res, hipStream_t s)
 {
-    if (S > 1) launch_dict_order_as<true>(L, mj, n, S, mask, parts, nparts, s);
-    else launch_dict_order_as<false>(L, mj, n, S, mask, parts, nparts, s);
+    if (S > 1) launch_dict_order_as<true>(L, mj, n, S, mask, parts, nparts, res, s);
+    else launch_dict_order_as<false>(L, mj, n, S, mask, parts, nparts, res, s);
 }
 
 }  // namespace
@@ -1584,7 +1575,7 @@ static cv_status sort_impl(const cv_records* in, const uint64_t* soff, uint32_t 
         const int gi = cvh::grid_for(n, 256 * 8, 2048);
         hipLaunchKernelGGL(S > 1 ? k_dict_insert<true> : k_dict_insert<false>, dim3(gi), dim3(256), 0, s,
                            in->journey_id, in->ts_ms, nn, L.table, mask, L.meta, parts, soff, S);
-        launch_dict_order(L, mj, nn, S, mask, parts, (u32)gi, s);
+        launch_dict_order(L, mj, nn, S, mask, parts, (u32)gi, res, s);
         // interleaved input (short runs of equal ids): the payload packed per
         // record for the fused gather, in the same pass
         hipLaunchKernelGGL(S > 1 ? k_pack_hist<true> : k_pack_hist<false>, dim3(gs), dim3(256), 0, s, in->journey_id,
@@ -1593,9 +1584,8 @@ static cv_status sort_impl(const cv_records* in, const uint64_t* soff, uint32_t 
                            s, in->journey_id,
                            in->ts_ms, in->lat_deg, in->lon_deg, in->speed_mps, feat ? L.pay : nullptr, nn, L.table,
                            mask, L.meta, L.K0, L.hist, soff, S);
-        radix_scan(L.hist, L.offs, MAX_PASSES, s, &L.meta->w0);
     }
-    radix_passes(L.K0, L.K1, nullptr, L.V0, L.V1, nn, nullptr, &L.meta->key_bits, MAX_PASSES, L.offs, L.status,
+    radix_passes(L.K0, L.K1, nullptr, L.V0, L.V1, nn, nullptr, &L.meta->key_bits, MAX_PASSES, L.hist, L.status,
                  L.meta->tickets, s, /*timed=*/true, &L.meta->ib, &L.meta->w0);
     const u64* dict_ids = S > 1 ? L.dlf : L.dl1;  // journey ids by rank
     if (feat) {
@@ -1614,7 +1604,6 @@ static cv_status sort_impl(const cv_records* in, const uint64_t* soff, uint32_t 
                            so.journey_id, so.ts_ms, so.lat_deg, so.lon_deg, so.speed_mps, soff, S);
     }
     cvh::debug_sort(L.K0, L.K1, &L.meta->passes, &L.meta->range_err, &L.meta->overflow, n, perm, soff, S, s);
-    if (res) hipLaunchKernelGGL(k_sort_finish, dim3(1), dim3(64), 0, s, L.meta, res);
     return cvh::last_launch_status();
 }
 

@@ -767,7 +767,7 @@ struct cv_stream {
     // flush scratch
     u64 *gK0, *gK1, *jK0, *jK1;
     u32 *gC, *gV0, *gV1, *jV0, *jV1, *jfirst;
-    u32 *ghist, *goffs, *jhist, *joffs;
+    u32 *ghist, *jhist;
     u64 *gstatus, *jstatus;
     size_t zero_off, zero_bytes;  // region cleared at creation (tables) - informational
 };
@@ -823,7 +823,6 @@ struct StreamLayout {
         f("gV0", c.take<u32>(gslots));
         f("gV1", c.take<u32>(gslots));
         f("ghist", c.take<u32>(MAX_PASSES * RADIX));
-        f("goffs", c.take<u32>(MAX_PASSES * RADIX));
         f("gstatus", c.take<u64>(gst * RADIX + 1));
         f("jK0", c.take<u64>(jslots + 1));
         f("jK1", c.take<u64>(jslots + 1));
@@ -831,7 +830,6 @@ struct StreamLayout {
         f("jV1", c.take<u32>(jslots + 1));
         f("jfirst", c.take<u32>(jslots + 1));
         f("jhist", c.take<u32>(MAX_PASSES * RADIX));
-        f("joffs", c.take<u32>(MAX_PASSES * RADIX));
         f("jstatus", c.take<u64>(jst * RADIX + 1));
     }
 };
@@ -976,7 +974,6 @@ cv_status cv_stream_create(const cv_grid_spec* grid, uint64_t max_journeys, uint
         else if (nm == "gV0") st->gV0 = (u32*)p;
         else if (nm == "gV1") st->gV1 = (u32*)p;
         else if (nm == "ghist") st->ghist = (u32*)p;
-        else if (nm == "goffs") st->goffs = (u32*)p;
         else if (nm == "gstatus") st->gstatus = (u64*)p;
         else if (nm == "jK0") st->jK0 = (u64*)p;
         else if (nm == "jK1") st->jK1 = (u64*)p;
@@ -984,7 +981,6 @@ cv_status cv_stream_create(const cv_grid_spec* grid, uint64_t max_journeys, uint
         else if (nm == "jV1") st->jV1 = (u32*)p;
         else if (nm == "jfirst") st->jfirst = (u32*)p;
         else if (nm == "jhist") st->jhist = (u32*)p;
-        else if (nm == "joffs") st->joffs = (u32*)p;
         else if (nm == "jstatus") st->jstatus = (u64*)p;
     });
     cv_sort_workspace_size(max_batch, max_batch ? max_batch : 1, &st->sort_ws_bytes);
@@ -1109,12 +1105,11 @@ cv_status cv_stream_flush(cv_stream* st, const cv_journeys* journeys, uint64_t j
                        st->jslots, st->meta, st->jK0, st->jV0);
     const u32* jn = &st->meta->jcount;
     radix_hist(st->jK0, (u32)jrows, jn, MAX_PASSES, nullptr, st->jhist, cvh::grid_for(jrows, 256, 1024), s);
-    radix_scan(st->jhist, st->joffs, MAX_PASSES, s);
     // 8 passes: the sorted pairs end in (jK0, jV0); pass 0 reads the slot values from jV0 via jfirst copy
     u32* vfirst = st->jfirst;
     if (hipMemcpyAsync(vfirst, st->jV0, jrows * sizeof(u32), hipMemcpyDeviceToDevice, s) != hipSuccess)
         return CV_ERR_DEVICE;
-    radix_passes(st->jK0, st->jK1, vfirst, st->jV0, st->jV1, (u32)jrows, jn, nullptr, MAX_PASSES, st->joffs,
+    radix_passes(st->jK0, st->jK1, vfirst, st->jV0, st->jV1, (u32)jrows, jn, nullptr, MAX_PASSES, st->jhist,
                  st->jstatus, st->meta->jtickets, s);
     cv_status e = CV_OK;
     if (jcap > 0) {
@@ -1140,8 +1135,7 @@ cv_status cv_stream_flush(cv_stream* st, const cv_journeys* journeys, uint64_t j
     const u32* cnt = &st->meta->gm.compact_n;
     const u32* bits = &st->meta->gm.key_bits;
     radix_hist(st->gK0, (u32)st->gslots, cnt, MAX_PASSES, bits, st->ghist, cvh::grid_for(st->gslots, 256, 1024), s);
-    radix_scan(st->ghist, st->goffs, MAX_PASSES, s);
-    radix_passes(st->gK0, st->gK1, st->gC, st->gV0, st->gV1, (u32)st->gslots, cnt, bits, MAX_PASSES, st->goffs,
+    radix_passes(st->gK0, st->gK1, st->gC, st->gV0, st->gV1, (u32)st->gslots, cnt, bits, MAX_PASSES, st->ghist,
                  st->gstatus, st->meta->gm.tickets, s);
     hipLaunchKernelGGL(k_iota_if_nopass, dim3(cvh::grid_for(st->gslots, 256, 1024)), dim3(256), 0, s, &st->meta->gm,
                        st->gC, st->gV0, (u32)st->gslots);
