@@ -307,6 +307,24 @@ __device__ __forceinline__ u64 shard_starts_in(const u64* __restrict__ off, u32 
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ int lane_id() { return __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0)); }
 
+// The value of the lane below (lane 0 keeps its own): the wave's shift right by
+// one lane as a data-parallel move, one vector instruction per 32-bit word where a
+// shuffle goes through the LDS unit.
+__device__ __forceinline__ u32 lane_below(u32 v)
+{
+    return (u32)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x138 /* wave_shr:1 */, 0xf, 0xf, false);
+}
+__device__ __forceinline__ u64 lane_below(u64 v)
+{
+    return (u64)lane_below((u32)v) | ((u64)lane_below((u32)(v >> 32)) << 32);
+}
+__device__ __forceinline__ i64 lane_below(i64 v) { return (i64)lane_below((u64)v); }
+__device__ __forceinline__ float lane_below(float v) { return __uint_as_float(lane_below(__float_as_uint(v))); }
+__device__ __forceinline__ double lane_below(double v)
+{
+    return __longlong_as_double((long long)lane_below((u64)__double_as_longlong(v)));
+}
+
 // number of set bits of `mask` in lanes below this lane
 __device__ __forceinline__ u32 popc_below(u64 mask)
 {
@@ -396,32 +414,7 @@ __device__ __forceinline__ u64 lb_peek(u64* p)
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// One thread: publish `agg` for `tile` and return the exclusive prefix.
-__device__ __forceinline__ u64 lookback_exclusive(u64* status, u32 tile, u64 agg)
-{
-    if (tile == 0) {
-        lb_publish(&status[0], LB_PRE | agg);
-        return 0;
-    }
-    lb_publish(&status[tile], LB_AGG | agg);
-    u64 excl = 0;
-    int t = (int)tile - 1;
-    while (t >= 0) {
-        u64 w = lb_peek(&status[t]);
-        u64 f = w & ~LB_VAL;
-        if (f == 0) {
-            __builtin_amdgcn_s_sleep(1);
-            continue;
-        }
-        excl += w & LB_VAL;
-        if (f == LB_PRE) break;
-        --t;
-    }
-    lb_publish(&status[tile], LB_PRE | (excl + agg));
-    return excl;
-}
-
-// Wave-parallel variant: the whole wave (all 64 lanes, uniform control flow)
+// Exclusive prefix of `tile`: the whole wave (all 64 lanes, uniform control flow)
 // inspects 64 predecessor tiles per step.  Returns the exclusive prefix in
 // every lane.  Lane 0 publishes.
 __device__ __forceinline__ u64 wave_lookback_exclusive(u64* status, u32 tile, u64 agg)
