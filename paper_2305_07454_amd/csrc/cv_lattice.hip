@@ -8,7 +8,7 @@
 //   k_lat_scatter  one thread per group: mean speed and distinct journeys
 //                  into the cell of its time bin and direction
 //   k_lat_minmax   per channel, min and max over the occupied cells
-//   k_lat_norm     one thread per (cell, direction): both channels rescaled
+//   k_lat_norm     both channels rescaled, in the stretches with occupied cells
 //   k_filt_*       order-preserving compaction of group indices
 #include <hip/hip_runtime.h>
 
@@ -24,10 +24,17 @@ namespace {
 constexpr int LB = 256;
 constexpr int FT = LB * 8;  // groups per filter tile
 
+// Bound by HBM writes; a block zeroes one contiguous stretch of LB * FU 16-byte
+// words (2.84 GB: 464 us, 6.1 TB/s; 541 with 8 192 blocks striding over the
+// whole tensor, 473 with FU 16, 555 with stores that bypass the caches).
+constexpr int FU = 4;
 __global__ void __launch_bounds__(LB) k_lat_fill(float4* __restrict__ p, u64 n4)
 {
     const float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (u64 i = (u64)blockIdx.x * LB + threadIdx.x; i < n4; i += (u64)gridDim.x * LB) p[i] = z;
+    const u64 i0 = (u64)blockIdx.x * (LB * FU) + threadIdx.x;
+#pragma unroll
+    for (int k = 0; k < FU; ++k)
+        if (i0 + k * LB < n4) p[i0 + k * LB] = z;
 }
 
 __global__ void __launch_bounds__(LB) k_lat_fill_tail(float* __restrict__ p, u64 from, u64 n)
@@ -61,33 +68,70 @@ __global__ void __launch_bounds__(LB) k_lat_scatter(const i64* __restrict__ key,
 
 // Per channel, min and max over occupied cells (volume > 0), as ordered
 // integer images.  Block b takes cells [CH * (b % cpi), +CH) of (time bin,
-// sector) image b / cpi (each thread CH / LB of them) and writes its four
-// partials (speed min / max, volume min / max) to part[4 b ..]; one block per
-// sector then reduces them into mm[4 d ..] (no atomics on shared addresses).
+// sector) image b / cpi and writes its four partials (speed min / max, volume
+// min / max) to part[4 b ..]; k_lat_mm_reduce joins them (no atomics on shared
+// addresses).  occ (nullable): one bit per 64 cells of the chunk, set where one
+// is occupied, so that the rescaling reads those cells only.
+// The volumes are read whole, CH / LB of them per thread before any is used
+// (16 bytes a load when the image lies on 16 bytes): 1.42 GB of a full day's in
+// 343 us, 4.1 TB/s; one load of 4 bytes at a time took 584.
 constexpr int CH = LB * 16;
+constexpr int SUB = CH / WAVE;  // stretches of 64 cells per chunk: the bits of a word
+static_assert(SUB == 64, "one word per chunk");
 
 __global__ void __launch_bounds__(LB) k_lat_minmax(const float* __restrict__ lat, u32 D, u64 cells, u64 cpi,
-                                                    u32* __restrict__ part)
+                                                    u32* __restrict__ part, u64* __restrict__ occ)
 {
-    __shared__ u32 s_mm[4];
+    constexpr int NWL = LB / WAVE, PT = CH / LB;
+    __shared__ u32 s_mm[NWL][4];
+    __shared__ u64 s_occ[NWL];
+    const int w = threadIdx.x / WAVE, l = lane_id();
     const u64 img = blockIdx.x / cpi;
     const u64 c0 = (blockIdx.x % cpi) * CH;
     const u32 d = (u32)(img % D);
     const float* sp = lat + (img / D * 2 * D + 2 * d) * cells;
     const float* vo = sp + cells;
     u32 smin = ~0u, smax = 0u, vmin = ~0u, vmax = 0u;
-#pragma unroll 4
-    for (int k = 0; k < CH / LB; ++k) {
-        const u64 i = c0 + (u64)k * LB + threadIdx.x;
-        if (i < cells) {
-            const float v = vo[i];
-            if (v > 0.f) {
-                const u32 a = ord_f32(sp[i]), b = ord_f32(v);
-                smin = a < smin ? a : smin;
-                smax = a > smax ? a : smax;
-                vmin = b < vmin ? b : vmin;
-                vmax = b > vmax ? b : vmax;
-            }
+    auto take = [&](float v, u64 i) {
+        const u32 a = ord_f32(sp[i]), b = ord_f32(v);
+        smin = a < smin ? a : smin;
+        smax = a > smax ? a : smax;
+        vmin = b < vmin ? b : vmin;
+        vmax = b > vmax ? b : vmax;
+    };
+    u64 oc = 0;
+    if (((uintptr_t)vo & 15u) == 0 && c0 + CH <= cells) {
+        float4 x[PT / 4];
+#pragma unroll
+        for (int k = 0; k < PT / 4; ++k) x[k] = *(const float4*)(vo + c0 + 4 * (u64)(k * LB + threadIdx.x));
+#pragma unroll
+        for (int k = 0; k < PT / 4; ++k) {
+            const u64 i = c0 + 4 * (u64)(k * LB + threadIdx.x);
+            const bool any = x[k].x > 0.f || x[k].y > 0.f || x[k].z > 0.f || x[k].w > 0.f;
+            const u64 m = __ballot(any);
+            // the wave's 256 cells are 4 stretches, 16 lanes each
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                if ((m >> (16 * q)) & 0xFFFFull) oc |= 1ull << (4 * (k * NWL + w) + q);
+            if (!any) continue;
+            if (x[k].x > 0.f) take(x[k].x, i);
+            if (x[k].y > 0.f) take(x[k].y, i + 1);
+            if (x[k].z > 0.f) take(x[k].z, i + 2);
+            if (x[k].w > 0.f) take(x[k].w, i + 3);
+        }
+    } else {
+        float x[PT];
+#pragma unroll
+        for (int k = 0; k < PT; ++k) {
+            const u64 i = c0 + (u64)k * LB + threadIdx.x;
+            x[k] = vo[i < cells ? i : cells - 1];
+        }
+#pragma unroll
+        for (int k = 0; k < PT; ++k) {
+            const u64 i = c0 + (u64)k * LB + threadIdx.x;
+            const bool on = i < cells && x[k] > 0.f;
+            if (__ballot(on)) oc |= 1ull << (k * NWL + w);
+            if (on) take(x[k], i);
         }
     }
 #pragma unroll
@@ -99,74 +143,73 @@ __global__ void __launch_bounds__(LB) k_lat_minmax(const float* __restrict__ lat
         vmin = c < vmin ? c : vmin;
         vmax = e > vmax ? e : vmax;
     }
-    if (threadIdx.x == 0) {
-        s_mm[0] = ~0u;
-        s_mm[1] = 0u;
-        s_mm[2] = ~0u;
-        s_mm[3] = 0u;
-    }
-    __syncthreads();
-    if (lane_id() == 0 && smin != ~0u) {
-        atomicMin(&s_mm[0], smin);
-        atomicMax(&s_mm[1], smax);
-        atomicMin(&s_mm[2], vmin);
-        atomicMax(&s_mm[3], vmax);
+    if (l == 0) {
+        s_mm[w][0] = smin;
+        s_mm[w][1] = smax;
+        s_mm[w][2] = vmin;
+        s_mm[w][3] = vmax;
+        s_occ[w] = oc;
     }
     __syncthreads();
     if (threadIdx.x == 0) {
-        u32* o = part + 4 * (u64)blockIdx.x;
-        o[0] = s_mm[0];
-        o[1] = s_mm[1];
-        o[2] = s_mm[2];
-        o[3] = s_mm[3];
+        for (int k = 1; k < NWL; ++k) {
+            smin = s_mm[k][0] < smin ? s_mm[k][0] : smin;
+            smax = s_mm[k][1] > smax ? s_mm[k][1] : smax;
+            vmin = s_mm[k][2] < vmin ? s_mm[k][2] : vmin;
+            vmax = s_mm[k][3] > vmax ? s_mm[k][3] : vmax;
+            oc |= s_occ[k];
+        }
+        *(uint4*)(part + 4 * (u64)blockIdx.x) = make_uint4(smin, smax, vmin, vmax);
+        if (occ) occ[blockIdx.x] = oc;
     }
 }
 
-// sector d = blockIdx.x: the partials of its images t * D + d, all chunks
-__global__ void __launch_bounds__(LB) k_lat_mm_reduce(const u32* __restrict__ part, u64 n_t, u32 D, u64 cpi,
-                                                       u32* __restrict__ mm)
+// the join of a wave's four extrema, in every lane
+__device__ __forceinline__ void mm_wave(uint4& a)
 {
-    __shared__ u32 s_mm[4];
-    const u32 d = blockIdx.x;
-    u32 a0 = ~0u, a1 = 0u, a2 = ~0u, a3 = 0u;
-    const u64 per = n_t * cpi;
-    for (u64 i = threadIdx.x; i < per; i += LB) {
-        const u64 b = ((i / cpi) * D + d) * cpi + i % cpi;
-        const u32* p = part + 4 * b;
-        a0 = p[0] < a0 ? p[0] : a0;
-        a1 = p[1] > a1 ? p[1] : a1;
-        a2 = p[2] < a2 ? p[2] : a2;
-        a3 = p[3] > a3 ? p[3] : a3;
-    }
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) {
-        const u32 x0 = __shfl_xor(a0, o, WAVE), x1 = __shfl_xor(a1, o, WAVE);
-        const u32 x2 = __shfl_xor(a2, o, WAVE), x3 = __shfl_xor(a3, o, WAVE);
-        a0 = x0 < a0 ? x0 : a0;
-        a1 = x1 > a1 ? x1 : a1;
-        a2 = x2 < a2 ? x2 : a2;
-        a3 = x3 > a3 ? x3 : a3;
+        const u32 x0 = __shfl_xor(a.x, o, WAVE), x1 = __shfl_xor(a.y, o, WAVE);
+        const u32 x2 = __shfl_xor(a.z, o, WAVE), x3 = __shfl_xor(a.w, o, WAVE);
+        a.x = x0 < a.x ? x0 : a.x;
+        a.y = x1 > a.y ? x1 : a.y;
+        a.z = x2 < a.z ? x2 : a.z;
+        a.w = x3 > a.w ? x3 : a.w;
     }
-    if (threadIdx.x == 0) {
-        s_mm[0] = ~0u;
-        s_mm[1] = 0u;
-        s_mm[2] = ~0u;
-        s_mm[3] = 0u;
+}
+
+// Block r of sector d (grid MR x D): the partials [r * per, (r + 1) * per) of
+// the sector's n_t * cpi, left in the first of them (one block per sector went
+// through 87 000 partials of a full day in 167 us).
+constexpr u32 MR = WAVE;
+__device__ __forceinline__ u64 mm_slot(u64 i, u32 d, u32 D, u64 cpi) { return ((i / cpi) * D + d) * cpi + i % cpi; }
+__global__ void __launch_bounds__(LB) k_lat_mm_reduce(u32* __restrict__ part, u64 n_t, u32 D, u64 cpi)
+{
+    __shared__ uint4 s_a[LB / WAVE];
+    const u32 d = blockIdx.y;
+    const u64 n = n_t * cpi, per = (n + MR - 1) / MR;
+    const u64 i0 = blockIdx.x * per, i1 = i0 + per < n ? i0 + per : n;
+    if (i0 >= n) return;
+    uint4 a = make_uint4(~0u, 0u, ~0u, 0u);
+    for (u64 i = i0 + threadIdx.x; i < i1; i += LB) {
+        const uint4 p = *(const uint4*)(part + 4 * mm_slot(i, d, D, cpi));
+        a.x = p.x < a.x ? p.x : a.x;
+        a.y = p.y > a.y ? p.y : a.y;
+        a.z = p.z < a.z ? p.z : a.z;
+        a.w = p.w > a.w ? p.w : a.w;
     }
+    mm_wave(a);
+    if (lane_id() == 0) s_a[threadIdx.x / WAVE] = a;
     __syncthreads();
-    if (lane_id() == 0) {
-        atomicMin(&s_mm[0], a0);
-        atomicMax(&s_mm[1], a1);
-        atomicMin(&s_mm[2], a2);
-        atomicMax(&s_mm[3], a3);
+    if (threadIdx.x != 0) return;
+    for (int k = 1; k < LB / WAVE; ++k) {
+        const uint4 p = s_a[k];
+        a.x = p.x < a.x ? p.x : a.x;
+        a.y = p.y > a.y ? p.y : a.y;
+        a.z = p.z < a.z ? p.z : a.z;
+        a.w = p.w > a.w ? p.w : a.w;
     }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        mm[4 * d + 0] = s_mm[0];
-        mm[4 * d + 1] = s_mm[1];
-        mm[4 * d + 2] = s_mm[2];
-        mm[4 * d + 3] = s_mm[3];
-    }
+    *(uint4*)(part + 4 * mm_slot(i0, d, D, cpi)) = a;
 }
 
 // occupied cell: (x - min) / (max - min) of its channel in double, rounded to
@@ -177,36 +220,62 @@ __device__ __forceinline__ float rescale(float x, float mn, float mx)
     return (float)(((double)x - (double)mn) / ((double)mx - (double)mn));
 }
 
-__global__ void __launch_bounds__(LB) k_lat_norm(float* __restrict__ lat, u32 D, u64 cells, u64 cpi,
-                                                  const u32* __restrict__ mm)
+// Block b rescales chunks [NCH * (b % gpi), +NCH) of image b / gpi: the stretches
+// of 64 cells that occ marks (every one without occ), a wave each (a full day's
+// 1.55 M occupied cells: 201 us, 542 when every volume was read again; 4 or 16
+// chunks per block 226 and 260).  The first
+// block of a sector's first image writes the channels' min and max as floats
+// (NaN for a channel with no occupied cell).
+constexpr u32 NCH = 8;
+__global__ void __launch_bounds__(LB) k_lat_norm(float* __restrict__ lat, u32 D, u64 cells, u64 cpi, u64 gpi, u64 n_t,
+                                                  const u32* __restrict__ part, const u64* __restrict__ occ,
+                                                  float* __restrict__ out)
 {
-    const u64 img = blockIdx.x / cpi;
-    const u64 c0 = (blockIdx.x % cpi) * CH;
+    constexpr int NWL = LB / WAVE, NU = 4;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
+    const int l = lane_id();
+    const u64 img = blockIdx.x / gpi;
+    const u64 ch0 = (blockIdx.x % gpi) * NCH;
     const u32 d = (u32)(img % D);
+    const u64 n = n_t * cpi, per = (n + MR - 1) / MR;
+    uint4 a = make_uint4(~0u, 0u, ~0u, 0u);
+    if ((u64)l * per < n) a = *(const uint4*)(part + 4 * mm_slot((u64)l * per, d, D, cpi));
+    mm_wave(a);
+    const float smn = unord_f32(a.x), smx = unord_f32(a.y);
+    const float vmn = unord_f32(a.z), vmx = unord_f32(a.w);
+    if (img == d && ch0 == 0 && threadIdx.x == 0) {
+        const float nan = __builtin_nanf("");
+        const bool none = a.x == ~0u;
+        out[4 * d + 0] = none ? nan : smn;
+        out[4 * d + 1] = none ? nan : smx;
+        out[4 * d + 2] = none ? nan : vmn;
+        out[4 * d + 3] = none ? nan : vmx;
+    }
     float* sp = lat + (img / D * 2 * D + 2 * d) * cells;
     float* vo = sp + cells;
-    const float smn = unord_f32(mm[4 * d + 0]), smx = unord_f32(mm[4 * d + 1]);
-    const float vmn = unord_f32(mm[4 * d + 2]), vmx = unord_f32(mm[4 * d + 3]);
-#pragma unroll 4
-    for (int k = 0; k < CH / LB; ++k) {
-        const u64 i = c0 + (u64)k * LB + threadIdx.x;
-        if (i < cells) {
-            const float v = vo[i];
-            if (v > 0.f) {
-                sp[i] = rescale(sp[i], smn, smx);
-                vo[i] = rescale(v, vmn, vmx);
+    for (u32 c = w; c < NCH && ch0 + c < cpi; c += NWL) {
+        const u64 c0 = (ch0 + c) * CH;
+        u64 m = occ ? occ[img * cpi + ch0 + c] : ~0ull;
+        while (m) {
+            u64 i[NU];
+            float v[NU], x[NU];
+#pragma unroll
+            for (int q = 0; q < NU; ++q) {
+                i[q] = cells;
+                if (m) i[q] = c0 + 64 * (u64)(__ffsll((long long)m) - 1) + l;
+                m &= m - 1;  // (0 stays 0)
+            }
+#pragma unroll
+            for (int q = 0; q < NU; ++q) v[q] = i[q] < cells ? vo[i[q]] : 0.f;
+#pragma unroll
+            for (int q = 0; q < NU; ++q) x[q] = v[q] > 0.f ? sp[i[q]] : 0.f;
+#pragma unroll
+            for (int q = 0; q < NU; ++q) {
+                if (!(v[q] > 0.f)) continue;
+                sp[i[q]] = rescale(x[q], smn, smx);
+                vo[i[q]] = rescale(v[q], vmn, vmx);
             }
         }
-    }
-}
-
-// the channels' min and max as floats (NaN for a channel with no occupied cell)
-__global__ void k_lat_mm_out(const u32* __restrict__ mm, float* __restrict__ out, u32 C)
-{
-    const u32 i = threadIdx.x;
-    if (i < 2 * C) {
-        const u32 lo = mm[i & ~1u];
-        out[i] = lo == ~0u ? __builtin_nanf("") : unord_f32(mm[i]);
     }
 }
 
@@ -326,8 +395,7 @@ cv_status cv_lattice_dense(const cv_groups* groups, uint64_t n_groups, const cv_
     if (h) hipLaunchKernelGGL(k_lat_fill_tail, dim3(1), dim3(LB), 0, s, lattice, (u64)0, h);
     const u64 n4 = (total - h) / 4;
     if (n4)
-        hipLaunchKernelGGL(k_lat_fill, dim3(cvh::grid_for(n4, LB, 8192)), dim3(LB), 0, s,
-                           (float4*)(lattice + h), n4);
+        hipLaunchKernelGGL(k_lat_fill, dim3(cvh::grid_for(n4, LB * FU)), dim3(LB), 0, s, (float4*)(lattice + h), n4);
     const u64 done = h + 4 * n4;
     if (done < total) hipLaunchKernelGGL(k_lat_fill_tail, dim3(1), dim3(LB), 0, s, lattice, done, total);
     if (n_groups)
@@ -344,7 +412,7 @@ cv_status cv_lattice_normalize_workspace_size(uint64_t n_t, const cv_grid_spec* 
     if (!bytes || !lattice_dims(grid, n_dir, cells, D) || n_t == 0) return CV_ERR_INVALID_ARGUMENT;
     const u64 cpi = ((u64)cells + CH - 1) / CH;
     if ((unsigned __int128)n_t * D * cpi >= ((unsigned __int128)1 << 31)) return CV_ERR_RANGE;
-    *bytes = cvh::align_up(n_t * D * cpi * 4 * sizeof(u32));
+    *bytes = cvh::align_up(n_t * D * cpi * 4 * sizeof(u32)) + cvh::align_up(n_t * D * cpi * sizeof(u64));
     return CV_OK;
 }
 
@@ -360,18 +428,20 @@ cv_status cv_lattice_normalize(float* lattice, uint64_t n_t, const cv_grid_spec*
     size_t need = 0;
     const cv_status e = cv_lattice_normalize_workspace_size(n_t, grid, n_dir, &need);
     if (e != CV_OK) return e;
-    if (!ws || !cvh::aligned(ws, cvh::WS_ALIGN) || ws_bytes < need) return CV_ERR_WORKSPACE;
+    // (a workspace without room for the occupancy words: every cell is read again)
+    const u64 blocks = n_t * D * (((u64)cells + CH - 1) / CH);
+    const size_t parts = cvh::align_up(blocks * 4 * sizeof(u32));
+    if (!ws || !cvh::aligned(ws, cvh::WS_ALIGN) || ws_bytes < parts) return CV_ERR_WORKSPACE;
     hipStream_t s = (hipStream_t)stream;
     cvh::TimedScope ts_("lattice_norm", s);
-    const u32 C = 2 * D;
-    u32* mm = reinterpret_cast<u32*>(channel_min_max);  // ordered images until the last step
-    const u64 cpi = ((u64)cells + CH - 1) / CH;          // blocks per image
-    const u64 blocks = n_t * D * cpi;
+    const u64 cpi = ((u64)cells + CH - 1) / CH;  // chunks per image
+    const u64 gpi = (cpi + NCH - 1) / NCH;
     u32* part = (u32*)ws;
-    hipLaunchKernelGGL(k_lat_minmax, dim3((unsigned)blocks), dim3(LB), 0, s, lattice, D, (u64)cells, cpi, part);
-    hipLaunchKernelGGL(k_lat_mm_reduce, dim3(D), dim3(LB), 0, s, part, (u64)n_t, D, cpi, mm);
-    hipLaunchKernelGGL(k_lat_norm, dim3((unsigned)blocks), dim3(LB), 0, s, lattice, D, (u64)cells, cpi, mm);
-    hipLaunchKernelGGL(k_lat_mm_out, dim3(1), dim3(256), 0, s, mm, channel_min_max, C);
+    u64* occ = ws_bytes >= need ? (u64*)((char*)ws + parts) : nullptr;
+    hipLaunchKernelGGL(k_lat_minmax, dim3((unsigned)blocks), dim3(LB), 0, s, lattice, D, (u64)cells, cpi, part, occ);
+    hipLaunchKernelGGL(k_lat_mm_reduce, dim3(MR, D), dim3(LB), 0, s, part, (u64)n_t, D, cpi);
+    hipLaunchKernelGGL(k_lat_norm, dim3((unsigned)(n_t * D * gpi)), dim3(LB), 0, s, lattice, D, (u64)cells, cpi, gpi,
+                       (u64)n_t, part, occ, channel_min_max);
     return cvh::last_launch_status();
 }
 
