@@ -3,9 +3,19 @@
 // columns on the device: the "E" of the ETL path ahead of the key prep.
 //
 //   k_csv_count   newlines per tile of CT bytes (16-byte loads)
-//   k_csv_scan    exclusive prefix of the tile counts
-//   k_csv_rows    row start offsets, in order
-//   k_csv_parse   one thread per row: the fields of the row
+//   k_csv_scan    exclusive prefix of the tile counts (texts of more than
+//                 CSV_SELF tiles; the parse sums the counts itself below that)
+//   k_csv_parse   per tile: the text staged in LDS with one bit per byte for
+//                 newlines, commas and quotes; then one thread per row that
+//                 starts in the tile
+//
+// A row's fields come from the bits (six commas, no quote) and are converted
+// eight characters at a time; a row of another shape, or one that runs past
+// the staged bytes, goes through the byte-wise parser, which alone says what is
+// malformed.  Bound by vector instructions and, in the count, by HBM: 4 M rows,
+// 292 MB, take 63 us to count and 172 to parse; reading the text a third time
+// for the row starts and finding the commas byte by byte in each row's thread
+// took 537, 404 of them the parse.
 #include <hip/hip_runtime.h>
 
 #include "cv_device.h"
@@ -15,85 +25,101 @@ using namespace cv;
 
 namespace {
 
-constexpr int CB = 256;          // threads per block
-constexpr int CPT = 64;          // bytes per thread
-constexpr int CT = CB * CPT;     // bytes per tile
+constexpr int CB = 256;            // threads per block
+constexpr int CT = 16 * 1024;      // bytes per tile (25 KB of LDS, six blocks per CU: with 32 KB tiles the
+                                   // parse of 4 M rows took 225 instead of 190 us, or 216 in blocks of 512)
+constexpr int CHALO = 1024;        // bytes staged after a tile for the rows that run over its end
+constexpr u64 CSV_SELF = 2048;     // tiles whose counts every block of the parse sums itself; in a longer text the
+constexpr int CG_L = 4;            // count takes groups of tiles, which one block scans
 
-// newline positions (relative to p) among the bytes of one thread's stretch
-// [p, p + len), len <= CPT; bit i of the result marks byte i
-__device__ __forceinline__ u64 newline_mask(const unsigned char* __restrict__ text, u64 p, u64 nbytes)
+// bytes of w that equal the byte c4 repeats, as the high bit of each byte
+__device__ __forceinline__ u32 eq_bytes(u32 w, u32 c4)
 {
-    u64 m = 0;
-    if (p + CPT <= nbytes) {
-        const uint4* q = reinterpret_cast<const uint4*>(text + p);
-        uint4 v[CPT / 16];
-#pragma unroll
-        for (int i = 0; i < CPT / 16; ++i) v[i] = q[i];
-#pragma unroll
-        for (int i = 0; i < CPT / 16; ++i) {
-            const u32 w[4] = {v[i].x, v[i].y, v[i].z, v[i].w};
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-#pragma unroll
-                for (int b = 0; b < 4; ++b)
-                    if (((w[j] >> (8 * b)) & 0xFFu) == 0x0Au) m |= 1ull << (16 * i + 4 * j + b);
-        }
-    } else {
-        for (int i = 0; i < CPT && p + i < nbytes; ++i)
-            if (text[p + i] == '\n') m |= 1ull << i;
-    }
-    return m;
+    const u32 t = w ^ c4;
+    return ~(((t & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | t | 0x7F7F7F7Fu);
+}
+// the four high bits as the low four bits of a word
+__device__ __forceinline__ u32 pack_bytes(u32 z) { return ((z >> 7) * 0x10204080u) >> 28; }
+
+// the 16 bytes at p of the text; bytes past its end are 0
+__device__ __forceinline__ uint4 load16(const unsigned char* __restrict__ text, u64 p, u64 nbytes)
+{
+    if (p + 16 <= nbytes) return *reinterpret_cast<const uint4*>(text + p);
+    u32 v[4] = {0, 0, 0, 0};
+    for (u32 i = 0; i < 16; ++i)
+        if (p + i < nbytes) v[i / 4] |= (u32)text[p + i] << (8 * (i % 4));
+    return make_uint4(v[0], v[1], v[2], v[3]);
 }
 
+// Newlines per group of CG tiles, and per tile as 16 bits of a word (one block
+// scans the groups, and what one CU can read is what bounds that: 18 000 tiles
+// one by one took 18 us, in groups 6; a short text's few tiles are counted each
+// by a block of its own, 5 us less at 2.7 MB); block 0 also clears the result
+// (the parse adds the malformed rows to it and sets the rest).
+template <int CG>
 __global__ void __launch_bounds__(CB) k_csv_count(const unsigned char* __restrict__ text, u64 nbytes,
-                                                  u32* __restrict__ tcnt)
+                                                  u32* __restrict__ gcnt, u64* __restrict__ sub, cv_result* res)
 {
-    __shared__ u32 s_w[CB / WAVE];
-    const u64 p = (u64)blockIdx.x * CT + (u64)threadIdx.x * CPT;
-    u32 c = p < nbytes ? (u32)__popcll(newline_mask(text, p, nbytes)) : 0u;
+    constexpr int Q = CT / 16 / CB;
+    static_assert(CG <= 4 && CT <= 32768, "a tile's count in 16 bits");
+    __shared__ u64 s_w[CB / WAVE];
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        cv_result r = {};
+        *res = r;
+    }
+    const u64 t0 = (u64)blockIdx.x * CG * CT;
+    if (t0 >= nbytes) return;
+    u64 c = 0;
+    uint4 v[CG * Q];
+    const u64 p0 = t0 + 16 * (u64)threadIdx.x;
+    if (t0 + CG * CT <= nbytes) {  // (no test per load: all in flight together)
+#pragma unroll
+        for (int k = 0; k < CG * Q; ++k) v[k] = *reinterpret_cast<const uint4*>(text + p0 + 16 * (u64)(k * CB));
+    } else {
+#pragma unroll
+        for (int k = 0; k < CG * Q; ++k) v[k] = load16(text, p0 + 16 * (u64)(k * CB), nbytes);
+    }
+#pragma unroll
+    for (int k = 0; k < CG * Q; ++k)
+        c += (u64)(u32)(__popc(eq_bytes(v[k].x, 0x0A0A0A0Au)) + __popc(eq_bytes(v[k].y, 0x0A0A0A0Au)) +
+                        __popc(eq_bytes(v[k].z, 0x0A0A0A0Au)) + __popc(eq_bytes(v[k].w, 0x0A0A0A0Au)))
+             << (16 * (k / Q));
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) c += __shfl_xor(c, o, WAVE);
     if (lane_id() == 0) s_w[threadIdx.x / WAVE] = c;
     __syncthreads();
     if (threadIdx.x == 0) {
-        u32 t = 0;
+        u64 t = 0;
         for (int w = 0; w < CB / WAVE; ++w) t += s_w[w];
-        tcnt[blockIdx.x] = t;
+        sub[blockIdx.x] = t;
+        gcnt[blockIdx.x] = (u32)((t & 0xFFFF) + ((t >> 16) & 0xFFFF) + ((t >> 32) & 0xFFFF) + (t >> 48));
     }
 }
 
+// (one block, 8 counts per thread and round, read before any is used)
 __global__ void __launch_bounds__(1024) k_csv_scan(u32* __restrict__ tcnt, u64 tiles)
 {
+    constexpr int P = 8;
     __shared__ u32 s_tmp[1024 / WAVE];
-    u64 carry = 0;
-    for (u64 b = 0; b < tiles; b += 1024) {
-        const u64 i = b + threadIdx.x;
-        const u32 v = i < tiles ? tcnt[i] : 0u;
+    u32 carry = 0;
+    for (u64 b = 0; b < tiles; b += 1024 * P) {
+        const u64 i = b + (u64)threadIdx.x * P;
+        u32 v[P], sum = 0;
+#pragma unroll
+        for (int k = 0; k < P; ++k) v[k] = tcnt[i + k < tiles ? i + k : tiles - 1];
+#pragma unroll
+        for (int k = 0; k < P; ++k) {
+            v[k] = i + k < tiles ? v[k] : 0u;
+            sum += v[k];
+        }
         u32 tot;
-        const u32 ex = block_exclusive_sum<1024>(v, s_tmp, tot);
-        if (i < tiles) tcnt[i] = (u32)(carry + ex);
+        u32 e = carry + block_exclusive_sum<1024>(sum, s_tmp, tot);
+#pragma unroll
+        for (int k = 0; k < P; ++k) {
+            if (i + k < tiles) tcnt[i + k] = e;
+            e += v[k];
+        }
         carry += tot;
-    }
-    if (threadIdx.x == 0) tcnt[tiles] = (u32)carry;
-}
-
-// Line starts: 0 and every byte after a newline, in order, into
-// start[0 .. cap_lines]; a line ends at the next start (its newline
-// included).  start[lines] = nbytes.
-__global__ void __launch_bounds__(CB) k_csv_rows(const unsigned char* __restrict__ text, u64 nbytes,
-                                                 const u32* __restrict__ tpre, u64* __restrict__ start, u64 cap_lines)
-{
-    __shared__ u32 s_tmp[CB / WAVE];
-    const u64 p = (u64)blockIdx.x * CT + (u64)threadIdx.x * CPT;
-    u64 m = p < nbytes ? newline_mask(text, p, nbytes) : 0ull;
-    u32 tot;
-    u32 at = tpre[blockIdx.x] + block_exclusive_sum<CB>((u32)__popcll(m), s_tmp, tot);
-    if (blockIdx.x == 0 && threadIdx.x == 0) start[0] = 0;
-    while (m) {
-        const int b = __ffsll((long long)m) - 1;
-        m &= m - 1;
-        ++at;  // the line after this newline
-        if (at <= cap_lines) start[at] = p + (u64)b + 1;
     }
 }
 
@@ -188,8 +214,6 @@ __device__ __forceinline__ bool parse_decimal(const unsigned char* s, int len, d
     return true;
 }
 
-constexpr int SB = 32 * 1024;  // LDS bytes staged per block
-
 struct Row {
     i64 jid, ts;
     double lat, lon, spd, hdg;
@@ -237,72 +261,342 @@ __device__ __forceinline__ Row parse_row(const unsigned char* s, u64 rl)
     return w;
 }
 
-// The rows that fit the capacity, after the header (meta: header lines
-// skipped, rows to parse), CB per block, one per thread; malformed rows are
-// counted in res->n_bad.  A block's rows are contiguous text: when they fit
-// SB bytes they are staged in LDS with 16-byte loads and parsed from there.
-__global__ void __launch_bounds__(CB) k_csv_parse(const unsigned char* __restrict__ text, u64 nbytes,
-                                                  const u64* __restrict__ start, const u64* __restrict__ meta,
-                                                  cv_records_out o, float* __restrict__ heading,
-                                                  uint8_t* __restrict__ row_ok, cv_result* res)
+// ------------------------------------------------------------------ fields,
+// eight characters at a time from staged text (dwords of LDS)
+
+// the 4 bytes from byte position p
+__device__ __forceinline__ u32 ld4(const u32* s, u32 p)
 {
-    __shared__ __attribute__((aligned(16))) unsigned char s_txt[SB + 16];
-    const u64 first = meta[0], rows = meta[1];
-    const u64 r0 = (u64)blockIdx.x * CB;
-    if (r0 >= rows) return;
-    const u64 r1 = r0 + CB < rows ? r0 + CB : rows;
-    const u64 B0 = start[first + r0], B1 = start[first + r1];
-    const u64 A0 = B0 & ~15ull;
-    const bool staged = B1 - A0 <= SB;
-    if (staged) {
-        for (u64 a = A0 + 16 * (u64)threadIdx.x; a < B1; a += 16 * CB) {
-            if (a + 16 <= nbytes) {
-                *reinterpret_cast<uint4*>(&s_txt[a - A0]) = *reinterpret_cast<const uint4*>(text + a);
-            } else {
-                for (u64 c = a; c < a + 16 && c < nbytes; ++c) s_txt[c - A0] = text[c];
-            }
+    return __builtin_amdgcn_alignbyte(s[(p >> 2) + 1], s[p >> 2], p & 3);
+}
+// the 8 bytes that end before position p
+__device__ __forceinline__ void ld8_end(const u32* s, u32 p, u32& lo, u32& hi)
+{
+    const u32 q = p - 8, i = q >> 2;
+    const u32 a = s[i], b = s[i + 1], c = s[i + 2];
+    lo = __builtin_amdgcn_alignbyte(b, a, q & 3);
+    hi = __builtin_amdgcn_alignbyte(c, b, q & 3);
+}
+
+// whether a byte of d (characters with '0' taken off by xor) is no digit
+__device__ __forceinline__ u32 no_digit(u32 d) { return ((d + 0x76767676u) | d) & 0x80808080u; }
+
+// the number of four digit bytes, the first character lowest
+__device__ __forceinline__ u32 num4(u32 d)
+{
+    return __builtin_amdgcn_udot4(d, 0x0000010Au, 0u, false) * 100u + __builtin_amdgcn_udot4(d, 0x010A0000u, 0u, false);
+}
+
+// The number of the last n (0 .. 8) of the 8 characters before p; false when
+// one of them is no digit.
+__device__ __forceinline__ bool num8(const u32* s, u32 p, u32 n, u32& out)
+{
+    u32 lo, hi;
+    ld8_end(s, p, lo, hi);
+    const u64 keep = n ? ~0ull << (64 - 8 * n) : 0ull;
+    lo = (lo ^ 0x30303030u) & (u32)keep;
+    hi = (hi ^ 0x30303030u) & (u32)(keep >> 32);
+    out = num4(lo) * 10000u + num4(hi);
+    return (no_digit(lo) | no_digit(hi)) == 0;
+}
+
+struct Pow10 {
+    double d[9];
+    u32 u[9];
+};
+
+// A plain decimal of at most 8 digits on either side of its point, as
+// parse_decimal gives it: m / 10^f with m below 2^53.  False for any other
+// form (which parse_decimal then decides).
+__device__ __forceinline__ bool quick_decimal(const u32* s, const Pow10& t, u32 a, u32 e, double& out)
+{
+    if (a >= e) return false;
+    const u32 c0 = ld4(s, a) & 0xFFu;
+    const bool neg = c0 == '-';
+    if (neg || c0 == '+') ++a;
+    const u32 len = e - a;  // (0: no digit below)
+    u32 lo, hi;
+    ld8_end(s, e, lo, hi);
+    const u64 in = len >= 8 ? ~0ull : (len ? ~0ull << (64 - 8 * len) : 0ull);
+    const u64 dots = ((u64)eq_bytes(lo, 0x2E2E2E2Eu) | ((u64)eq_bytes(hi, 0x2E2E2E2Eu) << 32)) & in;
+    u32 frac = 0, whole = len;
+    if (dots) {
+        frac = 7u - (u32)((63 - __clzll((long long)dots)) >> 3);
+        whole = len - frac - 1;
+    }
+    if (whole > 8 || whole + frac == 0) return false;
+    u32 ip, fp;
+    const bool okf = num8(s, e, frac, fp);
+    const bool okw = num8(s, e - frac - (dots ? 1u : 0u), whole, ip);
+    const u64 m = (u64)ip * t.u[frac] + fp;
+    const double v = frac ? (double)m / t.d[frac] : (double)m;
+    out = neg ? -v : v;
+    return okf && okw && m < (1ull << 53);
+}
+
+// "YYYY-MM-DD HH:MM:SS" with an optional fraction of 1 to 3 digits at [a, e);
+// false for anything that parse_ts would refuse
+__device__ __forceinline__ bool quick_ts(const u32* s, u32 a, u32 e, i64& out)
+{
+    const u32 len = e - a;
+    if (len != 19 && (len < 21 || len > 23)) return false;
+    const u32 i = a >> 2, sh = a & 3;
+    u32 x[7], w[6];
+#pragma unroll
+    for (int k = 0; k < 7; ++k) x[k] = s[i + k];
+#pragma unroll
+    for (int k = 0; k < 6; ++k) w[k] = __builtin_amdgcn_alignbyte(x[k + 1], x[k], sh);
+    const u32 f = len == 19 ? 0u : len - 20u;
+    const u32 y = w[0] ^ 0x30303030u, mo = (w[1] ^ 0x30303030u) & 0x00FFFF00u, dh = (w[2] ^ 0x30303030u) & 0xFF00FFFFu;
+    const u32 hm = (w[3] ^ 0x30303030u) & 0xFFFF00FFu, ss = (w[4] ^ 0x30303030u) & 0x00FFFF00u;
+    const u32 fr = (w[5] ^ 0x30303030u) & (f ? 0xFFFFFFFFu >> (32 - 8 * f) : 0u);
+    bool ok = (no_digit(y) | no_digit(mo) | no_digit(dh) | no_digit(hm) | no_digit(ss) | no_digit(fr)) == 0;
+    ok = ok && (w[1] & 0xFF0000FFu) == 0x2D00002Du && (w[2] & 0x00FF0000u) == 0x00200000u &&
+         (w[3] & 0x0000FF00u) == 0x00003A00u && (w[4] & 0x000000FFu) == 0x0000003Au &&
+         (f == 0 || (w[4] >> 24) == '.');
+    const u32 yy = num4(y);
+    const u32 m = __builtin_amdgcn_udot4(mo, 0x00010A00u, 0u, false);
+    const u32 d = __builtin_amdgcn_udot4(dh, 0x0000010Au, 0u, false);
+    const u32 h = (dh >> 24) * 10u + (hm & 0xFFu);
+    const u32 mi = __builtin_amdgcn_udot4(hm, 0x010A0000u, 0u, false);
+    const u32 se = __builtin_amdgcn_udot4(ss, 0x00010A00u, 0u, false);
+    const u32 ms = __builtin_amdgcn_udot4(fr, 0x00010A64u, 0u, false);
+    const bool leap = (yy % 4 == 0 && yy % 100 != 0) || yy % 400 == 0;
+    const u32 days = m == 2 ? 28u + (leap ? 1u : 0u) : 30u + ((m + (m >> 3)) & 1u);
+    ok = ok && yy >= 1 && m >= 1 && m <= 12 && d >= 1 && d <= days && h <= 23 && mi <= 59 && se <= 59;
+    // days since 1970-01-01 (eras of 400 years, March-based years)
+    const u32 ym = yy - (m <= 2 ? 1u : 0u);
+    const u32 era = ym / 400u, yoe = ym - era * 400u;
+    const u32 doy = (153u * (m > 2 ? m - 3u : m + 9u) + 2u) / 5u + d - 1u;
+    const u32 doe = yoe * 365u + yoe / 4u - yoe / 100u + doy;
+    const i64 day = (i64)era * 146097 + (i64)doe - 719468;
+    out = day * 86400000 + (i64)((h * 60u + mi) * 60000u + se * 1000u + ms);
+    return ok;
+}
+
+// 64 bits of a byte mask from bit p
+__device__ __forceinline__ u64 bits_from(const u64* m, u32 p)
+{
+    const u32 b = p & 63;
+    return b ? (m[p >> 6] >> b) | (m[(p >> 6) + 1] << (64 - b)) : m[p >> 6];
+}
+
+// The rows that start in the block's tile (line r starts at byte 0 or after
+// newline r - 1; base: newlines before the tile), one per thread and round;
+// header lines are skipped, rows past cap counted only.  The block of the last
+// tile writes the row count.
+constexpr int CST = CT + CHALO;      // staged bytes
+constexpr int CSW = CST / 64;        // words of a byte mask
+constexpr int CFRONT = 16;           // bytes before the first staged one (reads end at a position)
+constexpr int CROWS = 512;           // row starts listed per round
+__global__ void __launch_bounds__(CB) k_csv_parse(const unsigned char* __restrict__ text, u64 nbytes,
+                                                  const u32* __restrict__ gcnt, const u64* __restrict__ sub, u32 tiles,
+                                                  u32 CG, int summed, int header,
+                                                  cv_records_out o, float* __restrict__ heading,
+                                                  uint8_t* __restrict__ row_ok, u64 cap, cv_result* res)
+{
+    static_assert(CT % (64 * CB) == 0, "whole mask words per thread");
+    constexpr int WPT = CT / 64 / CB;  // newline words per thread
+    __shared__ __attribute__((aligned(16))) u32 s_txt[(CFRONT + CST + 32) / 4];
+    __shared__ __attribute__((aligned(8))) uint16_t s_nl[CST / 16 + 4], s_cm[CST / 16 + 12], s_qt[CST / 16 + 12];
+    __shared__ uint16_t s_row[CROWS];
+    __shared__ u32 s_tmp[CB / WAVE];
+    __shared__ Pow10 s_p;
+    const int tid = threadIdx.x;
+    const u64 t0 = (u64)blockIdx.x * CT;
+    const u64 left = nbytes - t0;
+    const u32 avail = left < (u64)CST ? (u32)left : (u32)CST;  // staged bytes of the text
+    // 1. the text and its bits
+    constexpr int Q = CT / 16 / CB;
+    static_assert(Q * CB * 16 == CT && CHALO / 16 <= CB, "whole rounds, then one for the bytes after the tile");
+    uint4 tv[Q + 1];
+    const u32 hc = (u32)(CT / 16) + (tid < CHALO / 16 ? tid : 0);  // (spare threads repeat the first)
+    if (t0 + CST <= nbytes) {
+#pragma unroll
+        for (int k = 0; k < Q; ++k) tv[k] = *reinterpret_cast<const uint4*>(text + t0 + 16 * (u64)(k * CB + tid));
+        tv[Q] = *reinterpret_cast<const uint4*>(text + t0 + 16 * (u64)hc);
+    } else {
+#pragma unroll
+        for (int k = 0; k < Q; ++k) tv[k] = load16(text, t0 + 16 * (u64)(k * CB + tid), nbytes);
+        tv[Q] = load16(text, t0 + 16 * (u64)hc, nbytes);
+    }
+#pragma unroll
+    for (int r = 0; r <= Q; ++r) {
+        if (r == Q && tid >= CHALO / 16) break;
+        const u32 c = r < Q ? (u32)(r * CB + tid) : hc;
+        const uint4 v = tv[r];
+        *reinterpret_cast<uint4*>(&s_txt[CFRONT / 4 + 4 * c]) = v;
+        const u32 x[4] = {v.x, v.y, v.z, v.w};
+        u32 nl = 0, cm = 0, qt = 0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            nl |= pack_bytes(eq_bytes(x[k], 0x0A0A0A0Au)) << (4 * k);
+            cm |= pack_bytes(eq_bytes(x[k], 0x2C2C2C2Cu)) << (4 * k);
+            qt |= pack_bytes(eq_bytes(x[k], 0x22222222u)) << (4 * k);
+        }
+        s_nl[c] = (uint16_t)nl;
+        s_cm[c] = (uint16_t)cm;
+        s_qt[c] = (uint16_t)qt;
+    }
+    if (tid < 12) {
+        s_cm[CST / 16 + tid] = 0;
+        s_qt[CST / 16 + tid] = 0;
+        if (tid < 4) s_txt[tid] = 0;
+        if (tid < 8) s_txt[(CFRONT + CST) / 4 + tid] = 0;
+    }
+    if (tid < 9) {
+        double d = 1.0;
+        u32 u = 1;
+        for (int k = 0; k < tid; ++k) {
+            d *= 10.0;
+            u *= 10u;
+        }
+        s_p.d[tid] = d;  // exact
+        s_p.u[tid] = u;
+    }
+    // 2. newlines before the tile
+    const u32 grp = blockIdx.x / CG;
+    u32 base;
+    if (summed) {
+        base = gcnt[grp];
+        __syncthreads();
+    } else {
+        u32 v = 0;
+        for (u32 i = tid; i < grp; i += CB) v += gcnt[i];
+        block_exclusive_sum<CB>(v, s_tmp, base);
+    }
+    {
+        u64 t = sub[grp];
+        for (u32 k = blockIdx.x % CG; k > 0; --k, t >>= 16) base += (u32)(t & 0xFFFF);
+    }
+    // the line that starts at the tile's first byte, if one does
+    const bool first = t0 == 0 || text[t0 - 1] == '\n';
+    const u64* nlw = reinterpret_cast<const u64*>(s_nl);
+    const u64* cmw = reinterpret_cast<const u64*>(s_cm);
+    const u64* qtw = reinterpret_cast<const u64*>(s_qt);
+    // 3. newlines of the tile that start a row inside it
+    u64 m[WPT];
+    u32 c = 0, allnl = 0;
+#pragma unroll
+    for (int k = 0; k < WPT; ++k) {
+        m[k] = nlw[tid * WPT + k];
+        allnl += (u32)__popcll(m[k]);
+        if (tid == CB - 1 && k == WPT - 1) m[k] &= ~(1ull << 63);  // the next tile's first byte
+        if (tid * WPT * 64 + 64 * (k + 1) >= (int)avail) {
+            // a newline that ends the text starts no row
+            const int last = (int)avail - 1 - (tid * WPT + k) * 64;
+            if (last < 64) m[k] &= last <= 0 ? 0ull : ((1ull << last) - 1);
+        }
+        c += (u32)__popcll(m[k]);
+    }
+    u32 starts;
+    const u32 before = block_exclusive_sum<CB>(c, s_tmp, starts);
+    const u32 R = starts + (first ? 1u : 0u);
+    const u64 line0 = (u64)base + (first ? 0 : 1);  // line of the tile's first row
+    if (blockIdx.x == tiles - 1) {
+        u32 nl;
+        block_exclusive_sum<CB>(allnl, s_tmp, nl);
+        if (tid == 0) {
+            const u64 lines = (u64)base + nl + (text[nbytes - 1] != '\n' ? 1 : 0);
+            const u64 rows = lines - ((header && lines) ? 1 : 0);
+            res->status = rows > cap ? CV_ERR_CAPACITY : CV_OK;
+            res->count = rows;
+            res->required = rows > cap ? rows : 0;
         }
     }
-    __syncthreads();
-    u64 bad = 0;
-    const u64 r = r0 + threadIdx.x;
-    if (r < r1) {
-        const u64 b = start[first + r];
-        const u64 rl = start[first + r + 1] - b;  // the row's bytes, its line end included
-        const Row w = staged ? parse_row(s_txt + (b - A0), rl) : parse_row(text + b, rl);
-        bad += w.ok ? 0 : 1;
-        o.journey_id[r] = w.jid;
-        o.ts_ms[r] = w.ts;
-        o.lat_deg[r] = w.lat;
-        o.lon_deg[r] = w.lon;
-        o.speed_mps[r] = (float)w.spd;
-        if (heading) heading[r] = (float)w.hdg;
-        if (row_ok) row_ok[r] = w.ok ? 1 : 0;
+    u32 bad = 0;
+    for (u32 r0 = 0; r0 < R; r0 += CROWS) {
+        // starts of rows [r0, r0 + CROWS)
+        if (first && r0 == 0 && tid == 0) s_row[0] = 0;
+        u32 k = before + (first ? 1u : 0u);
+#pragma unroll
+        for (int q = 0; q < WPT; ++q) {
+            u64 x = m[q];
+            const u32 n = (u32)__popcll(x);
+            if (k + n > r0 && k < r0 + CROWS) {
+                for (u32 j = k; x; ++j, x &= x - 1)
+                    if (j >= r0 && j < r0 + CROWS)
+                        s_row[j - r0] = (uint16_t)((tid * WPT + q) * 64 + __ffsll((long long)x));
+            }
+            k += n;
+        }
+        __syncthreads();
+        const u32 rn = R - r0 < CROWS ? R - r0 : CROWS;
+        for (u32 j = tid; j < rn; j += CB) {
+            const u64 line = line0 + r0 + j;
+            if (header && line == 0) continue;
+            const u64 row = line - (header ? 1 : 0);
+            if (row >= cap) continue;
+            const u32 a = s_row[j];
+            // its end: the next newline, or the end of the text
+            u32 wi = a >> 6;
+            u64 x = nlw[wi] & (~0ull << (a & 63));
+            while (!x && wi + 1 < (u32)CSW) x = nlw[++wi];
+            Row w;
+            bool done = false;
+            u32 e = 0;
+            const bool whole = x || t0 + CST >= nbytes;  // the row's end is staged
+            if (whole) {
+                e = x ? (wi << 6) + (u32)__ffsll((long long)x) - 1 : avail;
+                u32 z = e;
+                if (z > a && ((ld4(s_txt, CFRONT + z - 1) & 0xFFu) == '\r')) --z;
+                const u32 len = z - a;
+                if (len <= 128 && len > 0) {
+                    const u64 in0 = len >= 64 ? ~0ull : (1ull << len) - 1;
+                    const u64 in1 = len > 64 ? (len == 128 ? ~0ull : (1ull << (len - 64)) - 1) : 0ull;
+                    u64 lo = bits_from(cmw, a) & in0, hi = bits_from(cmw, a + 64) & in1;
+                    const bool quote = ((bits_from(qtw, a) & in0) | (bits_from(qtw, a + 64) & in1)) != 0;
+                    if (__popcll(lo) + __popcll(hi) == 6 && !quote) {
+                        u32 cp[6];
+#pragma unroll
+                        for (int q = 0; q < 6; ++q) {
+                            const bool l = lo != 0;
+                            const u64 y = l ? lo : hi;
+                            cp[q] = CFRONT + a + (l ? 0u : 64u) + (u32)__ffsll((long long)y) - 1u;
+                            if (l) lo &= lo - 1;
+                            else hi &= hi - 1;
+                        }
+                        const u32 p0 = CFRONT + a, pe = CFRONT + z;
+                        const u32 idn = cp[0] - p0;
+                        // the id's bytes, first one highest
+                        const u64 raw = (u64)ld4(s_txt, p0) | ((u64)ld4(s_txt, p0 + 4) << 32);
+                        const u64 id = __builtin_bswap64(raw) & (idn >= 1 && idn < 8 ? ~0ull << (64 - 8 * idn) : ~0ull);
+                        w.jid = (i64)id;
+                        done = idn >= 1 && idn <= 8 && (id >> 63) == 0;
+                        done = quick_ts(s_txt, cp[0] + 1, cp[1], w.ts) && done;
+                        done = quick_decimal(s_txt, s_p, cp[1] + 1, cp[2], w.lat) && done;
+                        done = quick_decimal(s_txt, s_p, cp[2] + 1, cp[3], w.lon) && done;
+                        done = quick_decimal(s_txt, s_p, cp[4] + 1, cp[5], w.spd) && done;
+                        w.hdg = __builtin_nan("");
+                        if (cp[5] + 1 < pe) done = quick_decimal(s_txt, s_p, cp[5] + 1, pe, w.hdg) && done;
+                        w.ok = true;
+                    }
+                }
+            }
+            if (!done) {
+                if (whole) {
+                    // its line end included when it has one
+                    w = parse_row((const unsigned char*)s_txt + CFRONT + a, (u64)(e - a) + (x ? 1 : 0));
+                } else {
+                    u64 q = t0 + CST;
+                    while (q < nbytes && text[q] != '\n') ++q;
+                    w = parse_row(text + t0 + a, (q < nbytes ? q + 1 : nbytes) - (t0 + a));
+                }
+            }
+            bad += w.ok ? 0u : 1u;
+            o.journey_id[row] = w.jid;
+            o.ts_ms[row] = w.ts;
+            o.lat_deg[row] = w.lat;
+            o.lon_deg[row] = w.lon;
+            o.speed_mps[row] = (float)w.spd;
+            if (heading) heading[row] = (float)w.hdg;
+            if (row_ok) row_ok[row] = w.ok ? 1 : 0;
+        }
+        __syncthreads();
     }
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) bad += __shfl_xor(bad, d, WAVE);
     if (lane_id() == 0 && bad) atomicAdd((unsigned long long*)&res->n_bad, (unsigned long long)bad);
-}
-
-// result: rows = lines (a last line without its newline counts) minus the header
-__global__ void k_csv_begin(const u32* __restrict__ tcnt, u64 tiles, const unsigned char* __restrict__ text,
-                            u64 nbytes, int header, u64 cap, u64* __restrict__ start, u64* __restrict__ meta,
-                            cv_result* res)
-{
-    if (threadIdx.x != 0) return;
-    const u64 nl = tcnt[tiles];
-    const u64 lines = nl + ((nbytes && text[nbytes - 1] != '\n') ? 1 : 0);
-    const u64 skip = (header && lines) ? 1 : 0;
-    const u64 rows = lines - skip;
-    // the end of the last line, when it lies within the offsets kept
-    if (lines <= cap + skip) start[lines] = nbytes;
-    meta[0] = skip;
-    meta[1] = rows < cap ? rows : cap;
-    cv_result r = {};
-    r.status = rows > cap ? CV_ERR_CAPACITY : CV_OK;
-    r.count = rows;
-    r.required = rows > cap ? rows : 0;
-    *res = r;
 }
 
 }  // namespace
@@ -335,24 +629,18 @@ cv_status cv_csv_extract(const char* text, uint64_t nbytes, int32_t has_header, 
     cvh::TimedScope ts_("csv_extract", s);
     const u64 tiles = (nbytes + CT - 1) / CT;
     cvh::Carver c(ws);
-    u32* tcnt = c.take<u32>(tiles + 1);
-    u64* start = c.take<u64>(capacity + 3);
-    u64* meta = c.take<u64>(2);
+    const bool summed = tiles > CSV_SELF;
+    const u32 cg = summed ? CG_L : 1;
+    const u64 groups = (tiles + cg - 1) / cg;
+    u64* sub = c.take<u64>(groups);
+    u32* gcnt = c.take<u32>(groups);
     const unsigned char* t = (const unsigned char*)text;
-    if (tiles) hipLaunchKernelGGL(k_csv_count, dim3((unsigned)tiles), dim3(CB), 0, s, t, (u64)nbytes, tcnt);
-    hipLaunchKernelGGL(k_csv_scan, dim3(1), dim3(1024), 0, s, tcnt, tiles);
-    // offsets of the first capacity + 1 (+ header) lines
-    const u64 cap_lines = capacity + 2;
-    if (tiles)
-        hipLaunchKernelGGL(k_csv_rows, dim3((unsigned)tiles), dim3(CB), 0, s, t, (u64)nbytes, tcnt, start,
-                           cap_lines);
-    else
-        cvh::fill_u64(start, 0ull, 1, s);
-    hipLaunchKernelGGL(k_csv_begin, dim3(1), dim3(64), 0, s, tcnt, tiles, t, (u64)nbytes, has_header ? 1 : 0,
-                       (u64)capacity, start, meta, res);
-    if (capacity)
-        hipLaunchKernelGGL(k_csv_parse, dim3((unsigned)((capacity + CB - 1) / CB)), dim3(CB), 0, s, t, (u64)nbytes,
-                           start, meta, *out, heading_deg, row_ok, res);
+    hipLaunchKernelGGL(summed ? k_csv_count<CG_L> : k_csv_count<1>, dim3((unsigned)(groups ? groups : 1)), dim3(CB), 0, s,
+                       t, (u64)nbytes, gcnt, sub, res);
+    if (!tiles) return cvh::last_launch_status();
+    if (summed) hipLaunchKernelGGL(k_csv_scan, dim3(1), dim3(1024), 0, s, gcnt, groups);
+    hipLaunchKernelGGL(k_csv_parse, dim3((unsigned)tiles), dim3(CB), 0, s, t, (u64)nbytes, gcnt, sub, (u32)tiles, cg,
+                       summed ? 1 : 0, has_header ? 1 : 0, *out, heading_deg, row_ok, (u64)capacity, res);
     return cvh::last_launch_status();
 }
 
