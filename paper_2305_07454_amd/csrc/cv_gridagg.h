@@ -112,16 +112,13 @@ __device__ __forceinline__ Fx192 run_sum192(const RunPart& p)
     return r;
 }
 
-// one step of a cross-lane reduction or scan: fold in the partial d lanes away
-// (xor: full reduction; up: the lane below) when `take`
-__device__ __forceinline__ void run_step(RunPart& p, int d, bool up, bool take)
+// step K of the segmented scan below (take: scan_takes' bits)
+template <int K>
+__device__ __forceinline__ void run_scan_step(RunPart& p, u32 take)
 {
-    const u64 lo = up ? (u64)__shfl_up((unsigned long long)p.lo, d, WAVE) : (u64)__shfl_xor((unsigned long long)p.lo, d, WAVE);
-    const u64 hi = up ? (u64)__shfl_up((unsigned long long)p.hi, d, WAVE) : (u64)__shfl_xor((unsigned long long)p.hi, d, WAVE);
-    const u32 cn = up ? (u32)__shfl_up(p.cn, d, WAVE) : (u32)__shfl_xor(p.cn, d, WAVE);
-    const u32 mn = up ? (u32)__shfl_up(p.mn, d, WAVE) : (u32)__shfl_xor(p.mn, d, WAVE);
-    const u32 mx = up ? (u32)__shfl_up(p.mx, d, WAVE) : (u32)__shfl_xor(p.mx, d, WAVE);
-    if (take) {
+    const u64 lo = scan_move<K>(p.lo, 0ull), hi = scan_move<K>(p.hi, 0ull);
+    const u32 cn = scan_move<K>(p.cn, 0u), mn = scan_move<K>(p.mn, ~0u), mx = scan_move<K>(p.mx, 0u);
+    if ((take >> K) & 1u) {
         add128(p.lo, p.hi, lo, hi);
         p.cn += cn;
         p.mn = mn < p.mn ? mn : p.mn;
@@ -129,28 +126,22 @@ __device__ __forceinline__ void run_step(RunPart& p, int d, bool up, bool take)
     }
 }
 
-__device__ __forceinline__ void run_wave_reduce(RunPart& p)
-{
-#pragma unroll
-    for (int d = 1; d < WAVE; d <<= 1) run_step(p, d, false, true);
-}
-
 // segmented inclusive scan across lanes; `head` starts a segment
 __device__ __forceinline__ void run_seg_scan(RunPart& p, bool head)
 {
-    const int l = lane_id();
-    u32 take = 0;
-    bool f = head;
-#pragma unroll
-    for (int k = 0, d = 1; d < WAVE; ++k, d <<= 1) {
-        const bool fo = __shfl_up(f, d, WAVE);
-        if (l >= d) {
-            if (!f) take |= 1u << k;
-            f = f || fo;
-        }
-    }
-#pragma unroll
-    for (int k = 0, d = 1; d < WAVE; ++k, d <<= 1) run_step(p, d, true, ((take >> k) & 1u) != 0);
+    const u32 take = scan_takes(__ballot(head));
+    run_scan_step<0>(p, take);
+    run_scan_step<1>(p, take);
+    run_scan_step<2>(p, take);
+    run_scan_step<3>(p, take);
+    run_scan_step<4>(p, take);
+    run_scan_step<5>(p, take);
+}
+
+// the lane below's partial (lane 0: its own)
+__device__ __forceinline__ RunPart run_below(const RunPart& p)
+{
+    return RunPart{lane_below(p.lo), lane_below(p.hi), lane_below(p.cn), lane_below(p.mn), lane_below(p.mx)};
 }
 
 // Where a tile's group contributions go: the serving form's resident HBM
@@ -323,10 +314,10 @@ k_grid_agg(u32 n, const i64* __restrict__ jid, const i64* __restrict__ ts, const
                 if (g.sout) atomicAdd((unsigned long long*)&g.sout[sh], 1ull);
             }
         }
-        const i64 jp = __shfl_up(vj[rr], 1, WAVE);
-        const i64 tbp = __shfl_up(tb, 1, WAVE);
-        const u32 ltp = Pol::kStream ? (u32)__shfl_up((u32)vlt[rr], 1, WAVE) : 0u;
-        const i64 kp = __shfl_up(k, 1, WAVE);
+        const i64 jp = lane_below(vj[rr]);
+        const i64 tbp = lane_below(tb);
+        const u32 ltp = Pol::kStream ? lane_below((u32)vlt[rr]) : 0u;
+        const i64 kp = lane_below(k);
         if (lane == WAVE - 1) {
             s_lj[rr][w] = vj[rr];
             s_ltb[rr][w] = tb;
@@ -627,12 +618,7 @@ k_grid_agg(u32 n, const i64* __restrict__ jid, const i64* __restrict__ ts, const
         RunPart out = cur;
         run_seg_scan(out, hh);
         // the run open below this lane: the scan's value of the lane below
-        RunPart in;
-        in.lo = (u64)__shfl_up((unsigned long long)out.lo, 1, WAVE);
-        in.hi = (u64)__shfl_up((unsigned long long)out.hi, 1, WAVE);
-        in.cn = (u32)__shfl_up(out.cn, 1, WAVE);
-        in.mn = (u32)__shfl_up(out.mn, 1, WAVE);
-        in.mx = (u32)__shfl_up(out.mx, 1, WAVE);
+        RunPart in = run_below(out);
         if (l == 0) run_reset(in);
         if (hh && l > 0) {
             run_combine(in, pre);

@@ -360,14 +360,14 @@ __global__ void __launch_bounds__(256) k_dict_insert(const i64* __restrict__ jid
             {
                 // time order against the record before (none before record 0
                 // and before a shard's first record)
-                const u64 tp = __shfl_up(tv[k], 1, WAVE);
+                const u64 tp = lane_below(tv[k]);
                 const u64 tq = l == 0 ? prevt : tp;
                 if (valid && i > 0 && !sstart && tv[k] < tq) down = true;
                 prevt = __shfl(tv[k], WAVE - 1, WAVE);
             }
             // a record repeating the id before it adds nothing (in the
             // batched form, unless a shard starts at it)
-            const i64 jp = __shfl_up(j, 1, WAVE);
+            const i64 jp = lane_below(j);
             const bool dup = (l == 0 ? (hp && j == prevj) : j == jp) && !(SHARDS && sstart);
             prevj = __shfl(j, WAVE - 1, WAVE);
             hp = true;
@@ -757,7 +757,7 @@ __global__ void __launch_bounds__(256) k_pack_hist(const i64* __restrict__ jid, 
             // only the first lane of each run of equal ids probes the dictionary;
             // the others take its rank (lane 0 continues the carried run)
             const u64 j = valid ? jv[k] : EMPTY;
-            const u64 jp = __shfl_up(j, 1, WAVE);
+            const u64 jp = lane_below(j);
             const bool runhead = l == 0 ? !(hc && j == cj) : j != jp;
             u32 r = 0;
             const bool look = valid && runhead && j != EMPTY;
@@ -1402,9 +1402,9 @@ __global__ void __launch_bounds__(256) k_gather_feat(u32 n, const SortMeta* m, c
     for (int u = 0; u < GFI; ++u) {
         const long k = kk[u];
         const int g = u * NWB + w;
-        i64 pj = __shfl_up(oj[u], 1, WAVE), pt = __shfl_up(ot[u], 1, WAVE);
-        double pla = __shfl_up(ola[u], 1, WAVE), plo = __shfl_up(olo[u], 1, WAVE);
-        double psph = __shfl_up(osph[u], 1, WAVE), pcph = __shfl_up(ocph[u], 1, WAVE);
+        i64 pj = lane_below(oj[u]), pt = lane_below(ot[u]);
+        double pla = lane_below(ola[u]), plo = lane_below(olo[u]);
+        double psph = lane_below(osph[u]), pcph = lane_below(ocph[u]);
         if (l == 0) {
             pj = e_jid[g + 1];
             pt = e_ts[g + 1];
@@ -1443,8 +1443,8 @@ __global__ void __launch_bounds__(256) k_gather_feat(u32 n, const SortMeta* m, c
     for (int u = 0; u < GFI; ++u) {
         const long k = kk[u];
         const int g = u * NWB + w;
-        u32 pf = (u32)__shfl_up((int)ks[u].f, 1, WAVE);
-        double pv = __shfl_up(ks[u].v, 1, WAVE), pb = __shfl_up(ks[u].b, 1, WAVE);
+        u32 pf = lane_below(ks[u].f);
+        double pv = lane_below(ks[u].v), pb = lane_below(ks[u].b);
         if (l == 0) {
             pf = e_f[g + 1];
             pv = e_v[g + 1];

@@ -62,7 +62,7 @@ __device__ __forceinline__ u64 heads_of(i64 jv, u64 a, u64 end, i64& jprev, cons
     const int l = lane_id();
     const u64 r = a + l;
     const bool valid = r < end;
-    i64 jp = __shfl_up(jv, 1, WAVE);
+    i64 jp = lane_below(jv);
     if (l == 0) jp = jprev;
     jprev = __shfl(jv, WAVE - 1, WAVE);
     smask = 0;
@@ -337,75 +337,75 @@ __device__ __forceinline__ void part_combine(PartSum& a, const PartSum& b)
     a.n += b.n;
 }
 
-// Cross-lane steps work one field at a time, so that only that field's
-// shuffled copy is live next to the partial.  A step of distance d takes the
-// lane d away (xor for the full reduction, below for the segmented scan);
-// `take` says whether the step folds it in.
-__device__ __forceinline__ u64 shfl64(u64 v, int d, bool up)
+// Cross-lane steps work one field at a time, so that only that field's moved
+// copy is live next to the partial.  Step K of the segmented scan folds in the
+// lane that scan_move brings (where scan_takes' bit K says so); a step of the
+// full reduction the lane 2^K away by xor.
+template <int K, bool SCAN, class T>
+__device__ __forceinline__ T part_move(T v, typename std::common_type<T>::type none)
 {
-    return up ? (u64)__shfl_up((unsigned long long)v, d, WAVE) : (u64)__shfl_xor((unsigned long long)v, d, WAVE);
-}
-__device__ __forceinline__ u32 shfl32(u32 v, int d, bool up)
-{
-    return up ? (u32)__shfl_up(v, d, WAVE) : (u32)__shfl_xor(v, d, WAVE);
+    if constexpr (SCAN) return scan_move<K>(v, none);
+    else return (T)__shfl_xor(v, 1 << K, WAVE);
 }
 
-__device__ __forceinline__ void part_step(PartBox& p, int d, bool up, bool take)
+template <int K, bool SCAN>
+__device__ __forceinline__ void part_step(PartBox& p, u32 takes)
 {
+    const bool take = !SCAN || ((takes >> K) & 1u);
     u64 v;
-    v = shfl64(p.latmin, d, up);
+    v = part_move<K, SCAN>(p.latmin, ~0ull);
     if (take && v < p.latmin) p.latmin = v;
-    v = shfl64(p.latmax, d, up);
+    v = part_move<K, SCAN>(p.latmax, 0ull);
     if (take && v > p.latmax) p.latmax = v;
-    v = shfl64(p.lonmin, d, up);
+    v = part_move<K, SCAN>(p.lonmin, ~0ull);
     if (take && v < p.lonmin) p.lonmin = v;
-    v = shfl64(p.lonmax, d, up);
+    v = part_move<K, SCAN>(p.lonmax, 0ull);
     if (take && v > p.lonmax) p.lonmax = v;
-    const u32 x = shfl32(p.count, d, up);
+    const u32 x = part_move<K, SCAN>(p.count, 0u);
     if (take) p.count += x;
 }
-__device__ __forceinline__ void part_step(PartSum& p, int d, bool up, bool take)
+template <int K, bool SCAN>
+__device__ __forceinline__ void part_step(PartSum& p, u32 takes)
 {
-    const u64 dlo = shfl64(p.dlo, d, up), dhi = shfl64(p.dhi, d, up);
+    const bool take = !SCAN || ((takes >> K) & 1u);
+    const u64 dlo = part_move<K, SCAN>(p.dlo, 0ull), dhi = part_move<K, SCAN>(p.dhi, 0ull);
     if (take) add128(p.dlo, p.dhi, dlo, dhi);
-    const u64 slo = shfl64(p.slo, d, up), shi = shfl64(p.shi, d, up);
+    const u64 slo = part_move<K, SCAN>(p.slo, 0ull), shi = part_move<K, SCAN>(p.shi, 0ull);
     if (take) add128(p.slo, p.shi, slo, shi);
-    const u64 v = shfl64(p.maxd, d, up);
+    const u64 v = part_move<K, SCAN>(p.maxd, 0ull);
     if (take && v > p.maxd) p.maxd = v;
     u32 x;
-    x = shfl32(p.ndtz, d, up);
+    x = part_move<K, SCAN>(p.ndtz, 0u);
     if (take) p.ndtz += x;
-    x = shfl32(p.maxs, d, up);
+    x = part_move<K, SCAN>(p.maxs, 0u);
     if (take && x > p.maxs) p.maxs = x;
-    x = shfl32(p.n, d, up);
+    x = part_move<K, SCAN>(p.n, 0u);
     if (take) p.n += x;
+}
+
+template <bool SCAN, class P>
+__device__ __forceinline__ void part_steps(P& p, u32 takes)
+{
+    part_step<0, SCAN>(p, takes);
+    part_step<1, SCAN>(p, takes);
+    part_step<2, SCAN>(p, takes);
+    part_step<3, SCAN>(p, takes);
+    part_step<4, SCAN>(p, takes);
+    part_step<5, SCAN>(p, takes);
 }
 
 // full wave reduction; every lane ends with the total
 template <class P>
 __device__ __forceinline__ void part_wave_reduce(P& p)
 {
-#pragma unroll
-    for (int d = 1; d < WAVE; d <<= 1) part_step(p, d, false, true);
+    part_steps<false>(p, 0u);
 }
 
 // segmented inclusive scan across lanes; `head` starts a segment
 template <class P>
 __device__ __forceinline__ void part_seg_scan(P& p, bool head)
 {
-    const int l = lane_id();
-    u32 take = 0;
-    bool f = head;
-#pragma unroll
-    for (int k = 0, d = 1; d < WAVE; ++k, d <<= 1) {
-        const bool fo = __shfl_up(f, d, WAVE);
-        if (l >= d) {
-            if (!f) take |= 1u << k;
-            f = f || fo;
-        }
-    }
-#pragma unroll
-    for (int k = 0, d = 1; d < WAVE; ++k, d <<= 1) part_step(p, d, true, ((take >> k) & 1u) != 0);
+    part_steps<true>(p, scan_takes(__ballot(head)));
 }
 
 struct Out {
