@@ -473,6 +473,11 @@ static cv_status grid_impl(const cv_records* sorted, const u64* soff, u32 S, con
     g.t0 = grid->t0_ms;
     g.bin_ms = grid->bin_ms;
     g.tinv = 1.0 / (double)grid->bin_ms;
+    g.rlat = 1.0 / grid->dlat_deg;
+    g.rlon = 1.0 / grid->dlon_deg;
+    g.cells = (u64)grid->n_lat * (u64)grid->n_lon;
+    const auto inverts = [](double d) { return d > 1e-100 && d < 1e100; };
+    g.quick = grid->bin_ms < (1ll << 30) && g.cells < (1ull << 32) && inverts(grid->dlat_deg) && inverts(grid->dlon_deg);
     g.tmax = grid->n_t > 0 ? grid->n_t : (INT64_MAX / (grid->n_lat * grid->n_lon * (i64)(nd + 1)));
     g.soff = soff;
     g.S = S;

@@ -34,7 +34,6 @@ constexpr uint16_t H_ACC = 0x4000;   // a root with an accumulator (its index in
 // other values: the head index of the run's root (which holds H_ACC)
 constexpr uint16_t L_SEG = 0x8000;   // s_lpos: the head starts a (journey, time-bin) segment
 constexpr uint16_t L_ODD = 0x4000;   // s_lpos: the head's record has a speed outside the fast format
-constexpr uint8_t B_ODD = 32;        // record speed outside the 128-bit fast format
 constexpr u32 PART_ODD = 0x80000000u;
 
 // Where the partial rows go: a region of GT rows per tile, their count and
@@ -71,6 +70,15 @@ __device__ __forceinline__ GPart make_part(i64 jid, u64 lo, u64 hi, u32 cn, u32 
     return p;
 }
 
+// What bounds it: instructions (keys, run scans) and the latency of the LDS
+// passes between its barriers; its 29-36 bytes per record need half of its time.
+// Each wave takes WREC consecutive records, so the record before a row is the
+// row before's last lane, which the wave holds in scalar registers: no exchange
+// through LDS and no barrier before the run starts are known (rows striped over
+// the block needed both, and the time bin and flags kept per row).  Keys are
+// made by reciprocals with 32-bit arithmetic (grid_key_quick).  123 M records,
+// 0.01 deg x 15 min: 1541 -> 1263 us (3.6 GB, 2.8 TB/s); batched, 100 M in
+// 1000 shards, 0.001 deg x 1 min: 2781 -> 2362; headings, 24 M: 395 -> 292.
 // Four waves per SIMD for the plain key (what the LDS allows); the direction
 // forms carry a heading or bearing column too and keep three, which their
 // registers need without spilling.
@@ -97,22 +105,23 @@ k_grid_part(u32 n, const i64* __restrict__ jid, const i64* __restrict__ ts, cons
     __shared__ u64 s_c0[PR_MAX], s_c1[PR_MAX];  // sum: two carry-save 43-bit chunks (mod 2^86)
     __shared__ u32 s_cn[PR_MAX], s_mn[PR_MAX], s_mx[PR_MAX];
     __shared__ uint16_t s_orow[PR_MAX], s_opos[PR_MAX], s_ohead[PR_MAX];  // accumulator -> row, root position, head
-    __shared__ i64 s_lj[GI][NWG], s_ltb[GI][NWG], s_lk[GI][NWG];  // lane 63 of every wave row
     __shared__ u32 s_cnt[GI * NWG];
-    __shared__ uint8_t s_rodd[GI][NWG];
     __shared__ u64 s_tmp[GB / WAVE];
     __shared__ u32 s_tmp32[GB / WAVE];
     __shared__ u64 s_red[GB / WAVE];
 
     const int t = threadIdx.x;
     const int lane = lane_id();
-    const int w = t / WAVE;
+    const int w = __builtin_amdgcn_readfirstlane(t / WAVE);
     const u64 tile0 = (u64)blockIdx.x * GT;
     const u32 tvalid = (u32)((u64)n - tile0 < (u64)GT ? (u64)n - tile0 : (u64)GT);
 
-    // 1. the tile's records, rows of GB striped over the block (coalesced);
-    //    every column is loaded first so that all loads are in flight together
-    i64 vj[FL ? 1 : GI], vt[GI], vtb[GI], vk[GI];
+    // 1. the wave's records, WREC consecutive ones in rows of 64 (coalesced);
+    //    every column is loaded first so that all loads are in flight together.
+    //    The record before the wave's first comes along (in every lane).
+    const u64 wrec0 = tile0 + (u64)w * WREC;
+    const u64 pr = wrec0 == 0 ? 0 : (wrec0 - 1 < n ? wrec0 - 1 : (u64)n - 1);
+    i64 vj[FL ? 1 : GI], vt[GI], vk[GI];
     uint8_t vfl[FL ? GI : 1];
     double vla[GI], vlo[GI];
     float vsp[GI];
@@ -121,7 +130,7 @@ k_grid_part(u32 n, const i64* __restrict__ jid, const i64* __restrict__ ts, cons
     uint8_t vbf[KD == 2 ? GI : 1];
 #pragma unroll
     for (int rr = 0; rr < GI; ++rr) {
-        u64 r = tile0 + (u64)(rr * GB + t);
+        u64 r = wrec0 + (u64)(rr * WAVE + lane);
         r = r < n ? r : (u64)n - 1;  // past the end: a record in range, not used
         if constexpr (FL) vfl[rr] = first[r];
         else vj[rr] = jid[r];
@@ -135,8 +144,14 @@ k_grid_part(u32 n, const i64* __restrict__ jid, const i64* __restrict__ ts, cons
             vbf[rr] = g.bfl[r];
         }
     }
+    i64 cj = 0;
+    if constexpr (!FL) cj = jid[pr];
+    i64 ctb = time_bin(g, ts[pr]);  // time bin, key, ... of the record before a row's first
+    i64 ck = -2;                    // (a wave's first record starts a run)
+    u64 codd = spd_odd(spd[pr]) ? 1ull : 0ull;
     // the tile's first shard, its start and the next shard's start (the same
-    // addresses in every lane); a record before the next start needs no search
+    // addresses in every lane); a tile that ends before the next start lies in
+    // one shard, else its records look their shards up
     u32 sh0 = 0;
     u64 s0start = ~0ull, nxt = ~0ull;
     if (g.S > 1) {
@@ -144,107 +159,99 @@ k_grid_part(u32 n, const i64* __restrict__ jid, const i64* __restrict__ ts, cons
         s0start = g.soff[sh0];
         nxt = sh0 + 1 < g.S ? g.soff[sh0 + 1] : ~0ull;
     }
-    u64 n_out = 0;
-    uint8_t bq[GI];
+    const bool many = tile0 + tvalid > nxt;
+    const u64 sbits = g.S > 1 ? (u64)sh0 << g.kb : 0ull;
+    u32 n_out = 0;  // wave-uniform
+    u64 hm[GI];     // run heads of each row
+    u32 segm = 0, oddm = 0;  // bit rr: the lane's record of row rr starts a segment / has an odd speed
 #pragma unroll
     for (int rr = 0; rr < GI; ++rr) {
-        const int q = rr * GB + t;
+        const int q = w * WREC + rr * WAVE + lane;
         const u64 r = tile0 + (u64)q;
         const bool in = (u32)q < tvalid;
-        i64 k = -1, tb = 0;
-        bool sstart = false;
-        if (in) {
-            u32 sh = sh0;
-            if (g.S > 1) {
-                if (r < nxt) {
-                    sstart = r == s0start;
-                } else {
-                    sh = shard_from(g.soff, g.S, sh0, r);
-                    sstart = g.soff[sh] == r;
-                }
-            }
-            u32 dir = 0;
-            if constexpr (KD == 1) dir = dir_sector(g, (double)vh[rr], true);
-            if constexpr (KD == 2) dir = dir_sector(g, vb[rr], (vbf[rr] & CV_FLAG_BEARING_OK) != 0);
-            k = grid_key_in(g, sh, vt[rr], vla[rr], vlo[rr], tb, dir);
-            if (k < 0) {
-                ++n_out;
-                if (g.sout) atomicAdd((unsigned long long*)&g.sout[sh], 1ull);
+        u32 dir = 0;
+        if constexpr (KD == 1) dir = dir_sector(g, (double)vh[rr], true);
+        if constexpr (KD == 2) dir = dir_sector(g, vb[rr], (vbf[rr] & CV_FLAG_BEARING_OK) != 0);
+        i64 k, tb;
+        u32 sh = sh0;
+        bool sstart = r == s0start;
+        bool quick = grid_key_quick(g, sbits, vt[rr], vla[rr], vlo[rr], dir, tb, k) && g.quick;
+        if (many) {
+            if (in && r >= nxt) {
+                sh = shard_from(g.soff, g.S, sh0, r);
+                sstart = g.soff[sh] == r;
+                quick = false;
             }
         }
-        vtb[rr] = tb;
+        if (__ballot(!quick) != 0) {
+            if (!quick) k = grid_key_in(g, sh, vt[rr], vla[rr], vlo[rr], tb, dir);
+        }
         vk[rr] = k;
-        const i64 tbp = __shfl_up(tb, 1, WAVE);
-        const i64 kp = __shfl_up(k, 1, WAVE);
-        if (lane == WAVE - 1) {
-            if constexpr (!FL) s_lj[rr][w] = vj[rr];
-            s_ltb[rr][w] = tb;
-            s_lk[rr][w] = k;
+        const u64 outm = __ballot(in && k < 0);
+        if (outm) {
+            n_out += (u32)__popcll(outm);
+            if (g.sout && in && k < 0) atomicAdd((unsigned long long*)&g.sout[sh], 1ull);
         }
-        // lane 0 compares with lane 63 of the wave row before, below
-        bool seg;
+        // segment starts: a journey's (or shard's) first record, a new time bin
+        // (moves between lanes stand outside conditions: a lane that is switched
+        // off hands nothing on)
+        const i64 tbb = lane_below(tb, ctb);
+        const i64 kb = lane_below(k, ck);
+        bool seg = tb != tbb;
         if constexpr (FL) {
             // FIRST marks every journey start, shard starts included
-            seg = (in && (vfl[rr] & CV_FLAG_FIRST)) || (lane > 0 && tb != tbp);
+            seg = seg || (vfl[rr] & CV_FLAG_FIRST);
         } else {
-            const i64 jp = __shfl_up(vj[rr], 1, WAVE);
-            seg = sstart || (lane > 0 && (vj[rr] != jp || tb != tbp));
+            const i64 jb = lane_below(vj[rr], cj);
+            seg = seg || sstart || vj[rr] != jb;
+            cj = lane_last(vj[rr]);
         }
-        const bool odd = in && spd_odd(vsp[rr]);
-        // the tile's first record and the first record of every wave's share
-        // of the aggregation start runs: no run is split between waves
-        const bool run = seg || q % WREC == 0 || (lane > 0 && k != kp);
-        bq[rr] = (seg ? B_SEG : 0) | (run ? B_RUN : 0) | (odd ? B_ODD : 0);
+        // run starts: also a new key, the wave's first record (no run is split
+        // between waves), and a run of its own around a speed outside the fast
+        // format
+        bool run = seg || k != kb || (rr == 0 && lane == 0);
+        const bool odd = spd_odd(vsp[rr]);
         const u64 om = __ballot(odd);
-        if (lane == 0) s_rodd[rr][w] = om != 0;
+        if (om | codd) run = run || odd || ((((om << 1) | codd) >> lane) & 1ull);
+        codd = om >> 63;
+        ctb = lane_last(tb);
+        ck = lane_last(k);
+        hm[rr] = __ballot(run && in);
+        s_bits[q] = (run ? B_RUN : 0);
+        segm |= seg ? 1u << rr : 0u;
+        oddm |= odd ? 1u << rr : 0u;
     }
-    __syncthreads();
-
-    // 2. segment and run starts of lane 0, runs of one record around speeds
-    //    outside the fast format, and the run heads of each wave row
-    u64 hm[GI];
+    {
+        // the rows' head counts, one lane each
+        u32 c = 0;
 #pragma unroll
-    for (int rr = 0; rr < GI; ++rr) {
-        const int q = rr * GB + t;
-        const bool in = (u32)q < tvalid;
-        uint8_t b = bq[rr];
-        const int pr = w > 0 ? rr : rr - 1;
-        const int pw = w > 0 ? w - 1 : NWG - 1;
-        if (lane == 0 && q > 0 && in && !(b & B_SEG)) {
-            if ((!FL && vj[FL ? 0 : rr] != s_lj[pr][pw]) || vtb[rr] != s_ltb[pr][pw]) b |= B_SEG | B_RUN;
-            else if (vk[rr] != s_lk[pr][pw]) b |= B_RUN;
-        }
-        const bool chk = s_rodd[rr][w] || (lane == 0 && q > 0 && s_rodd[pr][pw]);
-        if (chk && in && ((b & B_ODD) || (q > 0 && spd_odd(spd[tile0 + (u64)q - 1])))) b |= B_RUN;
-        bq[rr] = b;
-        s_bits[q] = b;
-        hm[rr] = __ballot((b & B_RUN) && in);
-        if (lane == 0) s_cnt[rr * NWG + w] = (u32)__popcll(hm[rr]);
+        for (int rr = 0; rr < GI; ++rr) c = lane == rr ? (u32)__popcll(hm[rr]) : c;
+        if (lane < GI) s_cnt[w * GI + lane] = c;
     }
     __syncthreads();
 
-    // 3. the run-head list in position order (per-row ballots placed by one
-    //    prefix over the (row, wave) counts), with each head's key
+    // 2. the run-head list in position order (per-row ballots placed by one
+    //    prefix over the (wave, row) counts), with each head's key
     int L;
     {
         const u32 c = lane < GI * NWG ? s_cnt[lane] : 0u;
         const u32 inc = wave_inclusive_sum(c);
-        L = (int)__shfl(inc, GI * NWG - 1, WAVE);
-        const u64 below = (1ull << lane) - 1ull;
+        L = __builtin_amdgcn_readlane((int)inc, GI * NWG - 1);
 #pragma unroll
         for (int rr = 0; rr < GI; ++rr) {
-            const int q = rr * GB + t;
-            const u32 off = __shfl(inc - c, rr * NWG + w, WAVE);
+            if (hm[rr] == 0) continue;
+            const int q = w * WREC + rr * WAVE + lane;
+            const u32 off = (u32)__builtin_amdgcn_readlane((int)(inc - c), w * GI + rr);
             if ((hm[rr] >> lane) & 1ull) {
-                const u32 e = off + (u32)__popcll(hm[rr] & below);
-                s_lpos[e] = (uint16_t)(q | ((bq[rr] & B_SEG) ? L_SEG : 0) | ((bq[rr] & B_ODD) ? L_ODD : 0));
+                const u32 e = off + popc_below(hm[rr]);
+                s_lpos[e] = (uint16_t)(q | (((segm >> rr) & 1u) ? L_SEG : 0) | (((oddm >> rr) & 1u) ? L_ODD : 0));
                 s_hkey[e] = vk[rr];
             }
         }
     }
     __syncthreads();
 
-    // 4. the root of every run head: the earliest head of its segment with the
+    // 3. the root of every run head: the earliest head of its segment with the
     //    same key (itself when there is none); a look back that stops at the
     //    window's end before the segment's start makes the head its own root.
     //    Several roots of one (journey, key) only cost extra partial rows.
@@ -292,7 +299,7 @@ k_grid_part(u32 n, const i64* __restrict__ jid, const i64* __restrict__ ts, cons
         if (i < nv && ((bits8 >> (8 * i)) & B_RUN)) ++hc;
     __syncthreads();
 
-    // 5. numbering, in list order: roots get accumulators (the first PR_MAX of
+    // 4. numbering, in list order: roots get accumulators (the first PR_MAX of
     //    them), rows follow position order (a root with an accumulator writes
     //    one; a run of its own writes one; beyond PR_MAX roots, every run of a
     //    root without an accumulator writes its own).  One packed scan gives
@@ -412,7 +419,7 @@ k_grid_part(u32 n, const i64* __restrict__ jid, const i64* __restrict__ ts, cons
     if ((u32)t < RA) rj0 = jid[tile0 + s_opos[t]];
     if ((u32)(t + GB) < RA) rj1 = jid[tile0 + s_opos[t + GB]];
 
-    // 6. every run reduced once (a lane folds its PER consecutive records into
+    // 5. every run reduced once (a lane folds its PER consecutive records into
     //    pieces cut at run starts; one segmented scan joins the pieces of runs
     //    that cross lanes) and added into its root's accumulator, or written
     //    as a row of its own
@@ -483,12 +490,7 @@ k_grid_part(u32 n, const i64* __restrict__ jid, const i64* __restrict__ ts, cons
         // holds no start), joined across lanes
         RunPart out = cur;
         run_seg_scan(out, hh);
-        RunPart inr;
-        inr.lo = (u64)__shfl_up((unsigned long long)out.lo, 1, WAVE);
-        inr.hi = (u64)__shfl_up((unsigned long long)out.hi, 1, WAVE);
-        inr.cn = (u32)__shfl_up(out.cn, 1, WAVE);
-        inr.mn = (u32)__shfl_up(out.mn, 1, WAVE);
-        inr.mx = (u32)__shfl_up(out.mx, 1, WAVE);
+        RunPart inr = run_below(out);
         if (lane == 0) run_reset(inr);
         if (hh && lane > 0) {
             // the run open below this lane ends here: its head is the last one before q0
@@ -501,17 +503,16 @@ k_grid_part(u32 n, const i64* __restrict__ jid, const i64* __restrict__ ts, cons
     // the largest key of the tile's rows
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) {
-        n_out += __shfl_xor(n_out, d, WAVE);
         const u64 o = __shfl_xor(kmax, d, WAVE);
         kmax = o > kmax ? o : kmax;
     }
     if (lane == 0) {
         s_red[w] = kmax;
-        s_tmp32[w] = (u32)n_out;
+        s_tmp32[w] = n_out;
     }
     __syncthreads();
 
-    // 7. the rows of the accumulators
+    // 6. the rows of the accumulators
     for (u32 o = t; o < RA; o += GB) {
         const u64 at = (u64)blockIdx.x * GT + s_orow[o];
         // the 128-bit sum from its two 43-bit carry-save chunks, mod 2^86 and

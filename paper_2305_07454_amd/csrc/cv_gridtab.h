@@ -85,6 +85,9 @@ struct Spec {
     double lat0, lon0, dlat, dlon;
     i64 n_lat, n_lon, t0, bin_ms, tmax;
     double tinv;      // 1 / bin_ms, rounded (the time bin's quotient estimate)
+    double rlat, rlon;  // 1 / dlat, 1 / dlon, rounded (the cells' quotient estimates)
+    u64 cells;        // n_lat * n_lon
+    u32 quick;        // grid_key_quick may be used: bin_ms < 2^30, cells < 2^32, cell sizes that invert exactly enough
     const u64* soff;  // shard offsets (batched form) or nullptr
     u32 S;            // number of shards (0 or 1: one problem)
     u32 kb;           // bits of the cell key; the shard index sits above them
@@ -176,6 +179,40 @@ __device__ __forceinline__ i64 grid_key_in(const Spec& g, u32 sh, i64 ts, double
     i64 k = (td * g.n_lat + (i64)fy) * g.n_lon + (i64)fx;
     if (g.S > 1) k |= (i64)((u64)sh << g.kb);
     return k;
+}
+
+// floor of the IEEE quotient a / d by a multiply with r = fl(1 / d): the product
+// y and the quotient both lie within 2^-51 |y| of the true one, so their floors
+// agree unless a whole number lies that near y; false there, for a y next to
+// underflow and for an infinite or NaN a, where the division decides.
+__device__ __forceinline__ bool floor_quick(double a, double r, double& f)
+{
+    const double y = a * r;
+    f = floor(y);
+    return fabs(y - rint(y)) > fabs(y) * 0x1p-50 + 1e-290;
+}
+
+// grid_key_in where every part is short (g.quick; an offset below 2^30 ms and
+// no coordinate within a rounding of a cell's edge); false otherwise, with tb
+// and k unset.  A third of the instructions of the general form.
+__device__ __forceinline__ bool grid_key_quick(const Spec& g, u64 shard_bits, i64 ts, double la, double lo, u32 dir,
+                                               i64& tb, i64& k)
+{
+    const i64 a = ts - g.t0;
+    const u32 a32 = (u32)a, b32 = (u32)g.bin_ms;
+    int q = (int)floor((double)(int)a32 * g.tinv);
+    const int r = (int)(a32 - (u32)q * b32);
+    q += r < 0 ? -1 : (r >= (int)b32 ? 1 : 0);
+    double fy, fx;
+    bool ok = (u64)(a + (1ll << 30)) < (1ull << 31);
+    ok = floor_quick(la - g.lat0, g.rlat, fy) && ok;
+    ok = floor_quick(lo - g.lon0, g.rlon, fx) && ok;
+    const bool in = fy >= 0.0 && fy < (double)g.n_lat && fx >= 0.0 && fx < (double)g.n_lon && q >= 0 && q < g.tmax;
+    const u32 cell = (u32)fy * (u32)g.n_lon + (u32)fx;
+    const u64 base = g.nd ? ((u64)(u32)q * (g.nd + 1) + dir) * (u32)g.cells : (u64)(u32)q * (u32)g.cells;
+    tb = q;
+    k = in ? (i64)((base + cell) | shard_bits) : -1;
+    return ok;
 }
 
 // the same for record r (its shard found by binary search)
