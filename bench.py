@@ -442,10 +442,15 @@ def bench_plain(args, workload):
     assert npts == n, (npts, n)
     assert cnt + rg["n_out_of_grid"] == n, (cnt, rg["n_out_of_grid"], n)
 
-    # dominant kernel: the radix scatter passes that run (digit below the key width)
+    # dominant kernel: the radix scatter passes that run (digit below the key
+    # width), or, for input of whole journeys in near order, which needs none,
+    # the gather with the kinematics
     key_bits = rs["key_bits"]
     p0 = rs["packed_pass"]
     roof, pass_ms = radix_roofline(cvetl, n, rs)
+    sorts = roof is not None
+    if not sorts:
+        roof = gather_roofline(cvetl, n)
     stages = {}
     for fam in ("sort_prep", "gather", "features", "gather_features", "summary", "grid_agg", "grid_tail"):
         ms, c = cvetl.cv_timing_read(fam)
@@ -462,7 +467,7 @@ def bench_plain(args, workload):
 
     traffic = None
     tfile = os.path.join(ROOT, "profiles", "radix_pass_c1_traffic.md")
-    if workload == "c1" and args.n_journeys is None and os.path.exists(tfile):
+    if sorts and workload == "c1" and args.n_journeys is None and os.path.exists(tfile):
         t = read_traffic(tfile)
         if t.get("kernel_source_sha") == _kernel_sha() and t.get("sort_shape") == str(cvetl.cv_tuning_get("sort_shape")):
             traffic = float(t["traffic_bytes_per_launch"])
@@ -497,7 +502,7 @@ def bench_plain(args, workload):
         "path_roofline": path_roofline(stages, n, G, key_bits, p0, ms_step,
                                        design_bytes=282 if workload == "c1" else None,
                                        digit_bits=int(cvetl.cv_tuning_get("radix_bits")),
-                                       first_bits=first_digit_bits(rs)),
+                                       first_bits=first_digit_bits(rs), sorts=sorts),
         "direction_lattice": direction,
         "dense_lattice": lattice,
         "key_bits": key_bits,
@@ -702,7 +707,8 @@ def bench_csv(r, dev, rows=4_000_000):
 def radix_roofline(cvetl, n, rs, traffic=None):
     """Roofline of the record sort's radix scatter passes from the per-pass
     HIP-event timing families (working passes only: digits below the key
-    width)."""
+    width), and their time; None and the idle launches' time where the passes
+    had nothing to sort (they end before the card could move a pass's bytes)."""
     key_bits = rs["key_bits"]
     db = int(cvetl.cv_tuning_get("radix_bits"))
     w0 = first_digit_bits(rs)
@@ -719,6 +725,8 @@ def radix_roofline(cvetl, n, rs, traffic=None):
     avg_ms = pass_ms / max(launches, 1)
     per_launch = alg / max(launches, 1)
     achieved = per_launch / (avg_ms / 1e3) / 1e9 if avg_ms > 0 else 0.0
+    if achieved > HBM_PEAK_GBS:
+        return None, pass_ms
     kind = f"stable {db}-bit LSD scatter pass" if w0 == db else f"stable LSD scatter pass: a {w0}-bit first digit, then {db}-bit digits"
     return {"bound": "hbm", "kernel": f"k_radix_pass ({kind})",
             "tile_keys": cvetl.cv_tuning_get("sort_tile"),
@@ -726,6 +734,20 @@ def radix_roofline(cvetl, n, rs, traffic=None):
             "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic,
             "avg_launch_ms": round(avg_ms, 5), "launches": launches,
             "alg_bytes_per_launch": int(per_launch), "per_pass_ms": per_pass}, pass_ms
+
+
+def gather_roofline(cvetl, n):
+    """Roofline of the gather fused with the kinematics: the sorted word, the
+    position and speed columns read; the order, the sorted columns and the
+    features written."""
+    ms, c = cvetl.cv_timing_read("gather_features")
+    avg_ms = ms / max(c, 1)
+    alg = n * (8 + 20 + 4 + 36 + 49)
+    achieved = alg / (avg_ms / 1e3) / 1e9 if avg_ms > 0 else 0.0
+    return {"bound": "hbm", "kernel": "k_gather_feat (gather in sorted order with the kinematics)",
+            "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
+            "frac": round(achieved / HBM_PEAK_GBS, 4), "avg_launch_ms": round(avg_ms, 5), "launches": c,
+            "alg_bytes_per_launch": int(alg)}
 
 
 def first_digit_bits(rs):
@@ -745,15 +767,16 @@ def sort_pass_count(key_bits, first_bits=8, digit_bits=8):
 
 
 def path_roofline(stages, n, G, key_bits, p0, ms_step, design_bytes=None, digit_bits=8, interleaved=False,
-                  ts_in_key=True, first_bits=8):
+                  ts_in_key=True, first_bits=8, sorts=True):
     """Algorithmic bytes of the whole path per step (the per-record figures of
     each stage's kernels, plus the group tail) over the measured step time.
     design_bytes: the fixed per-record byte budget of the path's design (the
     same for any implementation of it), reported beside as a second fraction.
     interleaved: input with short runs of equal ids, for which the key packing
     also writes a 32-byte payload per record that the fused gather reads
-    instead of the columns.  ts_in_key: the sort key holds the time offset."""
-    passes = sort_pass_count(key_bits, first_bits, digit_bits)
+    instead of the columns.  ts_in_key: the sort key holds the time offset.
+    sorts: radix passes sort the keys (not for whole journeys in near order)."""
+    passes = sort_pass_count(key_bits, first_bits, digit_bits) if sorts else 0
     # the time offset survives in the final word only when nothing was dropped
     ts_read = 0 if (p0 == 0 and ts_in_key) else 8
     per = {"sort_prep": 16 + 24 + ((20 + 32) if interleaved and "gather_features" in stages else 0),

@@ -132,6 +132,43 @@ __device__ __forceinline__ void ds_count(const u64* __restrict__ list, const u64
     done(r, key);
 }
 
+// The same for (id, run) pairs without shards, with the records of the smaller
+// ids' runs (high half: start, low half: end) added up: done(r, id, before, run).
+template <class Done>
+__device__ __forceinline__ void ds_count_runs(const u64* __restrict__ list, const u64* __restrict__ runs, u32 n,
+                                              Done done)
+{
+    constexpr int NWD = DS_B / WAVE;
+    __shared__ u32 s_n[NWD][WAVE], s_r[NWD][WAVE];
+    const u32 i0 = blockIdx.x * WAVE;
+    if (i0 >= n) return;
+    const int l = lane_id();
+    const u32 w = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
+    const u32 i = i0 + l < n ? i0 + l : n - 1;
+    const u64 key = list[i];
+    const u32 per = (n + NWD - 1) / NWD;
+    const u32 a = w * per, b = a + per < n ? a + per : n;
+    u32 c = 0, rec = 0;
+#pragma unroll 8
+    for (u32 j = a; j < b; ++j) {
+        const u64 run = runs[j];
+        const bool less = list[j] < key;
+        c += less ? 1u : 0u;
+        rec += less ? (u32)run - (u32)(run >> 32) : 0u;
+    }
+    s_n[w][l] = c;
+    s_r[w][l] = rec;
+    __syncthreads();
+    if (w != 0 || i0 + l >= n) return;
+    u32 r = 0, before = 0;
+#pragma unroll
+    for (int k = 0; k < NWD; ++k) {
+        r += s_n[k][l];
+        before += s_r[k][l];
+    }
+    done(r, key, before, runs[i]);
+}
+
 // One step of the join: runs of `run` sorted ids, DS_FAN of them to a group.
 // Id i goes to its group's start plus its place in its own run plus the count
 // of smaller ids in each other run of the group (ids are distinct).  The
