@@ -722,6 +722,8 @@ def radix_roofline(cvetl, n, rs, traffic=None):
         launches += c
         alg += n * pass_bytes(p, p0) * c
         per_pass.append(round(ms / max(c, 1), 4))
+    if passes > 1 and cvetl.cv_timing_read("sort_pass1")[1] == 0:
+        alg = launches * n * sum(pass_bytes(p, p0) for p in range(passes))  # few keys: all passes in one launch
     avg_ms = pass_ms / max(launches, 1)
     per_launch = alg / max(launches, 1)
     achieved = per_launch / (avg_ms / 1e3) / 1e9 if avg_ms > 0 else 0.0

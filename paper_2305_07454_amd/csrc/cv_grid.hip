@@ -93,8 +93,7 @@ struct GridLayout {
         // last in the cleared range: a call clears what its tile shape uses
         status = c.take<u64>(stiles * RADIX + 1);
         zero_begin = (u32*)(c.base ? c.base + z0 : nullptr);
-        const u64 tile = (u64)sort_tile(sort_shape());
-        const size_t used = c.base ? (size_t)((char*)(status + ((pmax + tile - 1) / tile) * RADIX) - c.base) : 0;
+        const size_t used = c.base ? (size_t)((char*)(status + sort_status_words(pmax, true, false)) - c.base) : 0;
         zero_bytes = c.base ? cvh::align_up(used) - z0 : 0;
         bytes = c.size();
     }

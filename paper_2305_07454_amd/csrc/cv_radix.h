@@ -42,6 +42,9 @@ bool set_sort_shape(int i);
 int sort_tile(int i);
 int sort_block(int i);
 int sort_min_tile();
+// status words that a sort of at most n_max keys uses (counted: their number is
+// known on the device alone; wide: the first digit may have 9 bits)
+u64 sort_status_words(u64 n_max, bool counted, bool wide);
 // whether the selected shape has a 9-bit first-digit pass (512 threads or
 // more) and the tuning allows it
 bool sort_wide_first();
@@ -55,7 +58,9 @@ bool sort_wide_first();
 //                the data sits in (k1, v1) when p is odd, in (k0, v0) when even.
 void radix_hist(const u64* keys, u32 n_max, const u32* n_dev, int passes, const u32* bits_dev, u32* hist,
                 int grid, hipStream_t s);
-//                When `timed`, pass p is bracketed as timing family "sort_pass<p>".
+//                Few keys take all passes in one launch (k_radix_all).
+//                When `timed`, pass p is bracketed as timing family "sort_pass<p>"
+//                (a launch of all passes as "sort_pass0").
 //                pack [device, 3] (nullable): {ib, p0, w0}: from pass p0 on,
 //                key words hold (key >> 8 p0) << ib | index and no value
 //                arrays are used (p0 = 0: the input keys are packed

@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 
 #include <string>
+#include <type_traits>
 
 #include "cv_host.h"
 #include "cv_radix.h"
@@ -55,86 +56,77 @@ __global__ void __launch_bounds__(256) k_radix_hist(const u64* __restrict__ keys
         if (s_h[i]) atomicAdd(&hist[i], s_h[i]);
 }
 
-// One stable scatter pass on digit `pass`: bits [8*pass, 8*pass+8), or, with
-// a first digit of w0 = pack[2] bits (9): [0, w0) for pass 0 and
-// [w0 + 8 (pass - 1), w0 + 8 pass) after it.  DB: bits of the digit this
-// instantiation handles (8, or 9 for a wide first digit; a launch whose
-// width is not the pass's leaves at once).
-// vals_in == nullptr means the identity (input index).  LOOP: a block goes on
-// taking tiles (a grid smaller than the tile count); otherwise it takes one.
-template <int SORT_BLOCK, int SORT_ITEMS, bool LOOP, int DB = RADIX_BITS>
-__global__ void __launch_bounds__(SORT_BLOCK)
-k_radix_pass(const u64* __restrict__ keys_in, const u32* __restrict__ vals_in, u64* __restrict__ keys_out,
-             u32* __restrict__ vals_out, u32 n_max, const u32* __restrict__ n_dev, int pass,
-             const u32* __restrict__ bits_dev, const u32* __restrict__ hist, u64* __restrict__ status,
-             u32* __restrict__ ticket, const u32* __restrict__ pack)
+// LDS of a pass over tiles of B x I keys with digits of DB bits at most.
+template <int B, int I, int DB>
+struct RadixLds {
+    // staging: keys in digit order; then, in passes that carry index values,
+    // the values in the same order (the buffer reused as 32-bit words)
+    u64 keys[B * I];
+    u64 tmp[B / WAVE];
+    u32 start[1 << DB], gshift[1 << DB];
+    uint16_t whist[(B / WAVE) << DB];  // per-wave digit counts, then in-tile offsets (< tile, so 16 bits)
+};
+
+// What a pass needs besides its tile.
+struct RadixPass {
+    const u64* keys_in;
+    const u32* vals_in;  // nullptr: the identity (input index)
+    u64* keys_out;
+    u32* vals_out;
+    u64* status;
+    u32 n, tag, ib;
+    u32 dcnt;   // the pass's global count of digit threadIdx.x
+    int shift;  // the digit's lowest bit in the input words
+    int drop;   // key bits dropped by the pass that starts packing
+    bool pin, pout;  // input / output words are packed
+    bool tin, tout;  // words loaded / stored past the L2
+};
+
+// Key and value words of a pass.  THROUGH: the pass before (loads) or after it
+// (stores) runs in the same launch, on any XCD: the words go past the XCD's L2.
+template <bool THROUGH, class T>
+__device__ __forceinline__ T word_load(const T* p)
+{
+    return THROUGH ? __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : *p;
+}
+template <bool THROUGH, class T>
+__device__ __forceinline__ void word_store(T* p, T v)
+{
+    if (THROUGH) __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    else *p = v;
+}
+
+// One tile of a stable scatter pass on a digit of DB bits.  whist is clear and
+// every thread of the block has seen it so.
+template <int SORT_BLOCK, int SORT_ITEMS, int DB, class Lds>
+__device__ __forceinline__ void radix_tile(Lds& s, const RadixPass& a, u32 tile)
 {
     constexpr int NW = SORT_BLOCK / WAVE;
     constexpr int SORT_TILE = SORT_BLOCK * SORT_ITEMS;
     constexpr int RK = 1 << DB;  // digit values
     static_assert(SORT_BLOCK >= RK, "one thread per digit");
     static_assert(SORT_TILE <= 65535, "16-bit in-tile offsets");
-    // per-wave digit counts, then in-tile offsets (< SORT_TILE, so 16 bits)
-    __shared__ uint16_t s_whist[NW][RK];
-    __shared__ u32 s_start[RK];
-    __shared__ u32 s_gshift[RK];
-    // staging: keys in digit order; then, in passes that carry index values,
-    // the values in the same order (the buffer reused as 32-bit words)
-    __shared__ u64 s_keys[SORT_TILE];
-    __shared__ u64 s_tmp[NW];
-    __shared__ u32 s_tile;
-
-    // the launch's scalars from device memory, all loaded before any is used.
-    // packing: from pass p0 on, a key word holds (key >> 8 p0) << ib | index
-    // (a wide first digit only with p0 = 0)
-    u32 ib = 0, w0r = RADIX_BITS;
-    int p0 = 1 << 20;
-    if (pack) {
-        ib = pack[0];
-        p0 = (int)pack[1];
-        w0r = pack[2];
-    }
-    const u32 bits = bits_dev ? *bits_dev : ~0u;
-    const u32 n = n_dev ? *n_dev : n_max;
-    const int w0 = w0r == RADIX_BITS + 1 ? RADIX_BITS + 1 : RADIX_BITS;
-    if ((pass == 0 ? w0 : RADIX_BITS) != DB) return;  // the other width's launch takes this pass
-    const int lo = pass == 0 ? 0 : w0 + (pass - 1) * RADIX_BITS;  // the digit's lowest key bit
-    if ((u32)lo >= bits) return;
-    const bool pin = pass >= p0;           // input words are packed
-    const bool pout = pass + 1 >= p0;      // output words are packed
-    const int shift = pin ? (int)ib + lo - p0 * RADIX_BITS : lo;
-    // this pass's global count of digit threadIdx.x, read before it is needed
-    const u32 dcnt = threadIdx.x < RK ? hist[threadIdx.x] : 0u;
-    // Tiles are taken by ticket (with LOOP, until the tickets pass the last
-    // tile, so a grid smaller than the tile count covers every tile); a tile
-    // waits only on tiles whose tickets were taken before, by blocks already
-    // running.
-    // A block of a one-tile-per-block grid sized for n_max whose tile lies past
-    // a count read on the device leaves before it takes a ticket: exactly the
-    // first ceil(n / tile) blocks take the tickets 0 .. ceil(n / tile) - 1,
-    // and the idle ones put no load on the ticket counter.
-    if (!LOOP && (u64)blockIdx.x * SORT_TILE >= n) return;
-    for (;;) {
-    if (threadIdx.x == 0) s_tile = atomicAdd(ticket, 1u);
-    for (int i = threadIdx.x; i < NW * RK; i += SORT_BLOCK) (&s_whist[0][0])[i] = 0;
-    __syncthreads();
-    const u32 tile = s_tile;
+    const u64 n = a.n;
     const u64 tile_base = (u64)tile * SORT_TILE;
-    if (tile_base >= n) return;
-
+    const int shift = a.shift;
     const int w = threadIdx.x / WAVE;
     const int l = lane_id();
+    uint16_t* whist = s.whist + w * RK;
     u64 key[SORT_ITEMS];
     u32 val[SORT_ITEMS];
     u32 rnk[SORT_ITEMS];
     const u64 wbase = tile_base + (u64)w * (SORT_ITEMS * WAVE);
+    auto load = [&](auto through) {
 #pragma unroll
-    for (int i = 0; i < SORT_ITEMS; ++i) {
-        u64 idx = wbase + (u64)i * WAVE + l;
-        bool ok = idx < n;
-        key[i] = ok ? keys_in[idx] : ~0ull;
-        val[i] = (ok && !pin) ? (vals_in ? vals_in[idx] : (u32)idx) : 0u;
-    }
+        for (int i = 0; i < SORT_ITEMS; ++i) {
+            u64 idx = wbase + (u64)i * WAVE + l;
+            bool ok = idx < n;
+            key[i] = ok ? word_load<through()>(a.keys_in + idx) : ~0ull;
+            val[i] = (ok && !a.pin) ? (a.vals_in ? word_load<through()>(a.vals_in + idx) : (u32)idx) : 0u;
+        }
+    };
+    if (a.tin) load(std::true_type());
+    else load(std::false_type());
 #pragma unroll
     for (int i = 0; i < SORT_ITEMS; ++i) {
         u64 idx = wbase + (u64)i * WAVE + l;
@@ -143,10 +135,10 @@ k_radix_pass(const u64* __restrict__ keys_in, const u32* __restrict__ vals_in, u
         const u64 peers = wave_peers<DB>(d, __ballot(ok));
         u32 below = popc_below(peers);
         u32 cnt = __popcll(peers);
-        u32 before = ok ? (u32)s_whist[w][d] : 0u;
+        u32 before = ok ? (u32)whist[d] : 0u;
         rnk[i] = before + below;
         __builtin_amdgcn_wave_barrier();
-        if (ok && below == cnt - 1) s_whist[w][d] = (uint16_t)(before + cnt);
+        if (ok && below == cnt - 1) whist[d] = (uint16_t)(before + cnt);
         __builtin_amdgcn_wave_barrier();
     }
     __syncthreads();
@@ -157,21 +149,21 @@ k_radix_pass(const u64* __restrict__ keys_in, const u32* __restrict__ vals_in, u
         const int d = threadIdx.x;
 #pragma unroll
         for (int ww = 0; ww < NW; ++ww) {
-            u32 c = s_whist[ww][d];
-            s_whist[ww][d] = (uint16_t)tcount;
+            u32 c = s.whist[ww * RK + d];
+            s.whist[ww * RK + d] = (uint16_t)tcount;
             tcount += c;
         }
     }
     // one scan for the tile's digit starts and (high word) the pass's global
     // ones: a scan kernel between the histogram and the passes cost a launch
     u64 total;
-    const u64 ex = block_exclusive_sum<SORT_BLOCK>(((u64)dcnt << 32) | (threadIdx.x < RK ? tcount : 0u), s_tmp, total);
+    const u64 ex =
+        block_exclusive_sum<SORT_BLOCK>(((u64)a.dcnt << 32) | (threadIdx.x < RK ? tcount : 0u), s.tmp, total);
     const u32 start = (u32)ex, doff = (u32)(ex >> 32);
-    const u32 tag = (u32)pass + 1;
     if (threadIdx.x < RK) {
-        s_start[threadIdx.x] = start;
+        s.start[threadIdx.x] = start;
         // this tile's digit count, for the look-back of later tiles
-        lb_publish(status + (u64)tile * RK + threadIdx.x, rs_word(tile == 0 ? 2 : 1, tag, tcount));
+        lb_publish(a.status + (u64)tile * RK + threadIdx.x, rs_word(tile == 0 ? 2 : 1, a.tag, tcount));
     }
     __syncthreads();
 
@@ -184,8 +176,8 @@ k_radix_pass(const u64* __restrict__ keys_in, const u32* __restrict__ vals_in, u
         pos[i] = ~0u;
         if (idx < n) {
             u32 d = (u32)(key[i] >> shift) & (RK - 1);
-            pos[i] = s_start[d] + s_whist[w][d] + rnk[i];
-            s_keys[pos[i]] = key[i];
+            pos[i] = s.start[d] + whist[d] + rnk[i];
+            s.keys[pos[i]] = key[i];
         }
     }
     if (threadIdx.x < RK) {
@@ -203,13 +195,13 @@ k_radix_pass(const u64* __restrict__ keys_in, const u32* __restrict__ vals_in, u
                 u64 wv[LBW];
 #pragma unroll
                 for (int j = 0; j < LBW; ++j)
-                    wv[j] = t - j >= 0 ? lb_peek(status + (u64)(t - j) * RK + d) : 0ull;
+                    wv[j] = t - j >= 0 ? lb_peek(a.status + (u64)(t - j) * RK + d) : 0ull;
                 int used = 0;
 #pragma unroll
                 for (int j = 0; j < LBW; ++j) {
                     if (done || used < j) break;  // stopped earlier in this batch
                     const u32 hdr = (u32)(wv[j] >> 56);
-                    if (t - j < 0 || (hdr & 63u) != tag) break;
+                    if (t - j < 0 || (hdr & 63u) != a.tag) break;
                     excl += wv[j] & ((1ull << 56) - 1);
                     used = j + 1;
                     if ((hdr >> 6) == 2u) done = true;
@@ -217,9 +209,9 @@ k_radix_pass(const u64* __restrict__ keys_in, const u32* __restrict__ vals_in, u
                 t -= used;
                 if (!done && used < LBW) __builtin_amdgcn_s_sleep(1);
             }
-            lb_publish(status + (u64)tile * RK + d, rs_word(2, tag, excl + tcount));
+            lb_publish(a.status + (u64)tile * RK + d, rs_word(2, a.tag, excl + tcount));
         }
-        s_gshift[d] = doff + (u32)excl - start;
+        s.gshift[d] = doff + (u32)excl - start;
     }
     __syncthreads();
     const u32 tvalid = (u32)((n - tile_base) < (u64)SORT_TILE ? (n - tile_base) : (u64)SORT_TILE);
@@ -228,46 +220,183 @@ k_radix_pass(const u64* __restrict__ keys_in, const u32* __restrict__ vals_in, u
 #pragma unroll
     for (int k = 0; k < SORT_ITEMS; ++k) {
         const u32 j = threadIdx.x + (u32)k * SORT_BLOCK;
-        kk[k] = j < tvalid ? s_keys[j] : 0ull;
+        kk[k] = j < tvalid ? s.keys[j] : 0ull;
     }
-    if (pin) {
+    auto store = [&](auto through) {
+        constexpr bool TH = through();
+        if (a.pin) {
+#pragma unroll
+            for (int k = 0; k < SORT_ITEMS; ++k) {
+                const u32 j = threadIdx.x + (u32)k * SORT_BLOCK;
+                if (j < tvalid) word_store<TH>(a.keys_out + s.gshift[(u32)(kk[k] >> shift) & (RK - 1)] + j, kk[k]);
+            }
+            return;
+        }
+        // the index values follow the keys through the same staging buffer
+        __syncthreads();
+        u32* s_vals = (u32*)s.keys;
+#pragma unroll
+        for (int i = 0; i < SORT_ITEMS; ++i)
+            if (pos[i] != ~0u) s_vals[pos[i]] = val[i];
+        __syncthreads();
+        // the pass that starts packing packs on the way out
 #pragma unroll
         for (int k = 0; k < SORT_ITEMS; ++k) {
             const u32 j = threadIdx.x + (u32)k * SORT_BLOCK;
-            if (j < tvalid) keys_out[s_gshift[(u32)(kk[k] >> shift) & (RK - 1)] + j] = kk[k];
-        }
-        if constexpr (!LOOP) return;
-        __syncthreads();  // LDS free for the next tile
-        continue;
-    }
-    // the index values follow the keys through the same staging buffer
-    __syncthreads();
-    u32* s_vals = (u32*)s_keys;
-#pragma unroll
-    for (int i = 0; i < SORT_ITEMS; ++i)
-        if (pos[i] != ~0u) s_vals[pos[i]] = val[i];
-    __syncthreads();
-    // the pass that starts packing packs on the way out
-    const int drop = p0 * RADIX_BITS;
-#pragma unroll
-    for (int k = 0; k < SORT_ITEMS; ++k) {
-        const u32 j = threadIdx.x + (u32)k * SORT_BLOCK;
-        if (j < tvalid) {
-            const u32 g = s_gshift[(u32)(kk[k] >> shift) & (RK - 1)] + j;
-            const u32 v = s_vals[j];
-            if (pout) {
-                keys_out[g] = ((drop >= 64 ? 0ull : (kk[k] >> drop)) << ib) | (u64)v;
-            } else {
-                keys_out[g] = kk[k];
-                vals_out[g] = v;
+            if (j < tvalid) {
+                const u32 g = s.gshift[(u32)(kk[k] >> shift) & (RK - 1)] + j;
+                const u32 v = s_vals[j];
+                if (a.pout) {
+                    const u64 top = a.drop >= 64 ? 0ull : (kk[k] >> a.drop);
+                    word_store<TH, u64>(a.keys_out + g, (top << a.ib) | (u64)v);
+                } else {
+                    word_store<TH, u64>(a.keys_out + g, kk[k]);
+                    word_store<TH, u32>(a.vals_out + g, v);
+                }
             }
         }
+    };
+    if (a.tout) store(std::true_type());
+    else store(std::false_type());
+}
+
+// Packing and first digit of a sort, read from device memory.  From pass p0 on, a
+// key word holds (key >> 8 p0) << ib | index (a wide first digit only with p0 = 0).
+struct RadixForm {
+    u32 ib, w0;
+    int p0;
+    __device__ __forceinline__ explicit RadixForm(const u32* pack) : ib(0), w0(RADIX_BITS), p0(1 << 20)
+    {
+        if (!pack) return;
+        ib = pack[0];
+        p0 = (int)pack[1];
+        w0 = pack[2] == RADIX_BITS + 1 ? RADIX_BITS + 1 : RADIX_BITS;
     }
-    if constexpr (!LOOP) return;
-    __syncthreads();  // LDS free for the next tile
+    // the lowest key bit of a pass's digit
+    __device__ __forceinline__ int low(int pass) const { return pass == 0 ? 0 : (int)w0 + (pass - 1) * RADIX_BITS; }
+    __device__ __forceinline__ void set(RadixPass& a, int pass) const
+    {
+        a.tag = (u32)pass + 1;
+        a.ib = ib;
+        a.pin = pass >= p0;
+        a.pout = pass + 1 >= p0;
+        a.drop = p0 * RADIX_BITS;
+        a.shift = a.pin ? (int)ib + low(pass) - a.drop : low(pass);
+    }
+};
+
+// One stable scatter pass on digit `pass`: bits [8*pass, 8*pass+8), or, with
+// a first digit of w0 = pack[2] bits (9): [0, w0) for pass 0 and
+// [w0 + 8 (pass - 1), w0 + 8 pass) after it.  DB: bits of the digit this
+// instantiation handles (8, or 9 for a wide first digit; a launch whose
+// width is not the pass's leaves at once).
+// vals_in == nullptr means the identity (input index).  LOOP: a block goes on
+// taking tiles (a grid smaller than the tile count); otherwise it takes one.
+template <int SORT_BLOCK, int SORT_ITEMS, bool LOOP, int DB = RADIX_BITS>
+__global__ void __launch_bounds__(SORT_BLOCK)
+k_radix_pass(const u64* __restrict__ keys_in, const u32* __restrict__ vals_in, u64* __restrict__ keys_out,
+             u32* __restrict__ vals_out, u32 n_max, const u32* __restrict__ n_dev, int pass,
+             const u32* __restrict__ bits_dev, const u32* __restrict__ hist, u64* __restrict__ status,
+             u32* __restrict__ ticket, const u32* __restrict__ pack)
+{
+    constexpr int SORT_TILE = SORT_BLOCK * SORT_ITEMS;
+    __shared__ RadixLds<SORT_BLOCK, SORT_ITEMS, DB> s;
+    __shared__ u32 s_tile;
+
+    // the launch's scalars from device memory, all loaded before any is used
+    const RadixForm form(pack);
+    const u32 bits = bits_dev ? *bits_dev : ~0u;
+    const u32 n = n_dev ? *n_dev : n_max;
+    if ((pass == 0 ? (int)form.w0 : RADIX_BITS) != DB) return;  // the other width's launch takes this pass
+    if ((u32)form.low(pass) >= bits) return;
+    RadixPass a{keys_in, vals_in, keys_out, vals_out, status, n};
+    form.set(a, pass);
+    a.tin = a.tout = false;
+    a.dcnt = threadIdx.x < (1 << DB) ? hist[threadIdx.x] : 0u;
+    // Tiles are taken by ticket (with LOOP, until the tickets pass the last
+    // tile, so a grid smaller than the tile count covers every tile); a tile
+    // waits only on tiles whose tickets were taken before, by blocks already
+    // running.
+    // A block of a one-tile-per-block grid sized for n_max whose tile lies past
+    // a count read on the device leaves before it takes a ticket: exactly the
+    // first ceil(n / tile) blocks take the tickets 0 .. ceil(n / tile) - 1,
+    // and the idle ones put no load on the ticket counter.
+    if (!LOOP && (u64)blockIdx.x * SORT_TILE >= n) return;
+    for (;;) {
+        if (threadIdx.x == 0) s_tile = atomicAdd(ticket, 1u);
+        for (int i = threadIdx.x; i < (SORT_BLOCK / WAVE) << DB; i += SORT_BLOCK) s.whist[i] = 0;
+        __syncthreads();
+        const u32 tile = s_tile;
+        if ((u64)tile * SORT_TILE >= n) return;
+        radix_tile<SORT_BLOCK, SORT_ITEMS, DB>(s, a, tile);
+        if constexpr (!LOOP) return;
+        __syncthreads();  // LDS free for the next tile
     }
 }
 
+// Every pass of a small sort in one launch: its passes are a few tiles each,
+// and those of digits that the keys turn out not to have are launches that do
+// nothing, each as long on the stream as a working one's start (4.5 us), and as
+// long to enqueue for a host that is the slower of the two.
+// Tickets run through the tiles of pass after pass.  A tile of a later pass
+// waits until the pass before it has counted all its tiles as done (tickets[1 +
+// pass]), that is, on earlier tickets only, whose blocks run: no block waits
+// for one that has not started.
+template <int SORT_BLOCK, int SORT_ITEMS>
+__global__ void __launch_bounds__(SORT_BLOCK)
+k_radix_all(u64* k0, u64* k1, const u32* v_first, u32* v0, u32* v1, u32 n_max, const u32* __restrict__ n_dev,
+            int max_passes, const u32* __restrict__ bits_dev, const u32* __restrict__ hist, u32 wide, u64* status,
+            u32* tickets, const u32* __restrict__ pack)
+{
+    constexpr u32 SORT_TILE = SORT_BLOCK * SORT_ITEMS;
+    __shared__ RadixLds<SORT_BLOCK, SORT_ITEMS, RADIX_BITS + 1> s;
+    __shared__ u32 s_tile;
+    const RadixForm form(pack);
+    const u32 bits = bits_dev ? *bits_dev : ~0u;
+    const u32 n = n_dev ? *n_dev : n_max;
+    int np = 0;
+    while (np < max_passes && (u32)form.low(np) < bits) ++np;
+    const u32 tiles = (u32)(((u64)n + SORT_TILE - 1) / SORT_TILE);
+    if (np == 0 || blockIdx.x >= tiles) return;
+    for (;;) {
+        if (threadIdx.x == 0) s_tile = atomicAdd(&tickets[0], 1u);
+        for (int i = threadIdx.x; i < (SORT_BLOCK / WAVE) << (RADIX_BITS + 1); i += SORT_BLOCK) s.whist[i] = 0;
+        __syncthreads();
+        u32 tile = s_tile;
+        int pass = 0;
+        for (; pass < np && tile >= tiles; ++pass) tile -= tiles;
+        if (pass == np) return;
+        if (pass > 0) {
+            if (threadIdx.x == 0) {
+                while (__hip_atomic_load(&tickets[pass], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < tiles)
+                    __builtin_amdgcn_s_sleep(4);
+            }
+            __syncthreads();
+        }
+        RadixPass a{(pass & 1) ? k1 : k0, pass == 0 ? v_first : ((pass & 1) ? v1 : v0), (pass & 1) ? k0 : k1,
+                    (pass & 1) ? v0 : v1, status, n};
+        form.set(a, pass);
+        a.tin = pass > 0;
+        a.tout = pass + 1 < np;
+        const u32* h = hist + (wide ? hist_wide_off(pass) : pass * RADIX);
+        if (pass == 0 && form.w0 == RADIX_BITS + 1) {
+            a.dcnt = threadIdx.x < 2 * RADIX ? h[threadIdx.x] : 0u;
+            radix_tile<SORT_BLOCK, SORT_ITEMS, RADIX_BITS + 1>(s, a, tile);
+        } else {
+            a.dcnt = threadIdx.x < RADIX ? h[threadIdx.x] : 0u;
+            radix_tile<SORT_BLOCK, SORT_ITEMS, RADIX_BITS>(s, a, tile);
+        }
+        // Each thread's words have arrived before the tile is counted.  They were
+        // written through, so that this wait is enough; a fence at agent scope
+        // would write back the XCD's L2 for every tile (1 M keys, four passes:
+        // 92 us, 339 with a fence of every wave, 79 written through).
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+        __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+        __syncthreads();                     // LDS free for the next tile
+        if (pass + 1 < np && threadIdx.x == 0)
+            __hip_atomic_fetch_add(&tickets[1 + pass], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+}
 
 }  // namespace
 
@@ -285,6 +414,23 @@ namespace {
 // loop over tiles (a form that needs more registers, so fewer blocks per CU).
 constexpr u64 DEVICE_COUNT_GRID = 2048;
 constexpr u64 DEVICE_COUNT_MAX_TILES = 1ull << 17;
+
+// Sorts of few keys take k_radix_all, whatever the shape: tiles of 512 x 8 keys
+// where the chip has idle CUs left (500 000 keys, three passes that work: 84 ->
+// 49 us; 30 000: 46 -> 26), of 512 x 16 above (1 M, four passes: 108 -> 82; 2 M, two:
+// 88 -> 59).  A pass between others writes its words through, some 8-byte runs
+// at a time, and at 2 M keys and four passes that takes what the launches saved
+// (126, 128 us; 4 M 157, 211).  A count known on the device alone is mostly
+// far below its bound (the grid's partial rows: 2 M records 125 -> 110 us with the
+// emit, 4 M 154 -> 156 where a record in eight has a row of its own, 88 -> 75
+// where one in fifty has; 8 M 188 -> 243 and 92 -> 81).
+constexpr int ALL_B = 512;
+constexpr u64 ALL_GRID = 512;
+int all_items(u64 n_max, bool counted)  // keys per thread; 0: a launch per pass
+{
+    if (counted) return n_max <= (1u << 22) ? 8 : 0;
+    return n_max <= (1u << 19) ? 8 : n_max <= (1u << 21) ? 16 : 0;
+}
 
 // tile shapes compiled into the library; the sort uses sort_shape()
 struct Shape {
@@ -324,6 +470,13 @@ bool set_sort_shape(int i)
 int sort_tile(int i) { return SHAPES[i].block * SHAPES[i].items; }
 int sort_block(int i) { return SHAPES[i].block; }
 bool sort_wide_first() { return g_wide_first && SHAPES[g_shape].block >= 2 * RADIX; }
+u64 sort_status_words(u64 n_max, bool counted, bool wide)
+{
+    const int items = all_items(n_max, counted);
+    const u64 tile = items ? (u64)ALL_B * items : (u64)sort_tile(g_shape);
+    const bool nine = wide && (items || SHAPES[g_shape].block >= 2 * RADIX);
+    return (n_max + tile - 1) / tile * (nine ? 2 * RADIX : RADIX) + 1;
+}
 int sort_min_tile()
 {
     int m = sort_tile(0);
@@ -341,6 +494,15 @@ void radix_passes(u64* k0, u64* k1, const u32* v_first, u32* v0, u32* v1, u32 n_
     const u64 tile = (u64)sort_tile(sh);
     // the kernels read the first digit's width with the packing words
     if (w0_dev && w0_dev != pack + 2) return;  // (the record sort keeps them adjacent)
+    if (const int items = all_items(n_max, n_dev != nullptr)) {
+        cvh::TimedScope ts_(timed ? names[0] : nullptr, s);
+        const u64 at = ((u64)n_max + ALL_B * items - 1) / (ALL_B * items);
+        const dim3 grid((unsigned)(at < 1 ? 1 : at < ALL_GRID ? at : ALL_GRID));
+        auto* kern = items == 8 ? k_radix_all<ALL_B, 8> : k_radix_all<ALL_B, 16>;
+        hipLaunchKernelGGL(kern, grid, dim3(ALL_B), 0, s, k0, k1, v_first, v0, v1, n_max, n_dev, passes, bits_dev, hist,
+                           w0_dev ? 1u : 0u, status, tickets, pack);
+        return;
+    }
     const u64 tiles = ((u64)n_max + tile - 1) / tile;
     for (int p = 0; p < passes; ++p) {
         const u64* kin = (p & 1) ? k1 : k0;

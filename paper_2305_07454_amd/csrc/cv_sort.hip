@@ -1496,9 +1496,8 @@ struct SortLayout {
         zero_begin = (u32*)(c.base ? c.base + z0 : nullptr);
         zero_bytes = z1 - z0;
         if (c.base) {
-            const u64 st = (u64)(sort_block(sort_shape()) >= 2 * RADIX ? 2 * RADIX : RADIX);
-            const u64 used = ((n + sort_tile(sort_shape()) - 1) / sort_tile(sort_shape())) * st + 1;
-            const size_t zu = cvh::align_up((size_t)((char*)(status + used) - (char*)c.base));
+            const size_t zu =
+                cvh::align_up((size_t)((char*)(status + sort_status_words(n, false, true)) - (char*)c.base));
             zero_bytes = (zu < z1 ? zu : z1) - z0;
         }
         K0 = c.take<u64>(n);
