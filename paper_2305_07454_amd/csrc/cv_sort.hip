@@ -860,7 +860,8 @@ __global__ void __launch_bounds__(256) k_dict_rank(const u64* __restrict__ sorte
 // is probed only where a run of equal ids starts, and the shard (batched form)
 // is followed forward from the range's first one.  SHARDS = false compiles the
 // plain form without the shard search.
-// One input record's payload, packed (the gather's form for interleaved input).
+// One input record's payload, packed (the form that gathers of every column read
+// of interleaved input).
 struct __attribute__((aligned(32))) PayRec {
     i64 ts;
     double lat, lon;
@@ -1128,16 +1129,18 @@ __global__ void __launch_bounds__(256) k_pack_hist(const i64* __restrict__ jid, 
 // in a time-ordered feed), where nearly every record probes the dictionary:
 // every block takes a contiguous range of tiles of PT records, and each
 // record's first probe is issued with the tile's others before any is used.
-// With `pay` (the fused gather), the tile's records are also regrouped
+// With `pay` (gathers of every column), the tile's records are also regrouped
 // by the low byte of their journey rank (a stable local multisplit, so equal
 // keys keep their input order): the key words and the packed payloads go to
 // the regrouped positions, and each payload carries its input index.  After
 // the sort, consecutive records of a journey then read consecutive payloads
 // of each tile instead of one cache line per record.
 constexpr int PT_B = 1024;               // threads per block (tiles of 4 096 records: half the per-tile scans and barriers of 2 048)
-constexpr int PT_I = 4;                  // records per thread
-constexpr int PT = PT_B * PT_I;          // records per tile
-template <bool SHARDS>
+// Records per thread: fewer where tiles of 4 096 would leave most CUs without one
+// (the whole preparation of 30 000 shuffled records with 1, 2 and 4: 37, 41 and 46 us;
+// 125 000: 45, 48, 54; 250 000: 59, 57, 62; 500 000: 83, 81, 87; 1 M: 137, 132, 120).
+inline int pack_items(u64 n) { return n <= (1u << 17) ? 1 : n <= (1u << 19) ? 2 : 4; }
+template <bool SHARDS, int PT_I>
 __global__ void __launch_bounds__(PT_B) k_pack_il(const i64* __restrict__ jid, const i64* __restrict__ ts,
                                                  const double* __restrict__ lat, const double* __restrict__ lon,
                                                  const float* __restrict__ spd, PayRec* __restrict__ pay, u32 n,
@@ -1145,6 +1148,7 @@ __global__ void __launch_bounds__(PT_B) k_pack_il(const i64* __restrict__ jid, c
                                                  u64* __restrict__ keys, u32* __restrict__ hist,
                                                  const u64* __restrict__ soff, u32 S)
 {
+    constexpr int PT = PT_B * PT_I;  // records per tile
     constexpr int NW = PT_B / WAVE;
     __shared__ u32 s_h[HIST_WIDE_WORDS];  // digit counts, wide layout (first digit w0 bits)
     __shared__ u64 c_key[NW][DCP];
@@ -1180,7 +1184,7 @@ __global__ void __launch_bounds__(PT_B) k_pack_il(const i64* __restrict__ jid, c
     const u64 tb1 = tb0 + per < tiles ? tb0 + per : tiles;
     u32 shw = (SHARDS && tb0 < tb1) ? shard_of(soff, S, tb0 * PT) : 0u;
     for (u64 tile = tb0; tile < tb1; ++tile) {
-        const u64 base = tile * PT + (u64)w * (PT_I * WAVE);  // this wave's 512 records
+        const u64 base = tile * PT + (u64)w * (PT_I * WAVE);  // this wave's records
         for (int i = l; i < RADIX; i += WAVE) s_whist[w][i] = 0;
         __syncthreads();
         u64 jv[PT_I], tv[PT_I];
@@ -1318,7 +1322,10 @@ __global__ void __launch_bounds__(PT_B) k_pack_il(const i64* __restrict__ jid, c
 // The final words are packed: (key >> 8 p0) << ib | source index.  Every
 // thread takes GU records a grid stride apart per round, their loads issued
 // together.  SHARDS = false compiles the plain form without the shard search;
-// FULL = true is the form for callers that want every sorted column.
+// FULL = true is the form for callers that want every sorted column; of
+// interleaved input it reads the packed payloads, one line per record instead of
+// one per column (the whole sort of 2 M records in time order: 292 -> 208 us, of
+// 20 M 2355 -> 1622, of 50 000 46 -> 46).
 constexpr int GU = 4;
 template <bool SHARDS, bool FULL>
 __global__ void __launch_bounds__(256) k_gather(u32 n, const SortMeta* m, const u64* __restrict__ K0,
@@ -1328,7 +1335,8 @@ __global__ void __launch_bounds__(256) k_gather(u32 n, const SortMeta* m, const 
                                                 const float* __restrict__ spd, u32* __restrict__ perm,
                                                 i64* __restrict__ o_jid, i64* __restrict__ o_ts,
                                                 double* __restrict__ o_lat, double* __restrict__ o_lon,
-                                                float* __restrict__ o_spd, const u64* __restrict__ soff, u32 S)
+                                                float* __restrict__ o_spd, const u64* __restrict__ soff, u32 S,
+                                                const PayRec* __restrict__ pay)
 {
     const u32 np = m->passes;
     const u32 tb = m->t_bits;
@@ -1348,6 +1356,7 @@ __global__ void __launch_bounds__(256) k_gather(u32 n, const SortMeta* m, const 
     const u64 tmask = tb >= 64 ? ~0ull : ((1ull << tb) - 1);
     const u64 tdiv = ((u64)m->t_p5) << m->t_sh;  // the time offset's unit
     const u64* K = (np & 1) ? K1 : K0;
+    const bool packed = FULL && pay_packed(m, n);  // the sort's index is a payload's place
     const u32 stride = gridDim.x * blockDim.x;
     for (u32 k0 = blockIdx.x * blockDim.x + threadIdx.x; k0 < n; k0 += GU * stride) {
         u64 wv[GU];
@@ -1363,12 +1372,25 @@ __global__ void __launch_bounds__(256) k_gather(u32 n, const SortMeta* m, const 
             // every column requested: all gathers issued before the first store
             double ola[GU], olo[GU];
             float osp[GU];
-            i64 oj[GU], ot[GU];
+            i64 oj[GU], ot[GU], pts[GU];
+            if (packed) {
 #pragma unroll
-            for (int u = 0; u < GU; ++u) {
-                ola[u] = lat[vv[u]];
-                olo[u] = lon[vv[u]];
-                osp[u] = spd[vv[u]];
+                for (int u = 0; u < GU; ++u) {
+                    const ulonglong2* q = (const ulonglong2*)(pay + vv[u]);
+                    const ulonglong2 a = q[0], b = q[1];
+                    pts[u] = (i64)a.x;
+                    ola[u] = __longlong_as_double((long long)a.y);
+                    olo[u] = __longlong_as_double((long long)b.x);
+                    osp[u] = __uint_as_float((u32)b.y);
+                    vv[u] = (u32)(b.y >> 32);
+                }
+            } else {
+#pragma unroll
+                for (int u = 0; u < GU; ++u) {
+                    ola[u] = lat[vv[u]];
+                    olo[u] = lon[vv[u]];
+                    osp[u] = spd[vv[u]];
+                }
             }
             if (rank_in_key) {
 #pragma unroll
@@ -1384,6 +1406,9 @@ __global__ void __launch_bounds__(256) k_gather(u32 n, const SortMeta* m, const 
             if (ts_in_key) {
 #pragma unroll
                 for (int u = 0; u < GU; ++u) ot[u] = (i64)(tmin + ((wv[u] >> ib) & tmask) * tdiv);
+            } else if (packed) {
+#pragma unroll
+                for (int u = 0; u < GU; ++u) ot[u] = pts[u];
             } else {
 #pragma unroll
                 for (int u = 0; u < GU; ++u) ot[u] = ts[vv[u]];
@@ -1873,6 +1898,7 @@ static cv_status sort_impl(const cv_records* in, const uint64_t* soff, uint32_t 
     const u32 mj = (u32)max_journeys;
     const u64 mask = L.slots - 1;
     const int gs = cvh::grid_for(n, 256, 2048);
+    const bool full = so.journey_id && so.ts_ms && so.lat_deg && so.lon_deg && so.speed_mps;
     {
         cvh::TimedScope ts_("sort_prep", s);
         // the insert's per-block parts lie in the second key buffer, which the
@@ -1892,14 +1918,16 @@ static cv_status sort_impl(const cv_records* in, const uint64_t* soff, uint32_t 
                            in->journey_id, in->ts_ms, nn, L.table, mask, L.meta, parts, soff, S);
         launch_dict_order(L, mj, nn, S, mask, parts, (u32)gi, res, s);
         // interleaved input (short runs of equal ids): the payload packed per
-        // record for the fused gather, in the same pass
+        // record for a gather of every column, in the same pass
         hipLaunchKernelGGL(S > 1 ? k_pack_hist<true> : k_pack_hist<false>, dim3(gs), dim3(256), 0, s, in->journey_id,
                            in->ts_ms, nn, L.table, mask, L.meta, L.K0, L.hist, soff, S,
                            (const u32*)L.dlf);
-        hipLaunchKernelGGL(S > 1 ? k_pack_il<true> : k_pack_il<false>, dim3(cvh::grid_for(n, PT, 2048)), dim3(PT_B), 0,
-                           s, in->journey_id,
-                           in->ts_ms, in->lat_deg, in->lon_deg, in->speed_mps, feat ? L.pay : nullptr, nn, L.table,
-                           mask, L.meta, L.K0, L.hist, soff, S);
+        const int pi = pack_items(n);
+        auto* il = S > 1 ? (pi == 1 ? k_pack_il<true, 1> : pi == 2 ? k_pack_il<true, 2> : k_pack_il<true, 4>)
+                         : (pi == 1 ? k_pack_il<false, 1> : pi == 2 ? k_pack_il<false, 2> : k_pack_il<false, 4>);
+        hipLaunchKernelGGL(il, dim3(cvh::grid_for(n, PT_B * pi, 2048)), dim3(PT_B), 0, s, in->journey_id, in->ts_ms,
+                           in->lat_deg, in->lon_deg, in->speed_mps, feat || full ? L.pay : nullptr, nn, L.table, mask,
+                           L.meta, L.K0, L.hist, soff, S);
     }
     radix_passes(L.K0, L.K1, nullptr, L.V0, L.V1, nn, nullptr, &L.meta->sort_bits, MAX_PASSES, L.hist, L.status,
                  L.meta->tickets, s, /*timed=*/true, &L.meta->ib, &L.meta->w0);
@@ -1912,12 +1940,11 @@ static cv_status sort_impl(const cv_records* in, const uint64_t* soff, uint32_t 
                            S, L.pay);
     } else {
         cvh::TimedScope ts_("gather", s);
-        const bool full = so.journey_id && so.ts_ms && so.lat_deg && so.lon_deg && so.speed_mps;
         auto gk = S > 1 ? (full ? k_gather<true, true> : k_gather<true, false>)
                         : (full ? k_gather<false, true> : k_gather<false, false>);
         hipLaunchKernelGGL(gk, dim3(cvh::grid_for(n, 256, 8192)), dim3(256), 0, s, nn, L.meta, L.K0, L.K1, dict_ids,
                            in->journey_id, in->ts_ms, in->lat_deg, in->lon_deg, in->speed_mps, perm,
-                           so.journey_id, so.ts_ms, so.lat_deg, so.lon_deg, so.speed_mps, soff, S);
+                           so.journey_id, so.ts_ms, so.lat_deg, so.lon_deg, so.speed_mps, soff, S, L.pay);
     }
     cvh::debug_sort(L.K0, L.K1, &L.meta->passes, &L.meta->range_err, &L.meta->overflow, n, perm, soff, S, s);
     return cvh::last_launch_status();

@@ -92,3 +92,27 @@ def test_streams_and_replays(cv):
         g.replay()
         torch.cuda.synchronize()
         assert np.array_equal(host(perm).astype(np.int64), exp[k])
+
+
+@pytest.mark.parametrize("n", [1, 1_023, 1_025, (1 << 17) - 1, (1 << 17) + 1, (1 << 19) - 1, (1 << 19) + 1, 1_048_577])
+@pytest.mark.parametrize("ids", [1_000, 70_000])
+def test_payload_tiles(cv, n, ids):
+    # interleaved ids: the payloads regrouped in tiles of 1 024, 2 048 and 4 096
+    # records, read by the gather of every column and by the one with the kinematics
+    import torch
+    print(f"[payload] n={n} ids={ids}", flush=True)
+    cols = _columns(n, ids, 12)
+    exp = np.lexsort((cols[1], cols[0]))
+    d = cv.to_device(cols)
+    perm, srt, _ = cv.cv_sort_records(d, max_journeys=ids + 1)
+    fperm, fsrt, feat, _ = cv.cv_sort_records_features(d, ids + 1)
+    for p, s in ((perm, srt), (fperm, fsrt)):
+        assert np.array_equal(host(p).astype(np.int64), exp)
+        for k, c in zip(("journey_id", "ts_ms", "lat_deg", "lon_deg", "speed_mps"), cols):
+            assert np.array_equal(host(s[k]), c[exp]), k
+    off, off_d = cv.shard_offsets([n // 3, 0, n - n // 3])
+    sperm, ssrt, _, _ = cv.cv_sort_records_features(d, 2 * ids + 2, shard_offsets=off_d)
+    a = n // 3
+    lo, hi = np.lexsort((cols[1][:a], cols[0][:a])), np.lexsort((cols[1][a:], cols[0][a:]))
+    assert np.array_equal(host(sperm).astype(np.int64), np.concatenate([lo, hi]))
+    assert np.array_equal(host(ssrt["lon_deg"]), np.concatenate([cols[3][:a][lo], cols[3][a:][hi]]))
