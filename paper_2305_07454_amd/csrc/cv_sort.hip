@@ -131,8 +131,9 @@ struct RunMask {
 
 // The sort's scratch in one launch: the meta words, the dictionary's empty
 // slots and the region cleared to zero.
+// used (nullable): the occupied slots' bits.
 __global__ void __launch_bounds__(256) k_sort_begin(SortMeta* m, u64* __restrict__ table, u64 words,
-                                                    u32* __restrict__ zero, u64 zwords)
+                                                    u32* __restrict__ zero, u64 zwords, u32* __restrict__ used)
 {
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         SortMeta z = {};
@@ -143,6 +144,8 @@ __global__ void __launch_bounds__(256) k_sort_begin(SortMeta* m, u64* __restrict
     ulonglong2* t2 = (ulonglong2*)table;  // slots are 16-byte pairs
     for (u64 i = i0; i < words / 2; i += stride) t2[i] = make_ulonglong2(EMPTY, EMPTY);
     for (u64 i = i0; i < zwords; i += stride) zero[i] = 0u;
+    if (used)
+        for (u64 i = i0; i < words / 64; i += stride) used[i] = 0u;  // (two words per slot)
 }
 
 // The dictionary is an open-addressing table of 16-byte slots {id, rank}:
@@ -159,8 +162,14 @@ __device__ __forceinline__ u64 slot_now(const u64* p)
 {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-// Returns the id's slot, or ~0 when the table is full.
-__device__ __forceinline__ u64 dict_insert_from(u64* table, u64 mask, u64 key, u64 h, u64 cur)
+// A slot's first insert sets its bit of `used` (nullable), so that the ids are
+// listed without reading a table that is mostly empty where the caller had to
+// allow for an id per record.  Returns the id's slot, or ~0 when the table is full.
+__device__ __forceinline__ void slot_used(u32* used, u64 h)
+{
+    if (used) atomicOr(&used[h / 32], 1u << (h % 32));
+}
+__device__ __forceinline__ u64 dict_insert_from(u64* table, u64 mask, u64 key, u64 h, u64 cur, u32* used)
 {
     for (u64 probe = 0; probe <= mask; ++probe) {
         if (cur == EMPTY) cur = slot_now(&table[2 * h]);
@@ -168,6 +177,7 @@ __device__ __forceinline__ u64 dict_insert_from(u64* table, u64 mask, u64 key, u
         if (cur == EMPTY) {
             u64 prev =
                 atomicCAS((unsigned long long*)&table[2 * h], (unsigned long long)EMPTY, (unsigned long long)key);
+            if (prev == EMPTY) slot_used(used, h);
             if (prev == EMPTY || prev == key) return h;
         }
         h = (h + 1) & mask;
@@ -186,14 +196,15 @@ __device__ __forceinline__ void run_store(u64* word, bool start, u32 at)
 __device__ __forceinline__ u32 run_start(u64 w) { return (u32)(w >> 32); }
 __device__ __forceinline__ u32 run_length(u64 w) { return (u32)w - (u32)(w >> 32); }
 // the run of `key` ends before record `at`
-__device__ __forceinline__ void run_end(u64* table, u64 mask, SortMeta* m, u64 key, u32 at, bool& full)
+__device__ __forceinline__ void run_end(u64* table, u64 mask, SortMeta* m, u64 key, u32 at, bool& full,
+                                        u32* used)
 {
     if (key == EMPTY) {
         m->min_end = at;
         return;
     }
     const u64 h = mix64(key) & mask;
-    const u64 slot = dict_insert_from(table, mask, key, h, table[2 * h]);
+    const u64 slot = dict_insert_from(table, mask, key, h, table[2 * h], used);
     if (slot == ~0ull) full = true;
     else run_store(&table[2 * slot + 1], false, at);
 }
@@ -205,7 +216,7 @@ __device__ __forceinline__ void run_end(u64* table, u64 mask, SortMeta* m, u64 k
 // compare-and-swap, so exactly one shard wins and any other sees it.
 // Returns false when the table is full.
 __device__ __forceinline__ bool dict_insert_tag(u64* table, u64 mask, u64 key, u64 h, ulonglong2 e, u64 sh,
-                                                bool& multi)
+                                                bool& multi, u32* used)
 {
     const ulonglong2* t2 = (const ulonglong2*)table;
     for (u64 probe = 0; probe <= mask; ++probe) {
@@ -217,6 +228,7 @@ __device__ __forceinline__ bool dict_insert_tag(u64* table, u64 mask, u64 key, u
         if (!mine && e.x == EMPTY) {
             const u64 prev =
                 atomicCAS((unsigned long long*)&table[2 * h], (unsigned long long)EMPTY, (unsigned long long)key);
+            if (prev == EMPTY) slot_used(used, h);
             mine = prev == EMPTY || prev == key;
         }
         if (mine) {
@@ -343,12 +355,14 @@ __device__ __forceinline__ void part_wave_join(InsPart& p)
 // start, and a window of a shard other than the one its wave's cache was
 // filled in empties the cache (whose entries would skip the shard check); a
 // window with a shard start inside goes without it.
-template <bool SHARDS>
+// USED: the occupied slots' bits are kept.
+template <bool SHARDS, bool USED>
 __global__ void __launch_bounds__(256) k_dict_insert(const i64* __restrict__ jid, const i64* __restrict__ ts, u32 n,
                                                      u64* __restrict__ table, u64 mask, SortMeta* m,
                                                      InsPart* __restrict__ parts, const u64* __restrict__ soff,
-                                                     u32 S)
+                                                     u32 S, u32* used_)
 {
+    u32* used = USED ? used_ : nullptr;
     // (the batched form's 16-byte probes and shard checks take it to 4 waves
     // per SIMD, with 3 windows per round as with 4)
     constexpr int DP = DPW;
@@ -518,8 +532,8 @@ __global__ void __launch_bounds__(256) k_dict_insert(const i64* __restrict__ jid
             if (!SHARDS && !far) {
                 // where the run before each run start ends; the last run
                 const u64 jb = (u64)lane_below(jv[k], jlast[k]);
-                if (((heads[k] >> l) & 1ull) && wi + l > 0) run_end(table, mask, m, jb, (u32)(wi + l), full);
-                if (wi + l + 1 == n) run_end(table, mask, m, j, n, full);
+                if (((heads[k] >> l) & 1ull) && wi + l > 0) run_end(table, mask, m, jb, (u32)(wi + l), full, used);
+                if (wi + l + 1 == n) run_end(table, mask, m, j, n, full, used);
             }
             const u32 cs = dict_cache_slot<DC>(j);
             // an earlier window of the round may have brought the id; of the
@@ -537,9 +551,9 @@ __global__ void __launch_bounds__(256) k_dict_insert(const i64* __restrict__ jid
                     // the record's shard: the window's, or searched where a shard starts inside it
                     const u64 i = wi + l;
                     const u32 sh = wsh[k] != ~0u ? wsh[k] : shard_of(soff, S, i < n ? i : (u64)n - 1);
-                    if (!dict_insert_tag(table, mask, j, ph[k], pe[k], (u64)sh, multi)) full = true;
+                    if (!dict_insert_tag(table, mask, j, ph[k], pe[k], (u64)sh, multi, used)) full = true;
                 } else {
-                    const u64 slot = dict_insert_from(table, mask, j, ph[k], pe[k].x);
+                    const u64 slot = dict_insert_from(table, mask, j, ph[k], pe[k].x, used);
                     if (slot == ~0ull) full = true;
                     else if (!far) run_store(&table[2 * slot + 1], true, (u32)(wi + l));
                 }
@@ -658,14 +672,20 @@ __device__ __forceinline__ void dict_settle(SortMeta* m, const InsPart* __restri
 }
 
 // The dictionary's ids to a list (any order), with their slots' second words
-// (batched: the ids' shards, else their runs).  Each
-// thread takes CPT_D slots per round, so that a round's one claim of list
-// places (atomics on one word, which serialise) covers 1 024 slots.
-constexpr int CPT_D = 4;
+// (batched: the ids' shards, else their runs), by their bits in `used` (nullable) or
+// from the table.  Each thread takes `per` slots per round, so that a round's one claim
+// of list places (atomics on one word, which serialise) covers 256 times as many.
+// Large tables are mostly empty (a push allows for an id per record): 4 M slots take
+// 74 us from the table, 31 by the bits, 512 k 20 and 10, and a serving session of
+// eight pushes went from 3062 to 2829 us.  Small ones are up to half full: setting
+// the bits costs as much as they save, and 16 slots to a thread 3 us more than 4.
+constexpr u64 USED_MIN = 1u << 18;  // slots from which the bits are kept
+inline __host__ __device__ u32 compact_slots(u64 slots) { return slots >= USED_MIN ? 16u : 4u; }
 __global__ void __launch_bounds__(256) k_dict_compact(u64* __restrict__ table, u64 slots, u32 max_j,
                                                       SortMeta* m, u64* __restrict__ list, u64* __restrict__ tag,
                                                       const InsPart* __restrict__ parts, u32 nparts, u32 n,
-                                                      u32 n_shards, u32 allow_wide, cv_result* res)
+                                                      u32 n_shards, u32 allow_wide, cv_result* res,
+                                                      const u32* __restrict__ used)
 {
     __shared__ u32 s_t[256 / WAVE];
     __shared__ u32 s_base;
@@ -675,30 +695,31 @@ __global__ void __launch_bounds__(256) k_dict_compact(u64* __restrict__ table, u
         tag[0] = n_shards > 1 ? 0ull : ((u64)m->min_start << 32) | m->min_end;
     }
     const ulonglong2* t2 = (const ulonglong2*)table;
-    const u64 stride = (u64)gridDim.x * 256 * CPT_D;
-    for (u64 b = (u64)blockIdx.x * 256 * CPT_D; b < slots; b += stride) {
-        ulonglong2 e[CPT_D];
-        u32 c = 0;
-#pragma unroll
-        for (int q = 0; q < CPT_D; ++q) {
-            const u64 sl = b + q * 256 + threadIdx.x;
-            e[q].x = EMPTY;
-            if (sl < slots) e[q] = t2[sl];
-            c += e[q].x != EMPTY;
+    const u32 per = compact_slots(slots);
+    const u64 stride = (u64)gridDim.x * 256;
+    for (u64 b = (u64)blockIdx.x * 256; b < slots / per; b += stride) {
+        const u64 s0 = (b + threadIdx.x) * per;
+        u32 mask = 0;
+        if (s0 < slots) {
+            if (used) {
+                mask = (used[s0 / 32] >> (s0 % 32)) & ((1u << per) - 1u);
+            } else {
+                for (u32 q = 0; q < per; ++q) mask |= table[2 * (s0 + q)] != EMPTY ? 1u << q : 0u;
+            }
         }
         u32 tot;
-        const u32 ex = block_exclusive_sum<256>(c, s_t, tot);
+        const u32 ex = block_exclusive_sum<256>((u32)__popc(mask), s_t, tot);
         if (threadIdx.x == 0) s_base = tot ? atomicAdd(&m->list_count, tot) : 0u;
         __syncthreads();
         u32 pos = s_base + ex + hm;
-#pragma unroll
-        for (int q = 0; q < CPT_D; ++q) {
-            if (e[q].x == EMPTY) continue;
+        for (; mask; mask &= mask - 1) {
+            const u64 sl = s0 + (u32)__ffs((int)mask) - 1;
+            const ulonglong2 e = t2[sl];
             if (pos < max_j) {
-                list[pos] = e[q].x ^ SIGN;
-                tag[pos] = e[q].y;
+                list[pos] = e.x ^ SIGN;
+                tag[pos] = e.y;
             } else if (n_shards <= 1) {
-                table[2 * (b + q * 256 + threadIdx.x) + 1] = 0;  // an id beyond the capacity gets no rank: 0
+                table[2 * sl + 1] = 0;  // an id beyond the capacity gets no rank: 0
             }
             ++pos;
         }
@@ -1800,7 +1821,7 @@ __global__ void __launch_bounds__(256) k_gather_feat(u32 n, const SortMeta* m, c
 // that it does not choose leaves at once.
 template <bool SH>
 void launch_dict_order_as(const SortLayout& L, u32 mj, u32 n, u32 S, u64 mask, const InsPart* parts, u32 nparts,
-                          cv_result* res, hipStream_t s)
+                          const u32* used, cv_result* res, hipStream_t s)
 {
     // the counted ids may not be written over the list they are counted in
     u64* out = SH ? L.dlf : L.dl1;
@@ -1808,8 +1829,9 @@ void launch_dict_order_as(const SortLayout& L, u32 mj, u32 n, u32 S, u64 mask, c
     u64* tag = SH ? words : nullptr;
     u64* runs = SH ? nullptr : L.dsk1;        // the journeys' runs by rank
     u32* delta = SH ? nullptr : (u32*)L.dlf;  // see k_dict_count
-    hipLaunchKernelGGL(k_dict_compact, dim3(cvh::grid_for(L.slots, 256 * CPT_D, 2048)), dim3(256), 0, s, L.table,
-                       L.slots, mj, L.meta, L.dl0, words, parts, nparts, n, S, sort_wide_first() ? 1u : 0u, res);
+    hipLaunchKernelGGL(k_dict_compact, dim3(cvh::grid_for(L.slots, 256 * compact_slots(L.slots), 2048)), dim3(256), 0, s, L.table,
+                       L.slots, mj, L.meta, L.dl0, words, parts, nparts, n, S, sort_wide_first() ? 1u : 0u, res,
+                       used);
     hipLaunchKernelGGL(k_dict_count<SH>, dim3(cvh::grid_for(mj < DS_COUNT ? mj : DS_COUNT, WAVE)), dim3(DS_B), 0, s,
                        L.meta, L.table, mask, L.dl0, words, out, delta);
     if (mj <= DS_COUNT) return;
@@ -1860,10 +1882,10 @@ void launch_dict_order_as(const SortLayout& L, u32 mj, u32 n, u32 S, u64 mask, c
 }
 
 void launch_dict_order(const SortLayout& L, u32 mj, u32 n, u32 S, u64 mask, const InsPart* parts, u32 nparts,
-                       cv_result* res, hipStream_t s)
+                       const u32* used, cv_result* res, hipStream_t s)
 {
-    if (S > 1) launch_dict_order_as<true>(L, mj, n, S, mask, parts, nparts, res, s);
-    else launch_dict_order_as<false>(L, mj, n, S, mask, parts, nparts, res, s);
+    if (S > 1) launch_dict_order_as<true>(L, mj, n, S, mask, parts, nparts, used, res, s);
+    else launch_dict_order_as<false>(L, mj, n, S, mask, parts, nparts, used, res, s);
 }
 
 }  // namespace
@@ -1906,17 +1928,22 @@ static cv_status sort_impl(const cv_records* in, const uint64_t* soff, uint32_t 
         // every buffer holds at least 256 bytes)
         InsPart* parts = (InsPart*)L.K1;
         static_assert(sizeof(InsPart) <= 256, "one part fits the smallest buffer");
+        // the occupied slots' bits lie in the first key buffer, which the packing
+        // writes later (not where the caller allows for far more ids than records)
+        u32* used = L.slots >= USED_MIN && L.slots / 8 <= n * sizeof(u64) ? (u32*)L.K0 : nullptr;
         const u64 fill_words = L.slots > L.zero_bytes / 4 ? L.slots : L.zero_bytes / 4;
         hipLaunchKernelGGL(k_sort_begin, dim3(cvh::grid_for(fill_words, 256, 4096)), dim3(256), 0, s, L.meta, L.table,
-                           2 * L.slots, L.zero_begin, (u64)(L.zero_bytes / 4));
+                           2 * L.slots, L.zero_begin, (u64)(L.zero_bytes / 4), used);
         // at least 8 windows per wave, so that a wave meets ids in its cache
         // (insert of 1 M shuffled records of 2 000 journeys 383 -> 55 us, of a
         // 2 M batch 242 -> 24, of a 437 k push 75 -> 27, of a 200 M batch 1 760 -> 1 430;
         // with the slots read again and one insert per id and window, below)
         const int gi = cvh::grid_for(n, 256 * 8, 2048);
-        hipLaunchKernelGGL(S > 1 ? k_dict_insert<true> : k_dict_insert<false>, dim3(gi), dim3(256), 0, s,
-                           in->journey_id, in->ts_ms, nn, L.table, mask, L.meta, parts, soff, S);
-        launch_dict_order(L, mj, nn, S, mask, parts, (u32)gi, res, s);
+        auto* ins = S > 1 ? (used ? k_dict_insert<true, true> : k_dict_insert<true, false>)
+                          : (used ? k_dict_insert<false, true> : k_dict_insert<false, false>);
+        hipLaunchKernelGGL(ins, dim3(gi), dim3(256), 0, s, in->journey_id, in->ts_ms, nn, L.table, mask,
+                           L.meta, parts, soff, S, used);
+        launch_dict_order(L, mj, nn, S, mask, parts, (u32)gi, used, res, s);
         // interleaved input (short runs of equal ids): the payload packed per
         // record for a gather of every column, in the same pass
         hipLaunchKernelGGL(S > 1 ? k_pack_hist<true> : k_pack_hist<false>, dim3(gs), dim3(256), 0, s, in->journey_id,

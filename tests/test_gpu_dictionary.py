@@ -87,3 +87,21 @@ def test_more_ids_than_the_capacity(cv, capacity):
     with pytest.raises(cv.CvError) as e:
         cv.cv_sort_records(cv.to_device(tuple(cols)), max_journeys=capacity)
     assert e.value.status == cv.CV_ERR_CAPACITY
+
+
+@pytest.mark.parametrize("n,capacity", [(33_000, 131_072), (4_095, 131_072), (4_096, 131_072), (4_097, 131_072),
+                                        (40_000, 600_000), (200_000, 200_000)])
+@pytest.mark.parametrize("J", [1, 500, 4_000])
+def test_ids_listed_by_their_bits(cv, n, capacity, J):
+    """Tables of 2^18 slots and more, whose occupied slots are listed by their
+    bits, with the records that give the bits room (slots / 64) and fewer."""
+    print(f"[dictionary] n={n} capacity={capacity} J={J}", flush=True)
+    cols = _columns(n, J, n - J)
+    perm, srt, r = cv.cv_sort_records(cv.to_device(tuple(cols)), max_journeys=capacity)
+    assert r["count"] == J
+    assert_exact("perm", u32(host(perm)), np.lexsort((cols[1], cols[0])).astype(np.uint32))
+    off = cv.shard_offsets([n // 2, n - n // 2])[1]
+    perm, srt, _, r = cv.cv_sort_records_features(cv.to_device(tuple(cols)), capacity, shard_offsets=off)
+    a = n // 2
+    exp = np.concatenate([np.lexsort((cols[1][:a], cols[0][:a])), np.lexsort((cols[1][a:], cols[0][a:]))])
+    assert_exact("perm", u32(host(perm)), exp.astype(np.uint32))
