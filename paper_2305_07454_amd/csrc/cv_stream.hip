@@ -82,7 +82,7 @@ struct StreamMeta {
                         // distinct-journey counts may be high (sticky)
     u32 ovf_next;       // overflow tables taken from the pool
     u32 ap_n;           // cells appended this push (records that counted their journey in a cell)
-    u32 pad3;
+    u32 ticket;         // tiles taken by k_st_heads this push
     u64 batch_late, batch_out;
     u64 total_records, total_late, total_out;
     u32 jcount;         // flush: occupied journey rows
@@ -126,9 +126,12 @@ __global__ void k_st_init_meta(StreamMeta* m)
     }
 }
 
-__global__ void k_st_begin(StreamMeta* m)
+// also clears the look-back words of the batch's tiles
+__global__ void __launch_bounds__(256) k_st_begin(StreamMeta* m, u64* __restrict__ status, u32 tiles)
 {
+    for (u32 i = threadIdx.x; i < tiles; i += 256) status[i] = 0;
     if (threadIdx.x == 0) {
+        m->ticket = 0;
         m->batch_late = 0;
         m->batch_out = m->gm.n_out;  // the count before this batch
         m->ap_n = 0;
@@ -137,60 +140,64 @@ __global__ void k_st_begin(StreamMeta* m)
 }
 
 // journey starts per tile of the sorted batch
-__global__ void __launch_bounds__(256) k_st_count(const i64* __restrict__ jid, u32 n, u32* __restrict__ cnt)
+// The batch's journeys in one pass over the sorted ids: boff[j] = position of batch
+// journey j's first record, boff[Jb] = n, Jb.  Tiles are taken by ticket; a tile's
+// starts are numbered by ballots per row of 64 records and follow the tiles before
+// (decoupled look-back over `status`).  Counting, scanning and numbering in three
+// launches read the ids twice and took 18 us of a push on average, this 7.
+__global__ void __launch_bounds__(256) k_st_heads(const i64* __restrict__ jid, u32 n, u32 tiles, StreamMeta* m,
+                                                  u64* __restrict__ status, u32* __restrict__ boff)
 {
-    __shared__ u32 tmp[4];
-    const u64 base = (u64)blockIdx.x * ST_TILE;
-    u32 c = 0;
-    for (int i = threadIdx.x; i < ST_TILE; i += 256) {
-        const u64 r = base + i;
-        if (r < n && (r == 0 || jid[r] != jid[r - 1])) ++c;
-    }
-    u32 tot;
-    block_exclusive_sum<256>(c, tmp, tot);
-    if (threadIdx.x == 0) cnt[blockIdx.x] = tot;
-}
-
-__global__ void __launch_bounds__(256) k_st_scan(u32* __restrict__ cnt, u32 tiles, StreamMeta* m)
-{
-    __shared__ u32 tmp[4];
-    __shared__ u32 carry;
-    if (threadIdx.x == 0) carry = 0;
+    constexpr int PER = ST_TILE / 256;        // rows per wave
+    constexpr int WREC = ST_TILE / 4;         // consecutive records per wave
+    static_assert(PER * 4 == WAVE, "one row count per lane");
+    __shared__ u32 s_cnt[WAVE];
+    __shared__ u32 s_tile, s_excl;
+    if (threadIdx.x == 0) s_tile = atomicAdd(&m->ticket, 1u);
     __syncthreads();
-    for (u32 b = 0; b < tiles; b += 256) {
-        const u32 i = b + threadIdx.x;
-        const u32 v = i < tiles ? cnt[i] : 0u;
-        u32 tot;
-        const u32 e = block_exclusive_sum<256>(v, tmp, tot);
-        if (i < tiles) cnt[i] = carry + e;
-        __syncthreads();
-        if (threadIdx.x == 0) carry += tot;
-        __syncthreads();
+    const u32 tile = s_tile;
+    const int l = lane_id();
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
+    const u64 base = (u64)tile * ST_TILE + (u64)w * WREC;
+    i64 v[PER];
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        const u64 r = base + (u64)i * WAVE + l;
+        v[i] = jid[r < n ? r : (u64)n - 1];
     }
-    if (threadIdx.x == 0) m->Jb = carry;
-}
-
-// boff[j] = sorted position of batch journey j's first record; boff[Jb] = n
-__global__ void __launch_bounds__(256) k_st_heads(const i64* __restrict__ jid, u32 n, const u32* __restrict__ prefix,
-                                                  const StreamMeta* m, u32* __restrict__ boff)
-{
-    __shared__ u32 tmp[4];
-    const u64 base = (u64)blockIdx.x * ST_TILE;
-    // each thread takes ST_TILE/256 consecutive records so positions stay ordered
-    constexpr int PER = ST_TILE / 256;
-    const u64 r0 = base + (u64)threadIdx.x * PER;
+    i64 before = base > 0 ? jid[base - 1 < n ? base - 1 : (u64)n - 1] : 0;
+    u64 hm[PER];
     u32 c = 0;
+#pragma unroll
     for (int i = 0; i < PER; ++i) {
-        const u64 r = r0 + i;
-        if (r < n && (r == 0 || jid[r] != jid[r - 1])) ++c;
+        const u64 r = base + (u64)i * WAVE + l;
+        const i64 b = lane_below(v[i], before);
+        before = lane_last(v[i]);
+        hm[i] = __ballot(r < n && (r == 0 || v[i] != b));
+        c = l == i ? (u32)__popcll(hm[i]) : c;
     }
-    u32 tot;
-    u32 e = block_exclusive_sum<256>(c, tmp, tot) + prefix[blockIdx.x];
+    if (l < PER) s_cnt[w * PER + l] = c;
+    __syncthreads();
+    const u32 mine = s_cnt[l];
+    const u32 inc = wave_inclusive_sum(mine);
+    const u32 total = (u32)__builtin_amdgcn_readlane((int)inc, WAVE - 1);
+    if (w == 0) {
+        const u64 e = wave_lookback_exclusive(status, tile, total);
+        if (l == 0) s_excl = (u32)e;
+    }
+    __syncthreads();
+    const u32 excl = s_excl;
+#pragma unroll
     for (int i = 0; i < PER; ++i) {
-        const u64 r = r0 + i;
-        if (r < n && (r == 0 || jid[r] != jid[r - 1])) boff[e++] = (u32)r;
+        if ((hm[i] >> l) & 1ull) {
+            const u32 at = (u32)__builtin_amdgcn_readlane((int)(inc - mine), w * PER + i);
+            boff[excl + at + popc_below(hm[i])] = (u32)(base + (u64)i * WAVE + l);
+        }
     }
-    if (blockIdx.x == 0 && threadIdx.x == 0) boff[m->Jb] = n;
+    if (tile == tiles - 1 && threadIdx.x == 0) {
+        m->Jb = excl + total;
+        boff[excl + total] = n;
+    }
 }
 
 __global__ void __launch_bounds__(256) k_st_journeys(const i64* __restrict__ jid, const u32* __restrict__ boff,
@@ -757,7 +764,7 @@ struct cv_stream {
     float* s_spd;
     double *fs_step, *fs_v, *fs_b;
     uint8_t* fs_flags;
-    u32 *tile_cnt, *boff, *bslot;
+    u32 *boff, *bslot;
     cv_result* sres;
     cv::JAcc* acc;  // exact partial summaries of the batch's journeys
     cv::AccX* accx;
@@ -786,7 +793,6 @@ struct StreamLayout {
     static void carve(cvh::Carver& c, u64 jslots, u64 gslots, u64 mb, F&& f)
     {
         const u64 opages = ovf_pages(jslots);
-        const u64 tiles = (mb + ST_TILE - 1) / ST_TILE;
         size_t sort_ws = 0;
         cv_sort_workspace_size(mb, mb ? mb : 1, &sort_ws);
         f("meta", c.take<StreamMeta>(1));
@@ -806,7 +812,6 @@ struct StreamLayout {
         f("fs_v", c.take<double>(mb));
         f("fs_b", c.take<double>(mb));
         f("fs_flags", c.take<uint8_t>(mb));
-        f("tile_cnt", c.take<u32>(tiles + 1));
         f("boff", c.take<u32>(mb + 1));
         f("bslot", c.take<u32>(mb + 1));
         f("sres", c.take<cv_result>(1));
@@ -928,11 +933,9 @@ cv_status cv_stream_create(const cv_grid_spec* grid, uint64_t max_journeys, uint
     g.t0 = grid->t0_ms;
     g.bin_ms = grid->bin_ms;
     g.tinv = 1.0 / (double)grid->bin_ms;
-    g.rlat = 1.0 / grid->dlat_deg;
-    g.rlon = 1.0 / grid->dlon_deg;
-    g.cells = (u64)grid->n_lat * (u64)grid->n_lon;
-    const auto inverts = [](double d) { return d > 1e-100 && d < 1e100; };
-    g.quick = grid->bin_ms < (1ll << 30) && g.cells < (1ull << 32) && inverts(grid->dlat_deg) && inverts(grid->dlon_deg);
+    g.rlat = g.rlon = 0.0;  // (the serving tiles are not bound by their keys: 460 us with them or the reciprocals)
+    g.cells = 0;
+    g.quick = 0;
     g.tmax = grid->n_t > 0 ? grid->n_t : (INT64_MAX / (grid->n_lat * grid->n_lon));
     g.soff = nullptr;
     g.S = 0;
@@ -965,7 +968,6 @@ cv_status cv_stream_create(const cv_grid_spec* grid, uint64_t max_journeys, uint
         else if (nm == "fs_v") st->fs_v = (double*)p;
         else if (nm == "fs_b") st->fs_b = (double*)p;
         else if (nm == "fs_flags") st->fs_flags = (uint8_t*)p;
-        else if (nm == "tile_cnt") st->tile_cnt = (u32*)p;
         else if (nm == "boff") st->boff = (u32*)p;
         else if (nm == "bslot") st->bslot = (u32*)p;
         else if (nm == "sres") st->sres = (cv_result*)p;
@@ -1011,7 +1013,7 @@ cv_status cv_stream_push(cv_stream* st, const cv_records* batch, const cv_featur
     const u64 n = batch->n;
     hipStream_t s = (hipStream_t)stream;
     if (n == 0) {
-        hipLaunchKernelGGL(k_st_begin, dim3(1), dim3(64), 0, s, st->meta);
+        hipLaunchKernelGGL(k_st_begin, dim3(1), dim3(256), 0, s, st->meta, (u64*)nullptr, 0u);
         if (res) {
             cvh::fill_u32(st->sres, 0u, sizeof(cv_result) / 4, s);
             hipLaunchKernelGGL(k_st_finish, dim3(1), dim3(64), 0, s, st->meta, st->sres, 0u, res);
@@ -1024,7 +1026,9 @@ cv_status cv_stream_push(cv_stream* st, const cv_records* batch, const cv_featur
         return CV_ERR_INVALID_ARGUMENT;
     const u32 nn = (u32)n;
     cvh::TimedScope ts_("stream_push", s);
-    hipLaunchKernelGGL(k_st_begin, dim3(1), dim3(64), 0, s, st->meta);
+    const u32 tiles = (u32)((n + ST_TILE - 1) / ST_TILE);
+    // the tiles' look-back words lie in the journeys' slots, which are written after them
+    hipLaunchKernelGGL(k_st_begin, dim3(1), dim3(256), 0, s, st->meta, (u64*)st->bslot, tiles);
     cv_records_out so{st->s_jid, st->s_ts, st->s_lat, st->s_lon, st->s_spd};
     cv_status e = CV_OK;
     {
@@ -1034,13 +1038,10 @@ cv_status cv_stream_push(cv_stream* st, const cv_records* batch, const cv_featur
         e = cv::sort_records_into(batch, n, st->perm, &so, st->sres, st->sort_ws, st->sort_ws_bytes, s);
         if (e != CV_OK) return e;
     }
-    const u32 tiles = (u32)((n + ST_TILE - 1) / ST_TILE);
     {
         cvh::TimedScope t2("stream_journeys", s);
-        hipLaunchKernelGGL(k_st_count, dim3(tiles), dim3(256), 0, s, st->s_jid, nn, st->tile_cnt);
-        hipLaunchKernelGGL(k_st_scan, dim3(1), dim3(256), 0, s, st->tile_cnt, tiles, st->meta);
-        hipLaunchKernelGGL(k_st_heads, dim3(tiles), dim3(256), 0, s, st->s_jid, nn, st->tile_cnt, st->meta,
-                           st->boff);
+        hipLaunchKernelGGL(k_st_heads, dim3(tiles), dim3(256), 0, s, st->s_jid, nn, tiles, st->meta,
+                           (u64*)st->bslot, st->boff);
         hipLaunchKernelGGL(k_st_journeys, dim3(cvh::grid_for(n, 256, 2048)), dim3(256), 0, s, st->s_jid, st->boff,
                            st->meta, st->jkeys, st->jslots - 1, st->rows, st->bslot);
     }
