@@ -42,6 +42,10 @@ constexpr u32 CMP_TILES = 4;     // tiles per block at least (one per wave)
 constexpr u32 CMP_FULL = 48;     // tiles per block from which twice as many blocks pay
 constexpr u32 EMIT_BLOCKS = 2048;
 constexpr u32 EMIT_CHUNKS = 2;   // chunks of the bound per block at least
+// With directions a tile may have a row for every two or three records, and the
+// blocks above are too few for the rows (derived bearings, emit of 100 000
+// records 142 us with them, 80 with these; 9 M: 983, 846).
+constexpr u32 DIRS_EMIT_BLOCKS = 4096, DIRS_EMIT_CHUNKS = 1;
 // sorted partial pairs per chunk of the head count and the emit
 constexpr int ECB = 256;
 constexpr int ECP = 4;  // (4: 118 VGPRs in the emit, 4 waves per SIMD)
@@ -69,7 +73,7 @@ struct GridLayout {
     u64 pmax, stiles, tiles, chunks;
     u32 cblocks, eblocks;
     size_t bytes;
-    GridLayout(void* ws, u64 n)
+    GridLayout(void* ws, u64 n, bool dirs = false)
     {
         cvh::Carver c(ws);
         tiles = (n + GT - 1) / GT;
@@ -77,7 +81,8 @@ struct GridLayout {
         stiles = (pmax + sort_min_tile() - 1) / sort_min_tile();
         chunks = (pmax + ECH - 1) / ECH;
         cblocks = (u32)cvh::grid_for(tiles, CMP_TILES, tiles > CMP_BLOCKS * CMP_FULL ? 2 * CMP_BLOCKS : CMP_BLOCKS);
-        eblocks = (u32)cvh::grid_for(chunks, EMIT_CHUNKS, EMIT_BLOCKS);
+        eblocks = dirs ? (u32)cvh::grid_for(chunks, DIRS_EMIT_CHUNKS, DIRS_EMIT_BLOCKS)
+                       : (u32)cvh::grid_for(chunks, EMIT_CHUNKS, EMIT_BLOCKS);
         meta = c.take<PartMeta>(1);
         part = c.take<GPart>(pmax);
         K0 = c.take<u64>(pmax);
@@ -89,11 +94,11 @@ struct GridLayout {
         size_t z0 = cvh::align_up(c.off);
         hist = c.take<u32>(MAX_PASSES * RADIX);
         lb1 = c.take<u64>(cblocks);
-        lb2 = c.take<u64>(eblocks);
+        lb2 = c.take<u64>((u64)cvh::grid_for(chunks, DIRS_EMIT_CHUNKS, DIRS_EMIT_BLOCKS));
         // last in the cleared range: a call clears what its tile shape uses
         status = c.take<u64>(stiles * RADIX + 1);
         zero_begin = (u32*)(c.base ? c.base + z0 : nullptr);
-        const size_t used = c.base ? (size_t)((char*)(status + sort_status_words(pmax, true, false)) - c.base) : 0;
+        const size_t used = c.base ? (size_t)((char*)(status + sort_status_words(pmax, RadixCount::few, false)) - c.base) : 0;
         zero_bytes = c.base ? cvh::align_up(used) - z0 : 0;
         bytes = c.size();
     }
@@ -461,7 +466,7 @@ static cv_status grid_impl(const cv_records* sorted, const u64* soff, u32 S, con
     if (capacity > 0 &&
         (!out->key || !out->count || !out->n_journeys || !out->sum_speed || !out->min_speed || !out->max_speed))
         return CV_ERR_INVALID_ARGUMENT;
-    GridLayout L(ws, n);
+    GridLayout L(ws, n, nd > 0);
     Spec g;
     g.lat0 = grid->lat0_deg;
     g.lon0 = grid->lon0_deg;
@@ -534,7 +539,8 @@ static cv_status grid_impl(const cv_records* sorted, const u64* soff, u32 S, con
                            L.meta, L.lb1, mpasses, L.hist);
         // key sort of the pairs
         radix_passes(L.K0, L.K1, L.V0, L.V0, L.V1, pmax, &L.meta->compact_n, &L.meta->key_bits, mpasses, L.hist,
-                     L.status, L.meta->tickets, s);
+                     L.status, L.meta->tickets, s, /*timed=*/false, nullptr, nullptr,
+                     nd ? RadixCount::many : RadixCount::few);
         // groups: runs of equal keys, their rows
         hipLaunchKernelGGL(k_gpart_emit, dim3(L.eblocks), dim3(ECB), 0, s, L.meta, L.K0, L.K1, L.V0, L.V1, L.part,
                            L.lb2, (u32)capacity, out->key, out->count, out->n_journeys, out->sum_speed, out->min_speed,

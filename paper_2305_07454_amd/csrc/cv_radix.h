@@ -42,9 +42,12 @@ bool set_sort_shape(int i);
 int sort_tile(int i);
 int sort_block(int i);
 int sort_min_tile();
-// status words that a sort of at most n_max keys uses (counted: their number is
-// known on the device alone; wide: the first digit may have 9 bits)
-u64 sort_status_words(u64 n_max, bool counted, bool wide);
+// What the host knows of a sort's number of keys: the number, or a bound that the
+// number is mostly far below, or may come near.
+enum class RadixCount { exact, few, many };
+// status words that a sort of at most n_max keys uses (wide: the first digit may
+// have 9 bits)
+u64 sort_status_words(u64 n_max, RadixCount count, bool wide);
 // whether the selected shape has a 9-bit first-digit pass (512 threads or
 // more) and the tuning allows it
 bool sort_wide_first();
@@ -68,8 +71,10 @@ void radix_hist(const u64* keys, u32 n_max, const u32* n_dev, int passes, const 
 //                w0_dev [device] (nullable): bits of the first digit (8 or
 //                9; 9 only with p0 = 0), the word after pack's two; hist then
 //                use the wide layout and status holds 512 words per tile.
+//                count: what n_max says of the number at n_dev.
 void radix_passes(u64* k0, u64* k1, const u32* v_first, u32* v0, u32* v1, u32 n_max, const u32* n_dev,
                   const u32* bits_dev, int passes, const u32* hist, u64* status, u32* tickets, hipStream_t s,
-                  bool timed = false, const u32* pack = nullptr, const u32* w0_dev = nullptr);
+                  bool timed = false, const u32* pack = nullptr, const u32* w0_dev = nullptr,
+                  RadixCount count = RadixCount::few);
 
 }  // namespace cv

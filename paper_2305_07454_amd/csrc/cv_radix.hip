@@ -423,12 +423,13 @@ constexpr u64 DEVICE_COUNT_MAX_TILES = 1ull << 17;
 // (126, 128 us; 4 M 157, 211).  A count known on the device alone is mostly
 // far below its bound (the grid's partial rows: 2 M records 125 -> 110 us with the
 // emit, 4 M 154 -> 156 where a record in eight has a row of its own, 88 -> 75
-// where one in fifty has; 8 M 188 -> 243 and 92 -> 81).
+// where one in fifty has; 8 M 188 -> 243 and 92 -> 81), except where the caller says
+// that it may come near it (directions: a row for every two or three records).
 constexpr int ALL_B = 512;
 constexpr u64 ALL_GRID = 512;
-int all_items(u64 n_max, bool counted)  // keys per thread; 0: a launch per pass
+int all_items(u64 n_max, RadixCount count)  // keys per thread; 0: a launch per pass
 {
-    if (counted) return n_max <= (1u << 22) ? 8 : 0;
+    if (count != RadixCount::exact) return n_max <= (count == RadixCount::few ? 1u << 22 : 1u << 19) ? 8 : 0;
     return n_max <= (1u << 19) ? 8 : n_max <= (1u << 21) ? 16 : 0;
 }
 
@@ -470,9 +471,9 @@ bool set_sort_shape(int i)
 int sort_tile(int i) { return SHAPES[i].block * SHAPES[i].items; }
 int sort_block(int i) { return SHAPES[i].block; }
 bool sort_wide_first() { return g_wide_first && SHAPES[g_shape].block >= 2 * RADIX; }
-u64 sort_status_words(u64 n_max, bool counted, bool wide)
+u64 sort_status_words(u64 n_max, RadixCount count, bool wide)
 {
-    const int items = all_items(n_max, counted);
+    const int items = all_items(n_max, count);
     const u64 tile = items ? (u64)ALL_B * items : (u64)sort_tile(g_shape);
     const bool nine = wide && (items || SHAPES[g_shape].block >= 2 * RADIX);
     return (n_max + tile - 1) / tile * (nine ? 2 * RADIX : RADIX) + 1;
@@ -486,7 +487,7 @@ int sort_min_tile()
 
 void radix_passes(u64* k0, u64* k1, const u32* v_first, u32* v0, u32* v1, u32 n_max, const u32* n_dev,
                   const u32* bits_dev, int passes, const u32* hist, u64* status, u32* tickets, hipStream_t s,
-                  bool timed, const u32* pack, const u32* w0_dev)
+                  bool timed, const u32* pack, const u32* w0_dev, RadixCount count)
 {
     static const char* const names[MAX_PASSES] = {"sort_pass0", "sort_pass1", "sort_pass2", "sort_pass3",
                                                   "sort_pass4", "sort_pass5", "sort_pass6", "sort_pass7"};
@@ -494,7 +495,7 @@ void radix_passes(u64* k0, u64* k1, const u32* v_first, u32* v0, u32* v1, u32 n_
     const u64 tile = (u64)sort_tile(sh);
     // the kernels read the first digit's width with the packing words
     if (w0_dev && w0_dev != pack + 2) return;  // (the record sort keeps them adjacent)
-    if (const int items = all_items(n_max, n_dev != nullptr)) {
+    if (const int items = all_items(n_max, n_dev ? count : RadixCount::exact)) {
         cvh::TimedScope ts_(timed ? names[0] : nullptr, s);
         const u64 at = ((u64)n_max + ALL_B * items - 1) / (ALL_B * items);
         const dim3 grid((unsigned)(at < 1 ? 1 : at < ALL_GRID ? at : ALL_GRID));

@@ -1543,7 +1543,7 @@ struct SortLayout {
         zero_bytes = z1 - z0;
         if (c.base) {
             const size_t zu =
-                cvh::align_up((size_t)((char*)(status + sort_status_words(n, false, true)) - (char*)c.base));
+                cvh::align_up((size_t)((char*)(status + sort_status_words(n, RadixCount::exact, true)) - (char*)c.base));
             zero_bytes = (zu < z1 ? zu : z1) - z0;
         }
         K0 = c.take<u64>(n);
@@ -1576,7 +1576,7 @@ namespace {
 // stencil as the features kernel (cv_kin.h) on them, so that the sorted
 // columns are not read back from memory.  Record t0 + 64 g + l of the tile is
 // lane l of group g = u * 4 + wave (u = 0, 1): its predecessor is lane l - 1
-// of the same group (a lane shuffle), or for lane 0 the last lane of group
+// of the same group (a lane move), or for lane 0 the last lane of group
 // g - 1, which leaves it in a small LDS edge array.  Edge slot 0 holds record
 // t0 - 2 and slot 1 record t0 - 1 (the tile's predecessor, whose own step
 // thread 0 evaluates); group g's last record goes to slot g + 2.

@@ -54,3 +54,23 @@ def test_merge_of_partial_rows(cv, n, shape):
     assert r["count"] == len(exp["key"]) and r["n_out_of_grid"] == int((key < 0).sum())
     for k, e in exp.items():
         assert np.array_equal(host(got[k]).astype(e.dtype), e), k
+
+
+@pytest.mark.parametrize("n", [1, 2049, 100_001, (1 << 19) - 100, (1 << 19) + 1, 2_200_000])
+def test_merge_of_direction_rows(cv, n):
+    """Directions that change at every record: a row for nearly each, in few and
+    in many keys' sorts, chunks taken one to a block."""
+    import torch
+    print(f"[grid merge] directions n={n}", flush=True)
+    rng = np.random.default_rng(n)
+    jid = np.sort(rng.integers(0, max(1, n // 900) + 1, n))
+    grid = gen.GridSpec(36.0, -95.0, 1.0, 1.0, 1, 1 << 12, gen.T0_MS, 1000, 4)
+    cell, sector = rng.integers(0, 1 << 12, n), rng.integers(0, 8, n)
+    spd = rng.integers(0, 40, n).astype(np.float32)
+    cols = cv.to_device((jid, np.full(n, gen.T0_MS), np.full(n, 36.5), -94.5 + cell, spd))
+    head = torch.from_numpy((sector * 45 + 10).astype(np.float32)).cuda()
+    got, r = cv.cv_grid_aggregate_dir(cols, grid, 8, 0.0, heading=head)
+    exp = _numpy_groups(jid, sector * (1 << 12) + cell, spd)
+    assert r["count"] == len(exp["key"]) and r["n_out_of_grid"] == 0
+    for k, e in exp.items():
+        assert np.array_equal(host(got[k]).astype(e.dtype), e), k
