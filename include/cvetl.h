@@ -162,7 +162,8 @@ const char* cv_strerror(cv_status s);
  *   perm          [device, n] out: perm[k] = input index of the k-th record.
  *   sorted        [host struct, nullable] out columns; any member may be NULL.
  *   res           [device, nullable] out: status, count = distinct journeys,
- *                 key_bits = bits of the packed (journey rank, time) key;
+ *                 key_bits = bits of the packed (journey rank, time) key
+ *                 (also of input whose order needs no pass over it);
  *                 status CV_ERR_RANGE if that key would exceed 64 bits.
  *   ws, ws_bytes  workspace of at least cv_sort_workspace_size(n, max_journeys).
  * --------------------------------------------------------------------- */
@@ -226,10 +227,11 @@ cv_status cv_journey_summary(const cv_records* sorted, const cv_features* feat,
  * result, minus the workspace.  The workspace is a library-owned device array
  * of CV_NOALLOC_SCRATCH_BYTES bytes; each GPU the library runs on holds its
  * own copy until the process ends.  The call allocates nothing.
- *   Limit: cv_summary_workspace_size(n, capacity) must not exceed
- *   CV_NOALLOC_SCRATCH_BYTES (about 152 bytes per row of min(n, capacity)
- *   plus a few bytes per 4096 records: some 200 000 journey rows), else
- *   CV_ERR_WORKSPACE and nothing is enqueued.
+ *   Limit: the least workspace that cv_journey_summary accepts (about 152
+ *   bytes per row of min(n, capacity) plus a few bytes per 4096 records: some
+ *   200 000 journey rows; cv_summary_workspace_size asks for a few bytes more
+ *   per 512 or 1024 records of short inputs) must not exceed
+ *   CV_NOALLOC_SCRATCH_BYTES, else CV_ERR_WORKSPACE and nothing is enqueued.
  *   The stream must belong to the current device.  CV_ERR_DEVICE when the
  *   array's device address cannot be obtained.
  *   Every call on one GPU uses that GPU's single array, and each call
@@ -325,7 +327,8 @@ cv_status cv_gather_column(const void* in, const uint32_t* perm, void* out, uint
  *   0 when max == min); empty cells stay 0.  channel_min_max [device,
  *   2 C floats] receives each channel's min and max (NaN for a channel with
  *   no occupied cell).  A workspace of cv_lattice_normalize_workspace_size
- *   bytes (256-byte aligned) holds per-block partials.
+ *   bytes (256-byte aligned) holds the extrema per 4 096 cells and the
+ *   occupied cells' places.
  * cv_groups_filter -- index [device, uint32] of the groups, in ascending
  *   order, whose distinct journeys are >= min_volume and whose mean speed
  *   (sum_speed / count) lies in [speed_lo, speed_hi]; res->count = groups
@@ -544,7 +547,9 @@ cv_status cv_tuning_get(const char* name /*[host]*/, int64_t* value /*[host]*/);
  * and accumulates the elapsed time; cv_timing_read synchronises those events.
  * Families: "sort_prep", "sort_pass0" .. "sort_pass7" (one per radix digit
  * pass of the record sort; a pass whose digit lies above the packed key's
- * width exits at once on the device), "gather", "features", "summary",
+ * width exits at once on the device, every pass where the input is whole
+ * journeys in near order; the passes of few records run in one launch, counted
+ * as "sort_pass0"), "gather", "features", "summary",
  * "grid_agg", "grid_tail".
  * --------------------------------------------------------------------- */
 cv_status cv_timing_enable(int on);

@@ -801,7 +801,9 @@ struct StreamLayout {
         f("tab", c.take<GEntry>(gslots));
         f("ovf_pool", c.take<u64>(opages * OVF_SLOTS));
         // everything above persists across pushes; everything below is per-push or per-flush scratch
-        f("sort_ws", c.take<char>(sort_ws));
+        // the sort's, and after it the summary's (a few bytes per 512 records of the sort's 64 each)
+        const size_t sum_ws = cv::sum_partials_bytes(mb);
+        f("sort_ws", c.take<char>(sort_ws > sum_ws ? sort_ws : sum_ws));
         f("perm", c.take<u32>(mb));
         f("s_jid", c.take<i64>(mb));
         f("s_ts", c.take<i64>(mb));
@@ -818,7 +820,6 @@ struct StreamLayout {
         const u64 arows = acc_rows(jslots, mb);
         f("acc", c.take<cv::JAcc>(arows));
         f("accx", c.take<cv::AccX>(arows));
-        f("sum_ws", c.take<char>(cv::sum_partials_bytes(mb)));
         f("ap", c.take<Append>(mb));
         const u64 gst = (gslots + sort_min_tile() - 1) / sort_min_tile();
         const u64 jst = (jslots + 1 + sort_min_tile() - 1) / sort_min_tile();
@@ -956,6 +957,7 @@ cv_status cv_stream_create(const cv_grid_spec* grid, uint64_t max_journeys, uint
         else if (nm == "ovf_pool") st->ovf_pool = (u64*)p;
         else if (nm == "sort_ws") {
             st->sort_ws = p;
+            st->sum_ws = p;
             st->resident_bytes = (size_t)((char*)p - (char*)state);
         }
         else if (nm == "perm") st->perm = (u32*)p;
@@ -973,7 +975,6 @@ cv_status cv_stream_create(const cv_grid_spec* grid, uint64_t max_journeys, uint
         else if (nm == "sres") st->sres = (cv_result*)p;
         else if (nm == "acc") st->acc = (cv::JAcc*)p;
         else if (nm == "accx") st->accx = (cv::AccX*)p;
-        else if (nm == "sum_ws") st->sum_ws = p;
         else if (nm == "ap") st->ap = (Append*)p;
         else if (nm == "gK0") st->gK0 = (u64*)p;
         else if (nm == "gK1") st->gK1 = (u64*)p;
