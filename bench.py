@@ -10,8 +10,8 @@ The default run measures, in one JSON line:
     (50 000 journeys, lognormal lengths with median 1 500 points, 5 %
     duplicated and 2 % swapped timestamps, 0.005 deg x 5 min grid), about
     124 M records -- Mrecords/s (median of per-step HIP events), the roofline
-    of the dominant kernel (radix scatter pass) measured with HIP events on its
-    launch stream, the whole path's algorithmic bytes over the step time, and
+    of the dominant kernel (the gather with the kinematics; the radix scatter
+    pass where the input needs one) measured with HIP events on its launch stream, the whole path's algorithmic bytes over the step time, and
     the CPU oracle timed on a bounded sample of the same workload;
   * "batched": 115 county-day shards of capped Zipf sizes (400 M records,
     0.001 deg x 1 min) in one set of launches, against the plain path called
@@ -466,10 +466,10 @@ def bench_plain(args, workload):
         lattice["csv_extract"] = bench_csv(r, dev)
 
     traffic = None
-    tfile = os.path.join(ROOT, "profiles", "radix_pass_c1_traffic.md")
-    if sorts and workload == "c1" and args.n_journeys is None and os.path.exists(tfile):
+    tfile = os.path.join(ROOT, "profiles", "gather_c1_traffic.md")
+    if not sorts and workload == "c1" and args.n_journeys is None and os.path.exists(tfile):
         t = read_traffic(tfile)
-        if t.get("kernel_source_sha") == _kernel_sha() and t.get("sort_shape") == str(cvetl.cv_tuning_get("sort_shape")):
+        if t.get("kernel_source_sha") == _kernel_sha():
             traffic = float(t["traffic_bytes_per_launch"])
 
     del pipe, rec
@@ -814,7 +814,7 @@ def pass_bytes(p, p0):
 
 
 def read_traffic(path):
-    """`key: value` lines of a traffic summary (HBM bytes per radix pass launch
+    """`key: value` lines of a traffic summary (HBM bytes per launch of the gather
     from the FETCH_SIZE / WRITE_SIZE counters, scaled by a copy of known size)."""
     out = {}
     for line in open(path):
@@ -827,7 +827,7 @@ def read_traffic(path):
 def _kernel_sha():
     import hashlib
     h = hashlib.sha256()
-    for f in ("cv_radix.h", "cv_radix.hip", "cv_device.h"):
+    for f in ("cv_sort.hip", "cv_kin.h", "cv_device.h"):
         with open(os.path.join(ROOT, "paper_2305_07454_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]
