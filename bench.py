@@ -11,8 +11,9 @@ The default run measures, in one JSON line:
     duplicated and 2 % swapped timestamps, 0.005 deg x 5 min grid), about
     124 M records -- Mrecords/s (median of per-step HIP events), the roofline
     of the dominant kernel (the gather with the kinematics; the radix scatter
-    pass where the input needs one) measured with HIP events on its launch stream, the whole path's algorithmic bytes over the step time, and
-    the CPU oracle timed on a bounded sample of the same workload;
+    pass where the input needs one) measured with HIP events on its launch
+    stream, the whole path's algorithmic bytes over the step time, and the CPU
+    oracle timed on a bounded sample of the same workload;
   * "batched": 115 county-day shards of capped Zipf sizes (400 M records,
     0.001 deg x 1 min) in one set of launches, against the plain path called
     per shard on the same resident input, with every shard's outputs compared;

@@ -379,9 +379,9 @@ __global__ void __launch_bounds__(256) k_dict_insert(const i64* __restrict__ jid
     i64 prevj = 0;  // last id of the previous window
     bool hp = false;
     // (plain form) the window before: time stamps, run starts, whether a time
-    // stamp falls in it; far: the input is not grouped (wave-uniform)
+    // stamp falls in it, inversions at 2 and 3; far: the input is not grouped (wave-uniform)
     u32 pt = 0;
-    u64 ph_ = 0, pdown = ~0ull, far = 0;
+    u64 ph_ = 0, pdown = ~0ull, pnear = ~0ull, far = 0;
     if (!SHARDS && wbeg < wend && wbeg > 0) {
         const u64 i = (wbeg - 1) * WAVE + l;
         const i64 j = jid[i];
@@ -470,15 +470,17 @@ __global__ void __launch_bounds__(256) k_dict_insert(const i64* __restrict__ jid
             runs += (u32)__popcll(heads[k]);
             if (!SHARDS && !far) {
                 // near order (JW): inversions at JW + 1 to 2 JW + 1, where a time
-                // stamp falls at all; none where there are none at 2 and 3 (the
-                // same rule with 1 for JW), as with rows that changed places
+                // stamp falls at all; none where there are none at 2 and 3, as
+                // with rows that changed places.  (Of records j < i in an inversion
+                // at 4 or more, the record 2 after j is in one with i, nearer, or
+                // with j, at 2: in this window, or among the last of the one before.)
                 const u32 x = (u32)tv[k];
                 const u64 vm = __ballot(valid);
                 far |= __ballot(dup && tv[k] - tq + JW_GAP >= 2 * JW_GAP) & vm;
                 const u64 falls = __ballot(tv[k] < tq) & ~heads[k] & vm;
+                u64 near = 0;
                 if (falls | pdown) {
                     RunMask rm(heads[k], ph_);
-                    u64 near = 0;
                     u32 y = x;
 #pragma unroll
                     for (int d = 1; d <= 3; ++d) {
@@ -486,7 +488,7 @@ __global__ void __launch_bounds__(256) k_dict_insert(const i64* __restrict__ jid
                         const u64 in = rm.next() & vm;
                         if (d > 1) near |= __ballot((int)(x - y) < 0) & in;
                     }
-                    if (near) {
+                    if (near | pnear) {
 #pragma unroll
                         for (int d = 4; d <= 2 * JW + 1; ++d) {
                             y = lane_below(y, (u32)__builtin_amdgcn_readlane((int)pt, WAVE - d));
@@ -497,6 +499,7 @@ __global__ void __launch_bounds__(256) k_dict_insert(const i64* __restrict__ jid
                 }
                 if (__popcll(heads[k]) > JW_HEADS) far = 1;
                 pdown = falls >> (WAVE - 2 * JW - 1);  // (those that the next window's pairs can span)
+                pnear = near >> (WAVE - 2 * JW - 1);
                 pt = x;
                 ph_ = heads[k];
             }

@@ -152,3 +152,28 @@ def test_many_journeys(cv, ids, max_journeys):
     order[a], order[a + 1] = a + 1, a
     names[ids // 2] = -2 ** 63
     _check(cv, names[run[order]], ts[order], max_journeys=max_journeys)
+
+
+@pytest.mark.parametrize("far", [2, 3, 4, 5, 6, 7, 8, 12])
+@pytest.mark.parametrize("back", [False, True])
+def test_one_record_out_of_place(cv, far, back):
+    # a single record out of its place, at every lane of a window and across the
+    # edge of the next, with the records around it in every close order
+    print(f"[grouped] one record moved by {far} back={back}", flush=True)
+    n = 600
+    rng = np.random.default_rng(far)
+    ts0 = gen.T0_MS + 1000 * np.arange(n)
+    for at in range(380, 380 + 130):
+        for near in (False, True):
+            order = np.arange(n)
+            block = list(order[at:at + far + 1])
+            order[at:at + far + 1] = block[-1:] + block[:-1] if back else block[1:] + block[:1]
+            if near:  # neighbours changed places around it
+                for i in (at + 1, at + far - 2, at + far + 2):
+                    if rng.random() < 0.5:
+                        order[i], order[i + 1] = order[i + 1], order[i]
+            ts = ts0[order]
+            jid = (np.arange(n) >= 300).astype(np.int64) * 7
+            cols = (jid, ts, np.full(n, 37.0), np.full(n, -92.0), np.zeros(n, np.float32))
+            perm = cv.cv_sort_records(cv.to_device(cols), max_journeys=4)[0]
+            assert np.array_equal(perm.cpu().numpy().astype(np.int64), np.lexsort((ts, jid))), (at, near)
