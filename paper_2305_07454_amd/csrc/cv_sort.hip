@@ -1391,7 +1391,11 @@ __global__ void __launch_bounds__(256) k_gather(u32 n, const SortMeta* m, const 
             wv[u] = K[k < n ? k : n - 1];  // past the end: a valid word, not stored
         }
 #pragma unroll
-        for (int u = 0; u < GU; ++u) vv[u] = (u32)(wv[u] & imask);
+        for (int u = 0; u < GU; ++u) {
+            // (input that changes under the call may leave a word of grouped input unwritten)
+            const u32 v = (u32)(wv[u] & imask);
+            vv[u] = v < n ? v : n - 1;
+        }
         if constexpr (FULL) {
             // every column requested: all gathers issued before the first store
             double ola[GU], olo[GU];
@@ -1637,7 +1641,11 @@ __global__ void __launch_bounds__(256) k_gather_feat(u32 n, const SortMeta* m, c
         wv[u] = K[k];
     }
 #pragma unroll
-    for (int u = 0; u < NS; ++u) vv[u] = (u32)(wv[u] & imask);
+    for (int u = 0; u < NS; ++u) {
+        // (input that changes under the call may leave a word of grouped input unwritten)
+        const u32 v = (u32)(wv[u] & imask);
+        vv[u] = v < n ? v : n - 1;
+    }
     double ola[NS], olo[NS];
     float osp[NS];
     i64 oj[NS], ot[NS];
