@@ -51,11 +51,11 @@ __device__ __forceinline__ uint4 load16(const unsigned char* __restrict__ text, 
     return make_uint4(v[0], v[1], v[2], v[3]);
 }
 
-// Newlines per group of CG tiles, and per tile as 16 bits of a word (one block
-// scans the groups, and what one CU can read is what bounds that: 18 000 tiles
-// one by one took 18 us, in groups 6; a short text's few tiles are counted each
-// by a block of its own, 5 us less at 2.7 MB); block 0 also clears the result
-// (the parse adds the malformed rows to it and sets the rest).
+// Newlines per group of CG tiles, and in a group of several per tile as 16 bits
+// of a word (one block scans the groups, and what one CU can read is what bounds
+// that: 18 000 tiles one by one took 18 us, in groups 6; a short text's few tiles
+// are counted each by a block of its own, 5 us less at 2.7 MB); block 0 also
+// clears the result (the parse adds the malformed rows to it and sets the rest).
 template <int CG>
 __global__ void __launch_bounds__(CB) k_csv_count(const unsigned char* __restrict__ text, u64 nbytes,
                                                   u32* __restrict__ gcnt, u64* __restrict__ sub, cv_result* res)
@@ -91,7 +91,7 @@ __global__ void __launch_bounds__(CB) k_csv_count(const unsigned char* __restric
     if (threadIdx.x == 0) {
         u64 t = 0;
         for (int w = 0; w < CB / WAVE; ++w) t += s_w[w];
-        sub[blockIdx.x] = t;
+        if (CG > 1) sub[blockIdx.x] = t;
         gcnt[blockIdx.x] = (u32)((t & 0xFFFF) + ((t >> 16) & 0xFFFF) + ((t >> 32) & 0xFFFF) + (t >> 48));
     }
 }
@@ -465,7 +465,7 @@ __global__ void __launch_bounds__(CB) k_csv_parse(const unsigned char* __restric
         for (u32 i = tid; i < grp; i += CB) v += gcnt[i];
         block_exclusive_sum<CB>(v, s_tmp, base);
     }
-    {
+    if (CG > 1) {
         u64 t = sub[grp];
         for (u32 k = blockIdx.x % CG; k > 0; --k, t >>= 16) base += (u32)(t & 0xFFFF);
     }
@@ -599,6 +599,27 @@ __global__ void __launch_bounds__(CB) k_csv_parse(const unsigned char* __restric
     if (lane_id() == 0 && bad) atomicAdd((unsigned long long*)&res->n_bad, (unsigned long long)bad);
 }
 
+// The call's scratch: the groups' newline counts and, where a group has several
+// tiles, the counts of its tiles.  At most 4 bytes per tile and the alignment,
+// whatever the capacity.
+struct CsvLayout {
+    u64 tiles, groups;
+    u32 cg;  // tiles per group
+    u64* sub;
+    u32* gcnt;
+    size_t bytes;
+    CsvLayout(void* ws, u64 nbytes)
+    {
+        cvh::Carver c(ws);
+        tiles = (nbytes + CT - 1) / CT;
+        cg = tiles > CSV_SELF ? CG_L : 1;
+        groups = (tiles + cg - 1) / cg;
+        sub = c.take<u64>(cg > 1 ? groups : 0);
+        gcnt = c.take<u32>(groups ? groups : 1);
+        bytes = c.size();
+    }
+};
+
 }  // namespace
 
 extern "C" {
@@ -606,10 +627,9 @@ extern "C" {
 cv_status cv_csv_workspace_size(uint64_t nbytes, uint64_t capacity, size_t* bytes)
 {
     if (!bytes || capacity >= (1ull << 32)) return CV_ERR_INVALID_ARGUMENT;
-    const u64 tiles = (nbytes + CT - 1) / CT;
-    if (tiles >= (1ull << 31)) return CV_ERR_INVALID_ARGUMENT;
-    *bytes = cvh::align_up((tiles + 1) * sizeof(u32)) + cvh::align_up((capacity + 3) * sizeof(u64)) +
-             cvh::align_up(2 * sizeof(u64));
+    const CsvLayout L(nullptr, nbytes);
+    if (L.tiles >= (1ull << 31)) return CV_ERR_INVALID_ARGUMENT;
+    *bytes = L.bytes;
     return CV_OK;
 }
 
@@ -627,20 +647,15 @@ cv_status cv_csv_extract(const char* text, uint64_t nbytes, int32_t has_header, 
     if (!ws || !cvh::aligned(ws, cvh::WS_ALIGN) || ws_bytes < need) return CV_ERR_WORKSPACE;
     hipStream_t s = (hipStream_t)stream;
     cvh::TimedScope ts_("csv_extract", s);
-    const u64 tiles = (nbytes + CT - 1) / CT;
-    cvh::Carver c(ws);
-    const bool summed = tiles > CSV_SELF;
-    const u32 cg = summed ? CG_L : 1;
-    const u64 groups = (tiles + cg - 1) / cg;
-    u64* sub = c.take<u64>(groups);
-    u32* gcnt = c.take<u32>(groups);
+    const CsvLayout L(ws, nbytes);
+    const bool summed = L.cg > 1;
     const unsigned char* t = (const unsigned char*)text;
-    hipLaunchKernelGGL(summed ? k_csv_count<CG_L> : k_csv_count<1>, dim3((unsigned)(groups ? groups : 1)), dim3(CB), 0, s,
-                       t, (u64)nbytes, gcnt, sub, res);
-    if (!tiles) return cvh::last_launch_status();
-    if (summed) hipLaunchKernelGGL(k_csv_scan, dim3(1), dim3(1024), 0, s, gcnt, groups);
-    hipLaunchKernelGGL(k_csv_parse, dim3((unsigned)tiles), dim3(CB), 0, s, t, (u64)nbytes, gcnt, sub, (u32)tiles, cg,
-                       summed ? 1 : 0, has_header ? 1 : 0, *out, heading_deg, row_ok, (u64)capacity, res);
+    hipLaunchKernelGGL(summed ? k_csv_count<CG_L> : k_csv_count<1>, dim3((unsigned)(L.groups ? L.groups : 1)), dim3(CB), 0,
+                       s, t, (u64)nbytes, L.gcnt, L.sub, res);
+    if (!L.tiles) return cvh::last_launch_status();
+    if (summed) hipLaunchKernelGGL(k_csv_scan, dim3(1), dim3(1024), 0, s, L.gcnt, L.groups);
+    hipLaunchKernelGGL(k_csv_parse, dim3((unsigned)L.tiles), dim3(CB), 0, s, t, (u64)nbytes, L.gcnt, L.sub, (u32)L.tiles,
+                       L.cg, summed ? 1 : 0, has_header ? 1 : 0, *out, heading_deg, row_ok, (u64)capacity, res);
     return cvh::last_launch_status();
 }
 
