@@ -98,7 +98,7 @@ struct GridLayout {
         // last in the cleared range: a call clears what its tile shape uses
         status = c.take<u64>(stiles * RADIX + 1);
         zero_begin = (u32*)(c.base ? c.base + z0 : nullptr);
-        const size_t used = c.base ? (size_t)((char*)(status + sort_status_words(pmax, RadixCount::few, false)) - c.base) : 0;
+        const size_t used = c.base ? (size_t)((char*)(status + sort_status_words(pmax, RadixCount::rows, false)) - c.base) : 0;
         zero_bytes = c.base ? cvh::align_up(used) - z0 : 0;
         bytes = c.size();
     }
@@ -540,7 +540,7 @@ static cv_status grid_impl(const cv_records* sorted, const u64* soff, u32 S, con
         // key sort of the pairs
         radix_passes(L.K0, L.K1, L.V0, L.V0, L.V1, pmax, &L.meta->compact_n, &L.meta->key_bits, mpasses, L.hist,
                      L.status, L.meta->tickets, s, /*timed=*/false, nullptr, nullptr,
-                     nd ? RadixCount::many : RadixCount::few);
+                     nd ? RadixCount::many : RadixCount::rows);
         // groups: runs of equal keys, their rows
         hipLaunchKernelGGL(k_gpart_emit, dim3(L.eblocks), dim3(ECB), 0, s, L.meta, L.K0, L.K1, L.V0, L.V1, L.part,
                            L.lb2, (u32)capacity, out->key, out->count, out->n_journeys, out->sum_speed, out->min_speed,

@@ -43,8 +43,8 @@ int sort_tile(int i);
 int sort_block(int i);
 int sort_min_tile();
 // What the host knows of a sort's number of keys: the number, or a bound that the
-// number is mostly far below, or may come near.
-enum class RadixCount { exact, few, many };
+// number is nearly always far below, mostly is, or may well come near.
+enum class RadixCount { exact, few, rows, many };
 // status words that a sort of at most n_max keys uses (wide: the first digit may
 // have 9 bits)
 u64 sort_status_words(u64 n_max, RadixCount count, bool wide);

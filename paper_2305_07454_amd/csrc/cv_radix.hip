@@ -420,16 +420,23 @@ constexpr u64 DEVICE_COUNT_MAX_TILES = 1ull << 17;
 // 49 us; 30 000: 46 -> 26), of 512 x 16 above (1 M, four passes: 108 -> 82; 2 M, two:
 // 88 -> 59).  A pass between others writes its words through, some 8-byte runs
 // at a time, and at 2 M keys and four passes that takes what the launches saved
-// (126, 128 us; 4 M 157, 211).  A count known on the device alone is mostly
-// far below its bound (the grid's partial rows: 2 M records 125 -> 110 us with the
-// emit, 4 M 154 -> 156 where a record in eight has a row of its own, 88 -> 75
-// where one in fifty has; 8 M 188 -> 243 and 92 -> 81), except where the caller says
-// that it may come near it (directions: a row for every two or three records).
+// (126, 128 us; 4 M 157, 211).  A count known on the device alone may be far below
+// its bound or come near it, and its line lies where one launch costs the second
+// no more than it saves the first:
+//   few   distinct ids, a flush's rows: 2 M ids allowed, a few thousand there, sort of
+//         the records 260 us in one launch and 270 in launches per pass; all there
+//         999 and 843; 4 M allowed and there 1821 and 1444;
+//   rows  the grid's partial rows (merge of 0.001 deg x 1 min): 1 M records, one in
+//         fifty with a row of its own, 72 and 90; every one 201 and 172; 2 M 77 and
+//         95, 412 and 237;
+//   many  the same with directions: a row for every two or three records.
 constexpr int ALL_B = 512;
 constexpr u64 ALL_GRID = 512;
 int all_items(u64 n_max, RadixCount count)  // keys per thread; 0: a launch per pass
 {
-    if (count != RadixCount::exact) return n_max <= (count == RadixCount::few ? 1u << 22 : 1u << 19) ? 8 : 0;
+    if (count == RadixCount::few) return n_max <= (1u << 21) ? 8 : 0;
+    if (count == RadixCount::rows) return n_max <= (1u << 20) ? 8 : 0;
+    if (count == RadixCount::many) return n_max <= (1u << 19) ? 8 : 0;
     return n_max <= (1u << 19) ? 8 : n_max <= (1u << 21) ? 16 : 0;
 }
 
