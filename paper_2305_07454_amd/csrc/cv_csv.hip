@@ -10,9 +10,9 @@
 //                 starts in the tile
 //
 // A row's fields come from the bits (six commas, no quote) and are converted
-// eight characters at a time; a row of another shape, or one that runs past
-// the staged bytes, goes through the byte-wise parser, which alone says what is
-// malformed.  Bound by vector instructions and, in the count, by HBM: 4 M rows,
+// eight characters at a time; what has another form goes through the byte-wise
+// parsers, which alone say what is malformed.  A row that runs past the staged
+// bytes (a tile's last one) is read by the whole block.  Bound by vector instructions and, in the count, by HBM: 4 M rows,
 // 292 MB, take 63 us to count and 172 to parse; reading the text a third time
 // for the row starts and finding the commas byte by byte in each row's thread
 // took 537, 404 of them the parse.
@@ -220,45 +220,29 @@ struct Row {
     bool ok;
 };
 
-// The fields of one row of rl bytes at s (its line end included).  Inlined
-// into each caller, so that a row staged in LDS is read with LDS loads.
-__device__ __forceinline__ Row parse_row(const unsigned char* s, u64 rl)
+__device__ __forceinline__ Row malformed()
 {
     Row w;
-    if (rl && s[rl - 1] == '\n') --rl;
-    if (rl && s[rl - 1] == '\r') --rl;
-    const int len = (int)(rl < (u64)(1 << 20) ? rl : (u64)(1 << 20));
-    // field boundaries: exactly six commas
-    int cpos[6];
-    int nc = 0;
-    bool ok = rl < (u64)(1 << 20);
-    for (int i = 0; i < len && ok; ++i) {
-        if (s[i] == ',') {
-            if (nc < 6) cpos[nc] = i;
-            ++nc;
-        } else if (s[i] == '"') {
-            ok = false;
-        }
-    }
-    ok = ok && nc == 6;
     w.jid = 0;
     w.ts = 0;
     w.lat = w.lon = w.spd = w.hdg = __builtin_nan("");
-    if (ok) {
-        ok = parse_id(s, cpos[0], w.jid) && parse_ts(s + cpos[0] + 1, cpos[1] - cpos[0] - 1, w.ts) &&
-             parse_decimal(s + cpos[1] + 1, cpos[2] - cpos[1] - 1, w.lat) &&
-             parse_decimal(s + cpos[2] + 1, cpos[3] - cpos[2] - 1, w.lon) &&
-             parse_decimal(s + cpos[4] + 1, cpos[5] - cpos[4] - 1, w.spd);
-        const int hl = len - cpos[5] - 1;
-        if (ok && hl > 0 && !parse_decimal(s + cpos[5] + 1, hl, w.hdg)) ok = false;
-    }
-    if (!ok) {
-        w.jid = 0;
-        w.ts = 0;
-        w.lat = w.lon = w.spd = w.hdg = __builtin_nan("");
-    }
-    w.ok = ok;
+    w.ok = false;
     return w;
+}
+
+// The fields of a row of len bytes at s (no line end, no quote) whose six commas
+// lie at cpos.  Inlined into each caller, so that a row staged in LDS is read with
+// LDS loads.
+__device__ __forceinline__ Row parse_fields(const unsigned char* s, const u32* cpos, u32 len)
+{
+    Row w = malformed();
+    const u32 hl = len - cpos[5] - 1;
+    w.ok = parse_id(s, (int)cpos[0], w.jid) && parse_ts(s + cpos[0] + 1, (int)(cpos[1] - cpos[0] - 1), w.ts) &&
+           parse_decimal(s + cpos[1] + 1, (int)(cpos[2] - cpos[1] - 1), w.lat) &&
+           parse_decimal(s + cpos[2] + 1, (int)(cpos[3] - cpos[2] - 1), w.lon) &&
+           parse_decimal(s + cpos[4] + 1, (int)(cpos[5] - cpos[4] - 1), w.spd) &&
+           (hl == 0 || parse_decimal(s + cpos[5] + 1, (int)hl, w.hdg));
+    return w.ok ? w : malformed();
 }
 
 // ------------------------------------------------------------------ fields,
@@ -381,6 +365,67 @@ __device__ __forceinline__ u64 bits_from(const u64* m, u32 p)
     return b ? (m[p >> 6] >> b) | (m[(p >> 6) + 1] << (64 - b)) : m[p >> 6];
 }
 
+// newlines, commas and quotes among 16 bytes, a bit each
+__device__ __forceinline__ void byte_marks(uint4 v, u32& nl, u32& cm, u32& qt)
+{
+    const u32 x[4] = {v.x, v.y, v.z, v.w};
+    nl = cm = qt = 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        nl |= pack_bytes(eq_bytes(x[k], 0x0A0A0A0Au)) << (4 * k);
+        cm |= pack_bytes(eq_bytes(x[k], 0x2C2C2C2Cu)) << (4 * k);
+        qt |= pack_bytes(eq_bytes(x[k], 0x22222222u)) << (4 * k);
+    }
+}
+
+constexpr u64 ROW_MAX = 1ull << 20;  // a row of so many bytes, its line end not counted, is malformed
+
+// A row that starts at byte b of the text and ends past the staged bytes, by the
+// whole block (all threads; the row in thread 0): 4 096 bytes a step until its end,
+// or until a seventh comma, a quote or ROW_MAX bytes have made it malformed whatever
+// follows.  60 000 rows of 3 KB take 0.26 ms, 2 500 of 40 KB 0.11; one thread
+// going through such a row byte by byte took 7.07 and 18.8, and many seconds where the
+// line breaks are missing.
+__device__ __forceinline__ Row long_row(const unsigned char* __restrict__ text, u64 nbytes, u64 b, u32* s_tmp)
+{
+    __shared__ u32 s_first, s_cp[6];
+    const u32 at = 16 * threadIdx.x;
+    u32 nc = 0;
+    bool quote = false, ended = false;
+    u64 end = nbytes;
+    for (u64 q = b & ~15ull;; q += 16 * CB) {
+        if (threadIdx.x == 0) s_first = ~0u;
+        u32 nl, cm, qt;
+        byte_marks(load16(text, q + at, nbytes), nl, cm, qt);
+        if (q + at < b) {
+            const u32 from = 0xFFFFu << (u32)(b - q);  // (thread 0 of the first step)
+            nl &= from;
+            cm &= from;
+            qt &= from;
+        }
+        __syncthreads();
+        if (nl) atomicMin(&s_first, at + (u32)__ffs((int)nl) - 1);
+        __syncthreads();
+        const u32 first = s_first;
+        const u32 upto = first <= at ? 0u : (first - at < 16 ? (1u << (first - at)) - 1 : 0xFFFFu);
+        cm &= upto;
+        qt &= upto;
+        u32 tot;
+        u32 c = nc + (block_exclusive_sum<CB>((u32)__popc(cm) | (qt ? 1u << 16 : 0u), s_tmp, tot) & 0xFFFFu);
+        for (; cm && c < 6; ++c, cm &= cm - 1) s_cp[c] = (u32)(q + at - b) + (u32)__ffs((int)cm) - 1;
+        nc += tot & 0xFFFFu;
+        quote |= (tot >> 16) != 0;
+        const u64 next = q + 16 * CB;
+        ended = first != ~0u || next >= nbytes;
+        if (first != ~0u) end = q + first;
+        if (ended || quote || nc > 6 || next - b >= ROW_MAX + 2) break;
+    }
+    __syncthreads();
+    if (threadIdx.x != 0 || !ended || quote || nc != 6) return malformed();
+    if (end > b && text[end - 1] == '\r') --end;
+    return end - b < ROW_MAX ? parse_fields(text + b, s_cp, (u32)(end - b)) : malformed();
+}
+
 // The rows that start in the block's tile (line r starts at byte 0 or after
 // newline r - 1; base: newlines before the tile), one per thread and round;
 // header lines are skipped, rows past cap counted only.  The block of the last
@@ -402,6 +447,8 @@ __global__ void __launch_bounds__(CB) k_csv_parse(const unsigned char* __restric
     __shared__ uint16_t s_row[CROWS];
     __shared__ u32 s_tmp[CB / WAVE];
     __shared__ Pow10 s_p;
+    __shared__ u32 s_long;  // the tile's row whose end is not staged (its last; ~0: none)
+    __shared__ u64 s_long_row;
     const int tid = threadIdx.x;
     const u64 t0 = (u64)blockIdx.x * CT;
     const u64 left = nbytes - t0;
@@ -426,18 +473,13 @@ __global__ void __launch_bounds__(CB) k_csv_parse(const unsigned char* __restric
         const u32 c = r < Q ? (u32)(r * CB + tid) : hc;
         const uint4 v = tv[r];
         *reinterpret_cast<uint4*>(&s_txt[CFRONT / 4 + 4 * c]) = v;
-        const u32 x[4] = {v.x, v.y, v.z, v.w};
-        u32 nl = 0, cm = 0, qt = 0;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            nl |= pack_bytes(eq_bytes(x[k], 0x0A0A0A0Au)) << (4 * k);
-            cm |= pack_bytes(eq_bytes(x[k], 0x2C2C2C2Cu)) << (4 * k);
-            qt |= pack_bytes(eq_bytes(x[k], 0x22222222u)) << (4 * k);
-        }
+        u32 nl, cm, qt;
+        byte_marks(v, nl, cm, qt);
         s_nl[c] = (uint16_t)nl;
         s_cm[c] = (uint16_t)cm;
         s_qt[c] = (uint16_t)qt;
     }
+    if (tid == 0) s_long = ~0u;
     if (tid < 12) {
         s_cm[CST / 16 + tid] = 0;
         s_qt[CST / 16 + tid] = 0;
@@ -505,6 +547,16 @@ __global__ void __launch_bounds__(CB) k_csv_parse(const unsigned char* __restric
         }
     }
     u32 bad = 0;
+    auto put = [&](u64 row, const Row& w) {
+        bad += w.ok ? 0u : 1u;
+        o.journey_id[row] = w.jid;
+        o.ts_ms[row] = w.ts;
+        o.lat_deg[row] = w.lat;
+        o.lon_deg[row] = w.lon;
+        o.speed_mps[row] = (float)w.spd;
+        if (heading) heading[row] = (float)w.hdg;
+        if (row_ok) row_ok[row] = w.ok ? 1 : 0;
+    };
     for (u32 r0 = 0; r0 < R; r0 += CROWS) {
         // starts of rows [r0, r0 + CROWS)
         if (first && r0 == 0 && tid == 0) s_row[0] = 0;
@@ -532,67 +584,71 @@ __global__ void __launch_bounds__(CB) k_csv_parse(const unsigned char* __restric
             u32 wi = a >> 6;
             u64 x = nlw[wi] & (~0ull << (a & 63));
             while (!x && wi + 1 < (u32)CSW) x = nlw[++wi];
-            Row w;
-            bool done = false;
-            u32 e = 0;
-            const bool whole = x || t0 + CST >= nbytes;  // the row's end is staged
-            if (whole) {
-                e = x ? (wi << 6) + (u32)__ffsll((long long)x) - 1 : avail;
-                u32 z = e;
-                if (z > a && ((ld4(s_txt, CFRONT + z - 1) & 0xFFu) == '\r')) --z;
-                const u32 len = z - a;
-                if (len <= 128 && len > 0) {
-                    const u64 in0 = len >= 64 ? ~0ull : (1ull << len) - 1;
-                    const u64 in1 = len > 64 ? (len == 128 ? ~0ull : (1ull << (len - 64)) - 1) : 0ull;
-                    u64 lo = bits_from(cmw, a) & in0, hi = bits_from(cmw, a + 64) & in1;
-                    const bool quote = ((bits_from(qtw, a) & in0) | (bits_from(qtw, a + 64) & in1)) != 0;
-                    if (__popcll(lo) + __popcll(hi) == 6 && !quote) {
-                        u32 cp[6];
+            if (!x && t0 + CST < nbytes) {  // the row's end is not staged
+                s_long = a;
+                s_long_row = row;
+                continue;
+            }
+            u32 z = x ? (wi << 6) + (u32)__ffsll((long long)x) - 1 : avail;
+            if (z > a && ((ld4(s_txt, CFRONT + z - 1) & 0xFFu) == '\r')) --z;
+            const u32 len = z - a;
+            // the row's commas, and whether it has the shape: six of them, no quote
+            u32 cp[6];
+            bool shape;
+            if (len <= 128) {
+                const u64 in0 = len >= 64 ? ~0ull : (1ull << len) - 1;
+                const u64 in1 = len > 64 ? (len == 128 ? ~0ull : (1ull << (len - 64)) - 1) : 0ull;
+                u64 lo = bits_from(cmw, a) & in0, hi = bits_from(cmw, a + 64) & in1;
+                shape = ((bits_from(qtw, a) & in0) | (bits_from(qtw, a + 64) & in1)) == 0 &&
+                        __popcll(lo) + __popcll(hi) == 6;
 #pragma unroll
-                        for (int q = 0; q < 6; ++q) {
-                            const bool l = lo != 0;
-                            const u64 y = l ? lo : hi;
-                            cp[q] = CFRONT + a + (l ? 0u : 64u) + (u32)__ffsll((long long)y) - 1u;
-                            if (l) lo &= lo - 1;
-                            else hi &= hi - 1;
-                        }
-                        const u32 p0 = CFRONT + a, pe = CFRONT + z;
-                        const u32 idn = cp[0] - p0;
-                        // the id's bytes, first one highest
-                        const u64 raw = (u64)ld4(s_txt, p0) | ((u64)ld4(s_txt, p0 + 4) << 32);
-                        const u64 id = __builtin_bswap64(raw) & (idn >= 1 && idn < 8 ? ~0ull << (64 - 8 * idn) : ~0ull);
-                        w.jid = (i64)id;
-                        done = idn >= 1 && idn <= 8 && (id >> 63) == 0;
-                        done = quick_ts(s_txt, cp[0] + 1, cp[1], w.ts) && done;
-                        done = quick_decimal(s_txt, s_p, cp[1] + 1, cp[2], w.lat) && done;
-                        done = quick_decimal(s_txt, s_p, cp[2] + 1, cp[3], w.lon) && done;
-                        done = quick_decimal(s_txt, s_p, cp[4] + 1, cp[5], w.spd) && done;
-                        w.hdg = __builtin_nan("");
-                        if (cp[5] + 1 < pe) done = quick_decimal(s_txt, s_p, cp[5] + 1, pe, w.hdg) && done;
-                        w.ok = true;
+                for (int q = 0; q < 6; ++q) {
+                    const bool l = lo != 0;
+                    const u64 y = l ? lo : hi;
+                    cp[q] = (l ? 0u : 64u) + (u32)__ffsll((long long)y) - 1u;
+                    if (l) lo &= lo - 1;
+                    else hi &= hi - 1;
+                }
+            } else {
+                u32 nc = 0;
+                u64 quote = 0;
+#pragma unroll
+                for (int q = 0; q < 6; ++q) cp[q] = 0;
+                for (u32 p = 0; p < len && nc <= 6; p += 64) {
+                    const u64 in = len - p >= 64 ? ~0ull : (1ull << (len - p)) - 1;
+                    u64 y = bits_from(cmw, a + p) & in;
+                    quote |= bits_from(qtw, a + p) & in;
+                    for (; y && nc <= 6; y &= y - 1, ++nc) {
+                        const u32 c = p + (u32)__ffsll((long long)y) - 1u;
+#pragma unroll
+                        for (int q = 0; q < 6; ++q) cp[q] = nc == (u32)q ? c : cp[q];
                     }
                 }
+                shape = nc == 6 && quote == 0;
             }
-            if (!done) {
-                if (whole) {
-                    // its line end included when it has one
-                    w = parse_row((const unsigned char*)s_txt + CFRONT + a, (u64)(e - a) + (x ? 1 : 0));
-                } else {
-                    u64 q = t0 + CST;
-                    while (q < nbytes && text[q] != '\n') ++q;
-                    w = parse_row(text + t0 + a, (q < nbytes ? q + 1 : nbytes) - (t0 + a));
-                }
+            Row w = malformed();
+            if (shape) {
+                const u32 p0 = CFRONT + a, pe = CFRONT + z;
+                const u32 idn = cp[0];
+                // the id's bytes, first one highest
+                const u64 raw = (u64)ld4(s_txt, p0) | ((u64)ld4(s_txt, p0 + 4) << 32);
+                const u64 id = __builtin_bswap64(raw) & (idn >= 1 && idn < 8 ? ~0ull << (64 - 8 * idn) : ~0ull);
+                w.jid = (i64)id;
+                w.ok = idn >= 1 && idn <= 8 && (id >> 63) == 0;
+                w.ok = quick_ts(s_txt, p0 + cp[0] + 1, p0 + cp[1], w.ts) && w.ok;
+                w.ok = quick_decimal(s_txt, s_p, p0 + cp[1] + 1, p0 + cp[2], w.lat) && w.ok;
+                w.ok = quick_decimal(s_txt, s_p, p0 + cp[2] + 1, p0 + cp[3], w.lon) && w.ok;
+                w.ok = quick_decimal(s_txt, s_p, p0 + cp[4] + 1, p0 + cp[5], w.spd) && w.ok;
+                if (p0 + cp[5] + 1 < pe) w.ok = quick_decimal(s_txt, s_p, p0 + cp[5] + 1, pe, w.hdg) && w.ok;
+                if (!w.ok) w = parse_fields((const unsigned char*)s_txt + p0, cp, len);
             }
-            bad += w.ok ? 0u : 1u;
-            o.journey_id[row] = w.jid;
-            o.ts_ms[row] = w.ts;
-            o.lat_deg[row] = w.lat;
-            o.lon_deg[row] = w.lon;
-            o.speed_mps[row] = (float)w.spd;
-            if (heading) heading[row] = (float)w.hdg;
-            if (row_ok) row_ok[row] = w.ok ? 1 : 0;
+            put(row, w);
         }
         __syncthreads();
+    }
+    if (s_long != ~0u) {
+        const Row w = long_row(text, nbytes, t0 + s_long, s_tmp);
+        if (tid == 0) put(s_long_row, w);
     }
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) bad += __shfl_xor(bad, d, WAVE);
