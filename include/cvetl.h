@@ -28,8 +28,9 @@
  * - Argument errors are returned synchronously as a cv_status and nothing is
  *   enqueued.  Conditions only the device can see (output capacity exceeded,
  *   key range too wide) are written to the caller's device-resident cv_result
- *   (`res`, may be NULL when the caller does not need it) by the last kernel
- *   of the call; read it after synchronising the stream.
+ *   (`res`, may be NULL when the caller does not need it) by a kernel of the
+ *   call, not always the last one (the sort's is known before the records
+ *   are moved): it holds nothing of use before the stream is synchronised.
  * - n == 0 is valid and produces empty outputs.  n must be < 2^32.
  * - Floating-point results are deterministic: every sum is accumulated exactly
  *   in fixed point (integer adds are order-independent) and rounded once.
@@ -132,7 +133,7 @@ typedef struct {
     float* max_speed;
 } cv_groups;
 
-/* Device-resident result word written by the last kernel of a call. */
+/* Device-resident result word written by a call's kernels. */
 typedef struct {
     uint32_t status;        /* cv_status of the device-side checks              */
     uint32_t flags;         /* sort call: bits of the first radix digit (8, or

@@ -27,26 +27,29 @@ constexpr int HI = 8;         // records per thread, rows of HB striped over the
 constexpr int HT = HB * HI;   // records per tile (40 M records: k_dup 785 us and k_trip 265; with tiles of 4 096
                               // 913 and 300, with 16 records per thread of 512 921 and 280)
 constexpr int HNW = HB / WAVE;
-constexpr int HT_SIZE = 2048; // records per 4 bytes of the workspace query (8-byte look-back words per tile fit)
-static_assert(HT >= 2 * HT_SIZE, "look-back words within the query");
+constexpr int HT_SIZE = 2048; // records per 4 bytes of the workspace query, whose multiples of 256 bytes hold an
+                              // 8-byte ticket counter and an 8-byte look-back word per tile
+static_assert(HT >= 4 * HT_SIZE, "two or more tiles: 16 tiles - 8 bytes asked for, 8 tiles + 8 used");
 
-// The tiles' look-back words cleared, and the result with the ticket counter
-// (its n_late word, 0 again in the result that the last tile writes).
-__global__ void __launch_bounds__(256) k_hyg_begin(u64* __restrict__ lb, u64 tiles, cv_result* res)
+// The ticket counter and the tiles' look-back words cleared; without a tile, the result.
+__global__ void __launch_bounds__(256) k_hyg_begin(u64* __restrict__ ws, u64 tiles, cv_result* res)
 {
     const u64 i = (u64)blockIdx.x * 256 + threadIdx.x;
-    if (i == 0) {
+    if (tiles == 0) {
         cv_result r = {};
-        *res = r;
+        if (i == 0) *res = r;
+    } else if (i <= tiles) {
+        ws[i] = 0ull;
     }
-    if (i < tiles) lb[i] = 0ull;
 }
 
 // The block's tile, by ticket: the tiles a block looks back on are held by
-// blocks already running.
-__device__ __forceinline__ u32 take_tile(cv_result* res, u32* s_tile)
+// blocks already running.  (The counter lies in the workspace, which no other call
+// uses: in the caller's result, a call on another stream with the same result
+// would have given out tiles that do not exist.)
+__device__ __forceinline__ u32 take_tile(u64* ticket, u32* s_tile)
 {
-    if (threadIdx.x == 0) *s_tile = (u32)atomicAdd((unsigned long long*)&res->n_late, 1ull);
+    if (threadIdx.x == 0) *s_tile = (u32)atomicAdd((unsigned long long*)ticket, 1ull);
     __syncthreads();
     return *s_tile;
 }
@@ -119,13 +122,14 @@ __device__ bool dup_before(const i64* jid, const i64* ts, const double* lat, con
 __global__ void __launch_bounds__(HB) k_dup(const i64* __restrict__ jid, const i64* __restrict__ ts,
                                             const double* __restrict__ lat, const double* __restrict__ lon,
                                             const float* __restrict__ spd, const u32* __restrict__ perm, u64 n,
-                                            u64* __restrict__ lb, cv_records_out o, u32* __restrict__ perm_out,
+                                            u64* ticket, u64* __restrict__ lb, cv_records_out o,
+                                            u32* __restrict__ perm_out,
                                             cv_result* res)
 {
     __shared__ u32 s_cnt[HI * HNW];
     __shared__ u32 s_tile;
     __shared__ u64 s_base;
-    const u32 tile = take_tile(res, &s_tile);
+    const u32 tile = take_tile(ticket, &s_tile);
     const u64 t0 = (u64)tile * HT + threadIdx.x;
     const int l = lane_id();
     // every column of the thread's records, and the record before each wave row (lane 0)
@@ -181,13 +185,13 @@ __global__ void __launch_bounds__(HB) k_dup(const i64* __restrict__ jid, const i
 // trip_id[k] = number of trip starts at or before k, minus one; trip
 // journeys[t] = the journey id of trip t's first record (t < cap)
 __global__ void __launch_bounds__(HB) k_trip(const i64* __restrict__ jid, const i64* __restrict__ ts, u64 n, i64 gap,
-                                             u64* __restrict__ lb, i64* __restrict__ trip_id,
+                                             u64* ticket, u64* __restrict__ lb, i64* __restrict__ trip_id,
                                              i64* __restrict__ trip_journey, u64 cap, cv_result* res)
 {
     __shared__ u32 s_cnt[HI * HNW];
     __shared__ u32 s_tile;
     __shared__ u64 s_base;
-    const u32 tile = take_tile(res, &s_tile);
+    const u32 tile = take_tile(ticket, &s_tile);
     const u64 t0 = (u64)tile * HT + threadIdx.x;
     const int l = lane_id();
     i64 vj[HI], vt[HI];
@@ -253,11 +257,11 @@ cv_status cv_drop_duplicates(const cv_records* sorted, const uint32_t* perm, con
     hipStream_t s = (hipStream_t)stream;
     cvh::TimedScope ts_("drop_duplicates", s);
     const u64 tiles = (n + HT - 1) / HT;
-    u64* lb = (u64*)ws;
-    hipLaunchKernelGGL(k_hyg_begin, dim3(cvh::grid_for(tiles, 256)), dim3(256), 0, s, lb, tiles, res);
+    u64 *ticket = (u64*)ws, *lb = ticket + 1;
+    hipLaunchKernelGGL(k_hyg_begin, dim3(cvh::grid_for(tiles + 1, 256)), dim3(256), 0, s, ticket, tiles, res);
     if (tiles)
         hipLaunchKernelGGL(k_dup, dim3((unsigned)tiles), dim3(HB), 0, s, sorted->journey_id, sorted->ts_ms,
-                           sorted->lat_deg, sorted->lon_deg, sorted->speed_mps, perm, n, lb, *out, perm_out, res);
+                           sorted->lat_deg, sorted->lon_deg, sorted->speed_mps, perm, n, ticket, lb, *out, perm_out, res);
     return cvh::last_launch_status();
 }
 
@@ -274,11 +278,11 @@ cv_status cv_split_trips(const cv_records* sorted, int64_t gap_ms, int64_t* trip
     hipStream_t s = (hipStream_t)stream;
     cvh::TimedScope ts_("split_trips", s);
     const u64 tiles = (n + HT - 1) / HT;
-    u64* lb = (u64*)ws;
-    hipLaunchKernelGGL(k_hyg_begin, dim3(cvh::grid_for(tiles, 256)), dim3(256), 0, s, lb, tiles, res);
+    u64 *ticket = (u64*)ws, *lb = ticket + 1;
+    hipLaunchKernelGGL(k_hyg_begin, dim3(cvh::grid_for(tiles + 1, 256)), dim3(256), 0, s, ticket, tiles, res);
     if (tiles)
         hipLaunchKernelGGL(k_trip, dim3((unsigned)tiles), dim3(HB), 0, s, sorted->journey_id, sorted->ts_ms, n,
-                           (i64)gap_ms, lb, trip_id, capacity ? trip_journey : nullptr, (u64)capacity, res);
+                           (i64)gap_ms, ticket, lb, trip_id, capacity ? trip_journey : nullptr, (u64)capacity, res);
     return cvh::last_launch_status();
 }
 
