@@ -107,7 +107,10 @@ constexpr u32 PD_FAR = 2;   // not the near order that grouped input has
 // 123 M records takes 549 us with it (476 without; a wave that has seen its input
 // to be otherwise goes on without it: 1 M shuffled 53 us as before), and the key
 // packing and radix passes 0.65 + 0.18 ms where they took 0.75 + 2.44 (the whole
-// call 9.19 -> 7.04 ms; 12.3 M: 1.15 -> 0.88).
+// call 9.19 -> 7.04 ms; 12.3 M: 1.15 -> 0.88).  A wave also ends it where it meets an id's
+// second run: in bundled feeds (runs of a few records in time order, ids coming back)
+// nothing else does, and every run's start and end went through the table (20 M
+// records in runs of 5, 8 000 ids: insert and packing 1.64 ms, 0.76 now).
 constexpr int JW = 3;
 static_assert(JW >= 1 && JW <= 3, "the check's first part covers distances up to 3");
 constexpr u64 JW_GAP = 1ull << 27;
@@ -192,6 +195,14 @@ __device__ __forceinline__ u64 dict_insert_from(u64* table, u64 mask, u64 key, u
 __device__ __forceinline__ void run_store(u64* word, bool start, u32 at)
 {
     __hip_atomic_store((u32*)word + (start ? 1 : 0), at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// the start of an id's run; false where another run's is there already (a wave that
+// sees one id twice has seen that the input is not whole journeys)
+__device__ __forceinline__ bool run_begin(u64* word, u32 at)
+{
+    if ((u32)(slot_now(word) >> 32) != (u32)(EMPTY >> 32)) return false;
+    run_store(word, true, at);
+    return true;
 }
 __device__ __forceinline__ u32 run_start(u64 w) { return (u32)(w >> 32); }
 __device__ __forceinline__ u32 run_length(u64 w) { return (u32)w - (u32)(w >> 32); }
@@ -512,6 +523,7 @@ __global__ void __launch_bounds__(256) k_dict_insert(const i64* __restrict__ jid
             // (an id of the cache is in the table, with the shard csh)
             const u32 cs = dict_cache_slot<DC>((u64)j);
             miss[k] = need && ((SHARDS && wsh[k] != csh) || c_key[w][cs] != (u64)j);
+            if (!SHARDS && !far) far = __ballot(need && !miss[k]);  // an id's second run
             ph[k] = mix64((u64)j) & mask;
             if (SHARDS) {
                 if (miss[k]) pe[k] = ((const ulonglong2*)table)[ph[k]];
@@ -532,37 +544,40 @@ __global__ void __launch_bounds__(256) k_dict_insert(const i64* __restrict__ jid
             const bool cached = !SHARDS || csh != ~0u;
             const u64 j = (u64)jv[k];
             const u64 wi = (w0 + k) * WAVE;  // the window's first record
-            if (!SHARDS && !far) {
-                // where the run before each run start ends; the last run
-                const u64 jb = (u64)lane_below(jv[k], jlast[k]);
-                if (((heads[k] >> l) & 1ull) && wi + l > 0) run_end(table, mask, m, jb, (u32)(wi + l), full, used);
-                if (wi + l + 1 == n) run_end(table, mask, m, j, n, full, used);
-            }
             const u32 cs = dict_cache_slot<DC>(j);
             // an earlier window of the round may have brought the id; of the
             // lanes that miss with one id, the one that owns its cache slot
             // inserts it (the first meetings of a table's few ids by every
             // wave at once are bound by atomics on the ids' slots)
             if (cached && miss[k]) miss[k] = c_key[w][cs] != j;
-            if (__ballot(miss[k]) == 0) continue;
-            if (miss[k]) c_own[w][cs] = (u32)l;
-            __builtin_amdgcn_wave_barrier();
-            const int own = miss[k] ? (int)c_own[w][cs] : l;
-            const u64 jown = (u64)__shfl((i64)j, own, WAVE);
-            if (miss[k] && (own == l || jown != j || !cached)) {
-                if (SHARDS) {
-                    // the record's shard: the window's, or searched where a shard starts inside it
-                    const u64 i = wi + l;
-                    const u32 sh = wsh[k] != ~0u ? wsh[k] : shard_of(soff, S, i < n ? i : (u64)n - 1);
-                    if (!dict_insert_tag(table, mask, j, ph[k], pe[k], (u64)sh, multi, used)) full = true;
-                } else {
-                    const u64 slot = dict_insert_from(table, mask, j, ph[k], pe[k].x, used);
-                    if (slot == ~0ull) full = true;
-                    else if (!far) run_store(&table[2 * slot + 1], true, (u32)(wi + l));
+            if (__ballot(miss[k]) != 0) {
+                if (miss[k]) c_own[w][cs] = (u32)l;
+                __builtin_amdgcn_wave_barrier();
+                const int own = miss[k] ? (int)c_own[w][cs] : l;
+                const u64 jown = (u64)__shfl((i64)j, own, WAVE);
+                bool again = false;  // the id's run here is its second
+                if (miss[k] && (own == l || jown != j || !cached)) {
+                    if (SHARDS) {
+                        // the record's shard: the window's, or searched where a shard starts inside it
+                        const u64 i = wi + l;
+                        const u32 sh = wsh[k] != ~0u ? wsh[k] : shard_of(soff, S, i < n ? i : (u64)n - 1);
+                        if (!dict_insert_tag(table, mask, j, ph[k], pe[k], (u64)sh, multi, used)) full = true;
+                    } else {
+                        const u64 slot = dict_insert_from(table, mask, j, ph[k], pe[k].x, used);
+                        if (slot == ~0ull) full = true;
+                        else if (!far) again = !run_begin(&table[2 * slot + 1], (u32)(wi + l));
+                    }
                 }
+                if (!SHARDS) far |= __ballot(again);
+                if (cached && miss[k] && own == l) c_key[w][cs] = j;
+                __builtin_amdgcn_wave_barrier();
             }
-            if (cached && miss[k] && own == l) c_key[w][cs] = j;
-            __builtin_amdgcn_wave_barrier();
+            if (!SHARDS && !far) {
+                // where the run before each run start ends; the last run
+                const u64 jb = (u64)lane_below(jv[k], jlast[k]);
+                if (((heads[k] >> l) & 1ull) && wi + l > 0) run_end(table, mask, m, jb, (u32)(wi + l), full, used);
+                if (wi + l + 1 == n) run_end(table, mask, m, j, n, full, used);
+            }
         }
     }
     if (has_min) atomicOr(&m->has_min, 1u);
