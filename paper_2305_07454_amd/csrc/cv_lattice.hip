@@ -221,18 +221,24 @@ __device__ __forceinline__ float rescale(float x, float mn, float mx)
 }
 
 // Block b rescales chunks [NCH * (b % gpi), +NCH) of image b / gpi: the stretches
-// of 64 cells that occ marks (every one without occ), a wave each (a full day's
-// 1.55 M occupied cells: 201 us, 542 when every volume was read again; 4 or 16
-// chunks per block 226 and 260).  The first
+// of 64 cells that occ marks (every one without occ), a wave each.  With 8 chunks
+// to a block (a full day's 1.55 M occupied cells: 201 us, 542 when every volume was
+// read again; 4 or 16 chunks per block 226 and 260) a lattice of fewer than NORM_FEW
+// chunks would leave CUs idle, and a wave with one chunk after the other in turn:
+// there a block takes one chunk and its waves a quarter of it each (scatter and
+// rescaling with 8 and 1: 24 full images of 200 x 200 cells 84 and 30 us, 288 a tenth
+// full 132 and 94, 96 full ones of 333 x 333 178 and 144; 320 full ones of 320 x 320,
+// 8 000 chunks, 439 and 408; the full day's 21 888 1209 and 1288).  The first
 // block of a sector's first image writes the channels' min and max as floats
 // (NaN for a channel with no occupied cell).
-constexpr u32 NCH = 8;
+constexpr u64 NORM_FEW = 8192;
+template <u32 NCH>
 __global__ void __launch_bounds__(LB) k_lat_norm(float* __restrict__ lat, u32 D, u64 cells, u64 cpi, u64 gpi, u64 n_t,
                                                   const u32* __restrict__ part, const u64* __restrict__ occ,
                                                   float* __restrict__ out)
 {
-    constexpr int NWL = LB / WAVE, NU = 4;
-    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
+    constexpr u32 NWL = LB / WAVE, NU = 4, SPLIT = NCH < NWL ? NWL / NCH : 1;  // waves per chunk
+    const u32 w = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
     const int l = lane_id();
     const u64 img = blockIdx.x / gpi;
     const u64 ch0 = (blockIdx.x % gpi) * NCH;
@@ -253,24 +259,25 @@ __global__ void __launch_bounds__(LB) k_lat_norm(float* __restrict__ lat, u32 D,
     }
     float* sp = lat + (img / D * 2 * D + 2 * d) * cells;
     float* vo = sp + cells;
-    for (u32 c = w; c < NCH && ch0 + c < cpi; c += NWL) {
+    for (u32 c = w / SPLIT; c < NCH && ch0 + c < cpi; c += NWL / SPLIT) {
         const u64 c0 = (ch0 + c) * CH;
-        u64 m = occ ? occ[img * cpi + ch0 + c] : ~0ull;
+        u64 m = (~0ull >> (SUB - SUB / SPLIT)) << (w % SPLIT * (SUB / SPLIT));  // the wave's stretches
+        if (occ) m &= occ[img * cpi + ch0 + c];
         while (m) {
             u64 i[NU];
             float v[NU], x[NU];
 #pragma unroll
-            for (int q = 0; q < NU; ++q) {
+            for (u32 q = 0; q < NU; ++q) {
                 i[q] = cells;
                 if (m) i[q] = c0 + 64 * (u64)(__ffsll((long long)m) - 1) + l;
                 m &= m - 1;  // (0 stays 0)
             }
 #pragma unroll
-            for (int q = 0; q < NU; ++q) v[q] = i[q] < cells ? vo[i[q]] : 0.f;
+            for (u32 q = 0; q < NU; ++q) v[q] = i[q] < cells ? vo[i[q]] : 0.f;
 #pragma unroll
-            for (int q = 0; q < NU; ++q) x[q] = v[q] > 0.f ? sp[i[q]] : 0.f;
+            for (u32 q = 0; q < NU; ++q) x[q] = v[q] > 0.f ? sp[i[q]] : 0.f;
 #pragma unroll
-            for (int q = 0; q < NU; ++q) {
+            for (u32 q = 0; q < NU; ++q) {
                 if (!(v[q] > 0.f)) continue;
                 sp[i[q]] = rescale(x[q], smn, smx);
                 vo[i[q]] = rescale(v[q], vmn, vmx);
@@ -435,12 +442,13 @@ cv_status cv_lattice_normalize(float* lattice, uint64_t n_t, const cv_grid_spec*
     hipStream_t s = (hipStream_t)stream;
     cvh::TimedScope ts_("lattice_norm", s);
     const u64 cpi = ((u64)cells + CH - 1) / CH;  // chunks per image
-    const u64 gpi = (cpi + NCH - 1) / NCH;
+    const u32 nch = blocks < NORM_FEW ? 1 : 8;
+    const u64 gpi = (cpi + nch - 1) / nch;
     u32* part = (u32*)ws;
     u64* occ = ws_bytes >= need ? (u64*)((char*)ws + parts) : nullptr;
     hipLaunchKernelGGL(k_lat_minmax, dim3((unsigned)blocks), dim3(LB), 0, s, lattice, D, (u64)cells, cpi, part, occ);
     hipLaunchKernelGGL(k_lat_mm_reduce, dim3(MR, D), dim3(LB), 0, s, part, (u64)n_t, D, cpi);
-    hipLaunchKernelGGL(k_lat_norm, dim3((unsigned)(n_t * D * gpi)), dim3(LB), 0, s, lattice, D, (u64)cells, cpi, gpi,
+    hipLaunchKernelGGL(nch == 1 ? k_lat_norm<1> : k_lat_norm<8>, dim3((unsigned)(n_t * D * gpi)), dim3(LB), 0, s, lattice, D, (u64)cells, cpi, gpi,
                        (u64)n_t, part, occ, channel_min_max);
     return cvh::last_launch_status();
 }
