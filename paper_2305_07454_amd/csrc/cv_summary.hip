@@ -36,11 +36,13 @@ constexpr int SB = 256;
 //   SI_M  up to N_M records;
 //   SI_L  above.
 // Whole summary, SI_S / SI_M / SI_L: 33 k records 26 / 48 / 105 us, 1 M 34 / 56 /
-// 124, 4 M 82 / 80 / 140, 8 M 162 / 143 / 162, 32 M 368 / 358 / 367, a 30 M batch
-// of shards 639 / 366 / 393; 100 M records 948 / 931 / 933 and a 200 M batch
-// - / 2 238 / 1 960.
+// 124, 4 M 82 / 80 / 140, 8 M 162 / 143 / 162, a 30 M batch of shards 639 / 366 /
+// 393; 100 M records 948 / 931 / 933 and a 200 M batch - / 2 238 / 1 960.  Where
+// SI_M ends follows journeys of thousands of records (SI_M / SI_L, 24 M: 260 / 266,
+// 26 M 280 / 284, 28 M 301 / 293, 33 M 351 / 326; of 150 records 453 / 502, 489 / 552,
+// 521 / 556, 613 / 617).
 constexpr int SI_S = 8, SI_M = 16, SI_L = 64;
-constexpr u64 N_S = 4ull << 20, N_M = 32ull << 20;
+constexpr u64 N_S = 4ull << 20, N_M = 25ull << 20;
 constexpr int FX_DIST = SUM_FX_DIST;  // distance: 2^-128 m resolution (exact for steps >= 2^-75 m)
 constexpr int FX_SPD = SUM_FX_SPD;    // speed: exact for every float32
 
