@@ -342,18 +342,29 @@ k_radix_pass(const u64* __restrict__ keys_in, const u32* __restrict__ vals_in, u
 // waits until the pass before it has counted all its tiles as done (tickets[1 +
 // pass]), that is, on earlier tickets only, whose blocks run: no block waits
 // for one that has not started.
-template <int SORT_BLOCK, int SORT_ITEMS>
-__global__ void __launch_bounds__(SORT_BLOCK)
-k_radix_all(u64* k0, u64* k1, const u32* v_first, u32* v0, u32* v1, u32 n_max, const u32* __restrict__ n_dev,
-            int max_passes, const u32* __restrict__ bits_dev, const u32* __restrict__ hist, u32 wide, u64* status,
-            u32* tickets, const u32* __restrict__ pack)
+struct RadixAll {
+    u64 *k0, *k1;
+    const u32* v_first;
+    u32 *v0, *v1;
+    u32 n_max;
+    const u32* n_dev;
+    int max_passes;
+    const u32* bits_dev;
+    const u32* hist;
+    u32 wide;
+    u64* status;
+    u32* tickets;
+    const u32* pack;
+};
+template <int SORT_BLOCK, int SORT_ITEMS, class Lds>
+__device__ __forceinline__ void radix_all(const RadixAll& r, u32 n, Lds& s, u32& s_tile)
 {
     constexpr u32 SORT_TILE = SORT_BLOCK * SORT_ITEMS;
-    __shared__ RadixLds<SORT_BLOCK, SORT_ITEMS, RADIX_BITS + 1> s;
-    __shared__ u32 s_tile;
-    const RadixForm form(pack);
-    const u32 bits = bits_dev ? *bits_dev : ~0u;
-    const u32 n = n_dev ? *n_dev : n_max;
+    u64 *const k0 = r.k0, *const k1 = r.k1;
+    u32 *const v0 = r.v0, *const v1 = r.v1, *const tickets = r.tickets;
+    const RadixForm form(r.pack);
+    const u32 bits = r.bits_dev ? *r.bits_dev : ~0u;
+    const int max_passes = r.max_passes;
     int np = 0;
     while (np < max_passes && (u32)form.low(np) < bits) ++np;
     const u32 tiles = (u32)(((u64)n + SORT_TILE - 1) / SORT_TILE);
@@ -373,12 +384,12 @@ k_radix_all(u64* k0, u64* k1, const u32* v_first, u32* v0, u32* v1, u32 n_max, c
             }
             __syncthreads();
         }
-        RadixPass a{(pass & 1) ? k1 : k0, pass == 0 ? v_first : ((pass & 1) ? v1 : v0), (pass & 1) ? k0 : k1,
-                    (pass & 1) ? v0 : v1, status, n};
+        RadixPass a{(pass & 1) ? k1 : k0, pass == 0 ? r.v_first : ((pass & 1) ? v1 : v0), (pass & 1) ? k0 : k1,
+                    (pass & 1) ? v0 : v1, r.status, n};
         form.set(a, pass);
         a.tin = pass > 0;
         a.tout = pass + 1 < np;
-        const u32* h = hist + (wide ? hist_wide_off(pass) : pass * RADIX);
+        const u32* h = r.hist + (r.wide ? hist_wide_off(pass) : pass * RADIX);
         if (pass == 0 && form.w0 == RADIX_BITS + 1) {
             a.dcnt = threadIdx.x < 2 * RADIX ? h[threadIdx.x] : 0u;
             radix_tile<SORT_BLOCK, SORT_ITEMS, RADIX_BITS + 1>(s, a, tile);
@@ -396,6 +407,27 @@ k_radix_all(u64* k0, u64* k1, const u32* v_first, u32* v0, u32* v1, u32 n_max, c
         if (pass + 1 < np && threadIdx.x == 0)
             __hip_atomic_fetch_add(&tickets[1 + pass], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
+}
+template <int B, int I>
+__global__ void __launch_bounds__(B) k_radix_all(RadixAll r)
+{
+    __shared__ RadixLds<B, I, RADIX_BITS + 1> s;
+    __shared__ u32 s_tile;
+    radix_all<B, I>(r, r.n_dev ? *r.n_dev : r.n_max, s, s_tile);
+}
+// the tile by a count known on the device alone
+constexpr u32 ALL_SMALL = 1u << 19;  // keys up to which tiles of 512 x 8 are the better ones
+template <int B>
+__global__ void __launch_bounds__(B) k_radix_all_counted(RadixAll r)
+{
+    __shared__ union {
+        RadixLds<B, 8, RADIX_BITS + 1> small;
+        RadixLds<B, 16, RADIX_BITS + 1> large;
+    } s;
+    __shared__ u32 s_tile;
+    const u32 n = *r.n_dev;
+    if (n <= ALL_SMALL) radix_all<B, 8>(r, n, s.small, s_tile);
+    else radix_all<B, 16>(r, n, s.large, s_tile);
 }
 
 }  // namespace
@@ -415,29 +447,35 @@ namespace {
 constexpr u64 DEVICE_COUNT_GRID = 2048;
 constexpr u64 DEVICE_COUNT_MAX_TILES = 1ull << 17;
 
-// Sorts of few keys take k_radix_all, whatever the shape: tiles of 512 x 8 keys
-// where the chip has idle CUs left (500 000 keys, three passes that work: 84 ->
+// Sorts of few keys take all passes in one launch, whatever the shape: tiles of 512 x 8
+// keys where the chip has idle CUs left (500 000 keys, three passes that work: 84 ->
 // 49 us; 30 000: 46 -> 26), of 512 x 16 above (1 M, four passes: 108 -> 82; 2 M, two:
 // 88 -> 59).  A pass between others writes its words through, some 8-byte runs
 // at a time, and at 2 M keys and four passes that takes what the launches saved
 // (126, 128 us; 4 M 157, 211).  A count known on the device alone may be far below
-// its bound or come near it, and its line lies where one launch costs the second
-// no more than it saves the first:
-//   few   distinct ids, a flush's rows: 2 M ids allowed, a few thousand there, sort of
-//         the records 260 us in one launch and 270 in launches per pass; all there
-//         999 and 843; 4 M allowed and there 1821 and 1444;
-//   rows  the grid's partial rows (merge of 0.001 deg x 1 min): 1 M records, one in
-//         fifty with a row of its own, 72 and 90; every one 201 and 172; 2 M 77 and
-//         95, 412 and 237;
+// its bound or come near it, so the kernel picks the tile, and the line lies where
+// one launch costs the second no more than launches per pass ever did:
+//   few   distinct ids, a flush's rows (the record sort whole, one launch / per pass):
+//         3 M ids allowed, 5 000 there 498 / 508 us, all there 1575 / 1466 (1680 when
+//         each pass read its offsets from a scan's launch); 4.1 M 603 / 615, 2008 / 1871
+//         (2022);
+//   rows  the grid's partial rows (the whole call; every record one of its own: random
+//         places): 1.2 M records at 0.001 deg x 1 min 101 / 109, random 306 / 304; 2 M 115 /
+//         123, 378 / 369; 3 M 140 / 149, 616 / 584 (567 with the scan);
 //   many  the same with directions: a row for every two or three records.
+// Tiles of 512 x 8 alone took 452 us for 2 M random records, 2375 for 4.1 M distinct ids.
 constexpr int ALL_B = 512;
-constexpr u64 ALL_GRID = 512;
-int all_items(u64 n_max, RadixCount count)  // keys per thread; 0: a launch per pass
+constexpr int ALL_GRID = 512;
+enum class AllForm { none, small, large, counted };  // none: a launch per pass
+AllForm all_form(u64 n_max, RadixCount count)
 {
-    if (count == RadixCount::few) return n_max <= (1u << 21) ? 8 : 0;
-    if (count == RadixCount::rows) return n_max <= (1u << 20) ? 8 : 0;
-    if (count == RadixCount::many) return n_max <= (1u << 19) ? 8 : 0;
-    return n_max <= (1u << 19) ? 8 : n_max <= (1u << 21) ? 16 : 0;
+    if (n_max <= ALL_SMALL) return AllForm::small;
+    switch (count) {
+    case RadixCount::exact: return n_max <= (1u << 21) ? AllForm::large : AllForm::none;
+    case RadixCount::few: return n_max <= (1u << 22) ? AllForm::counted : AllForm::none;
+    case RadixCount::rows: return n_max <= (1u << 21) ? AllForm::counted : AllForm::none;
+    default: return AllForm::none;
+    }
 }
 
 // tile shapes compiled into the library; the sort uses sort_shape()
@@ -480,9 +518,9 @@ int sort_block(int i) { return SHAPES[i].block; }
 bool sort_wide_first() { return g_wide_first && SHAPES[g_shape].block >= 2 * RADIX; }
 u64 sort_status_words(u64 n_max, RadixCount count, bool wide)
 {
-    const int items = all_items(n_max, count);
-    const u64 tile = items ? (u64)ALL_B * items : (u64)sort_tile(g_shape);
-    const bool nine = wide && (items || SHAPES[g_shape].block >= 2 * RADIX);
+    const AllForm form = all_form(n_max, count);
+    const u64 tile = form == AllForm::none ? (u64)sort_tile(g_shape) : (u64)ALL_B * (form == AllForm::large ? 16 : 8);
+    const bool nine = wide && (form != AllForm::none || SHAPES[g_shape].block >= 2 * RADIX);
     return (n_max + tile - 1) / tile * (nine ? 2 * RADIX : RADIX) + 1;
 }
 int sort_min_tile()
@@ -502,13 +540,15 @@ void radix_passes(u64* k0, u64* k1, const u32* v_first, u32* v0, u32* v1, u32 n_
     const u64 tile = (u64)sort_tile(sh);
     // the kernels read the first digit's width with the packing words
     if (w0_dev && w0_dev != pack + 2) return;  // (the record sort keeps them adjacent)
-    if (const int items = all_items(n_max, n_dev ? count : RadixCount::exact)) {
+    const AllForm form = all_form(n_max, n_dev ? count : RadixCount::exact);
+    if (form != AllForm::none) {
         cvh::TimedScope ts_(timed ? names[0] : nullptr, s);
-        const u64 at = ((u64)n_max + ALL_B * items - 1) / (ALL_B * items);
-        const dim3 grid((unsigned)(at < 1 ? 1 : at < ALL_GRID ? at : ALL_GRID));
-        auto* kern = items == 8 ? k_radix_all<ALL_B, 8> : k_radix_all<ALL_B, 16>;
-        hipLaunchKernelGGL(kern, grid, dim3(ALL_B), 0, s, k0, k1, v_first, v0, v1, n_max, n_dev, passes, bits_dev, hist,
-                           w0_dev ? 1u : 0u, status, tickets, pack);
+        const RadixAll all{k0, k1, v_first, v0, v1, n_max, n_dev, passes, bits_dev, hist, w0_dev ? 1u : 0u, status, tickets,
+                           pack};
+        auto* kern = form == AllForm::small ? k_radix_all<ALL_B, 8> :
+                     form == AllForm::large ? k_radix_all<ALL_B, 16> : k_radix_all_counted<ALL_B>;
+        const int at = ALL_B * (form == AllForm::large ? 16 : 8);
+        hipLaunchKernelGGL(kern, dim3(cvh::grid_for(n_max, at, ALL_GRID)), dim3(ALL_B), 0, s, all);
         return;
     }
     const u64 tiles = ((u64)n_max + tile - 1) / tile;
@@ -549,9 +589,6 @@ void radix_passes(u64* k0, u64* k1, const u32* v_first, u32* v0, u32* v1, u32 n_
     }
 }
 
-}  // namespace cv
-
-namespace cv {
 }  // namespace cv
 
 extern "C" {
