@@ -448,8 +448,8 @@ def bench_plain(args, workload):
     # the gather with the kinematics
     key_bits = rs["key_bits"]
     p0 = rs["packed_pass"]
-    roof, pass_ms = radix_roofline(cvetl, n, rs)
-    sorts = roof is not None
+    sorts = cvetl.cv_sort_passes(pipe.ws_sort) > 0
+    roof, pass_ms = radix_roofline(cvetl, n, rs, sorts=sorts)
     if not sorts:
         roof = gather_roofline(cvetl, n)
     stages = {}
@@ -705,11 +705,11 @@ def bench_csv(r, dev, rows=4_000_000):
     return info
 
 
-def radix_roofline(cvetl, n, rs, traffic=None):
+def radix_roofline(cvetl, n, rs, traffic=None, sorts=True):
     """Roofline of the record sort's radix scatter passes from the per-pass
     HIP-event timing families (working passes only: digits below the key
     width), and their time; None and the idle launches' time where the passes
-    had nothing to sort (they end before the card could move a pass's bytes)."""
+    had nothing to sort (sorts, as the sort itself says)."""
     key_bits = rs["key_bits"]
     db = int(cvetl.cv_tuning_get("radix_bits"))
     w0 = first_digit_bits(rs)
@@ -728,7 +728,7 @@ def radix_roofline(cvetl, n, rs, traffic=None):
     avg_ms = pass_ms / max(launches, 1)
     per_launch = alg / max(launches, 1)
     achieved = per_launch / (avg_ms / 1e3) / 1e9 if avg_ms > 0 else 0.0
-    if achieved > HBM_PEAK_GBS:
+    if not sorts:
         return None, pass_ms
     kind = f"stable {db}-bit LSD scatter pass" if w0 == db else f"stable LSD scatter pass: a {w0}-bit first digit, then {db}-bit digits"
     return {"bound": "hbm", "kernel": f"k_radix_pass ({kind})",

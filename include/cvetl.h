@@ -173,6 +173,12 @@ cv_status cv_sort_records(const cv_records* in, uint64_t max_journeys, uint32_t*
                           const cv_records_out* sorted, cv_result* res, void* ws, size_t ws_bytes,
                           void* stream);
 
+/* cv_sort_passes -- (measurement support) how many radix passes moved the
+ *   records of the last sort of n > 0 records that used the workspace ws,
+ *   written to passes [device]: 0 for whole journeys in near order.  Enqueue
+ *   it after that sort and before ws serves another call. */
+cv_status cv_sort_passes(const void* ws, uint32_t* passes, void* stream);
+
 /* ------------------------------------------------------------------------
  * cv_journey_features -- per-point kinematics of records already in
  * (journey, time) order.  For record k with predecessor p = k-1 in the same

@@ -1501,6 +1501,11 @@ __global__ void __launch_bounds__(256) k_gather(u32 n, const SortMeta* m, const 
     }
 }
 
+__global__ void k_passes(const SortMeta* m, u32* passes)
+{
+    if (threadIdx.x == 0) *passes = m->passes;
+}
+
 __global__ void k_empty_result(cv_result* res)
 {
     if (threadIdx.x == 0) {
@@ -2022,6 +2027,13 @@ cv_status cv_sort_workspace_size(uint64_t n, uint64_t max_journeys, size_t* byte
     SortLayout L(nullptr, n, max_journeys);
     *bytes = L.bytes;
     return CV_OK;
+}
+
+cv_status cv_sort_passes(const void* ws, uint32_t* passes, void* stream)
+{
+    if (!ws || !cvh::aligned(ws, cvh::WS_ALIGN) || !passes || !cvh::aligned(passes, 4)) return CV_ERR_INVALID_ARGUMENT;
+    hipLaunchKernelGGL(k_passes, dim3(1), dim3(64), 0, (hipStream_t)stream, (const SortMeta*)ws, passes);
+    return cvh::last_launch_status();
 }
 
 cv_status cv_sort_records(const cv_records* in, uint64_t max_journeys, uint32_t* perm, const cv_records_out* sorted,

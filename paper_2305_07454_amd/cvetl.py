@@ -135,6 +135,8 @@ def _declare(L):
     L.cv_sort_records.argtypes = [ctypes.POINTER(CvRecords), U64, P, ctypes.POINTER(CvRecordsOut), P, P,
                                   ctypes.c_size_t, P]
     L.cv_sort_records.restype = S
+    L.cv_sort_passes.argtypes = [P, P, P]
+    L.cv_sort_passes.restype = S
     L.cv_sort_records_features.argtypes = [ctypes.POINTER(CvRecords), U64, P, ctypes.POINTER(CvRecordsOut),
                                            ctypes.POINTER(CvFeatures), P, P, ctypes.c_size_t, P]
     L.cv_sort_records_features.restype = S
@@ -327,6 +329,13 @@ def cv_sort_records(rec, max_journeys=None, want_sorted=True, ws=None, stream=No
                                stream=stream)
     _check(r["status"], "cv_sort_records (device)")
     return perm, out, r
+
+
+def cv_sort_passes(ws, stream=None):
+    """Radix passes that the last sort in the workspace ws ran (0: whole journeys in near order)."""
+    passes = torch.zeros(1, dtype=torch.int32, device=ws.device)
+    _check(lib().cv_sort_passes(_ptr(ws), _ptr(passes), _stream(stream)), "cv_sort_passes")
+    return int(passes.cpu()[0])
 
 
 def cv_sort_records_features(rec, max_journeys, ws=None, stream=None, shard_offsets=None):
