@@ -3,8 +3,10 @@
 Sweeps the compiled radix-pass tile shapes (threads x keys per thread) on a
 workload and keeps the fastest per workload signature (record count, whether
 the batch is many shards, grid cardinality) in a JSON cache next to this file.
-The plain workloads are timed by the record sort's scatter passes (the
-library's per-kernel HIP-event timing); the batched workload (many uneven
+The plain workloads, their records in the order of a time-ordered feed, are timed
+by the record sort's scatter passes (the library's per-kernel HIP-event timing;
+journey files in near order need no pass, and up to 2^21 records all passes share one
+launch of its own shape: both are refused); the batched workload (many uneven
 shards in one set of launches) by its whole step, since its shape choice also
 moves the group-key sort of the grid merge.  ``apply(n, workload)`` installs the
 cached choice of the same signature, nearest in n, or leaves the library
@@ -19,6 +21,8 @@ import json
 import os
 import sys
 import time
+
+ONE_LAUNCH = 1 << 21  # records up to which a sort's passes share one launch of its own shape
 
 CACHE = os.path.join(os.path.dirname(os.path.abspath(__file__)), "tuning.json")
 
@@ -63,16 +67,24 @@ def apply(n: int, workload: str | None = None) -> dict | None:
 
 
 def sweep_sort_shapes(rec, grid, reps=5, log=print):
-    """Time the record sort passes for every compiled shape on one batch."""
+    """Time the record sort passes for every compiled shape on one batch.
+    ValueError for a batch that says nothing of the shapes: one that no pass
+    sorts, or of so few records that all passes share a launch."""
     import torch
     from . import cvetl
     n = int(rec["journey_id"].numel())
+    if n <= ONE_LAUNCH:
+        raise ValueError(f"{n} records: up to {ONE_LAUNCH} the passes share one launch, whatever the shape")
+    mj = max(1, min(n, 1 << 20))
+    ws = cvetl.workspace(cvetl._size(cvetl.lib().cv_sort_workspace_size, n, mj), rec["journey_id"].device)
     shapes = cvetl.cv_tuning_get("sort_shapes")
     results = []
     for sh in range(shapes):
         cvetl.cv_tuning_set("sort_shape", sh)
         tile = cvetl.cv_tuning_get("sort_tile")
-        perm, srt, r = cvetl.cv_sort_records(rec)          # warm-up and key width
+        perm, srt, r = cvetl.cv_sort_records(rec, max_journeys=mj, ws=ws)  # warm-up and key width
+        if cvetl.cv_sort_passes(ws) == 0:
+            raise ValueError("whole journeys in near order: no pass sorts them")
         db = int(cvetl.cv_tuning_get("radix_bits"))
         w0 = int(r.get("flags") or db)  # bits of the first digit (9 where that saves a pass)
         kb = int(r["key_bits"])
@@ -81,7 +93,7 @@ def sweep_sort_shapes(rec, grid, reps=5, log=print):
         cvetl.cv_timing_reset()
         cvetl.cv_timing_enable(True)
         for _ in range(reps):
-            cvetl.cv_sort_records(rec, sync=False)
+            cvetl.cv_sort_records(rec, max_journeys=mj, ws=ws, sync=False)
         torch.cuda.synchronize()
         cvetl.cv_timing_enable(False)
         ms = [cvetl.cv_timing_read(f"sort_pass{p}") for p in range(passes)]
@@ -153,6 +165,10 @@ def main():
     n = r.n
     rec = cvetl.to_device(r)
     del r
+    if args.workload != "c2":
+        order = torch.sort(rec["ts_ms"], stable=True)[1]
+        rec = {k: v[order] for k, v in rec.items()}
+        del order
     grid = gen.GRIDS[args.workload]
     if args.workload == "c2":
         res = sweep_batched(rec, sizes, grid, args.reps, log=say)
