@@ -697,6 +697,9 @@ __device__ __forceinline__ void dict_settle(SortMeta* m, const InsPart* __restri
 // 74 us from the table, 31 by the bits, 512 k 20 and 10, and a serving session of
 // eight pushes went from 3062 to 2829 us.  Small ones are up to half full: setting
 // the bits costs as much as they save, and 16 slots to a thread 3 us more than 4.
+// (16 slots of a table without bits are 256 bytes per thread: where the bits were kept
+// only for tables that the records' key words could hold the bits of, 10 000 records
+// with 16 M ids allowed took 681 us to sort, 249 with bits.)
 constexpr u64 USED_MIN = 1u << 18;  // slots from which the bits are kept
 inline __host__ __device__ u32 compact_slots(u64 slots) { return slots >= USED_MIN ? 16u : 4u; }
 __global__ void __launch_bounds__(256) k_dict_compact(u64* __restrict__ table, u64 slots, u32 max_j,
@@ -1959,9 +1962,9 @@ static cv_status sort_impl(const cv_records* in, const uint64_t* soff, uint32_t 
         // every buffer holds at least 256 bytes)
         InsPart* parts = (InsPart*)L.K1;
         static_assert(sizeof(InsPart) <= 256, "one part fits the smallest buffer");
-        // the occupied slots' bits lie in the first key buffer, which the packing
-        // writes later (not where the caller allows for far more ids than records)
-        u32* used = L.slots >= USED_MIN && L.slots / 8 <= n * sizeof(u64) ? (u32*)L.K0 : nullptr;
+        // the occupied slots' bits lie in the second list of ids, which is written once
+        // the first is complete (fewer than four slots, of a bit each, per id allowed)
+        u32* used = L.slots >= USED_MIN ? (u32*)L.dl1 : nullptr;
         const u64 fill_words = L.slots > L.zero_bytes / 4 ? L.slots : L.zero_bytes / 4;
         hipLaunchKernelGGL(k_sort_begin, dim3(cvh::grid_for(fill_words, 256, 4096)), dim3(256), 0, s, L.meta, L.table,
                            2 * L.slots, L.zero_begin, (u64)(L.zero_bytes / 4), used);
