@@ -69,15 +69,16 @@ struct GPart {
 };
 static_assert(sizeof(GPart) == 32, "partial layout");
 
+// (a snapshot of the serving form holds this struct: its fields keep their places)
 struct GridMeta {
-    u32 groups;     // groups after the merge of the partials
+    u32 spare0;
     u32 overflow;   // HBM table full
     u64 n_out;      // records outside the grid
     u64 max_key;    // largest key seen
     u32 key_bits;
     u32 passes;
     u32 compact_n;
-    u32 chunks;     // chunks of sorted partial pairs (the partial-row merge)
+    u32 spare1;
     u32 tickets[MAX_PASSES];
 };
 

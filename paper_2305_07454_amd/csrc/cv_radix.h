@@ -30,8 +30,6 @@ constexpr int MAX_PASSES = 8;
 // digit's 512 counters, then 256 per later digit.
 constexpr int HIST_WIDE_WORDS = (MAX_PASSES + 1) * RADIX;
 __host__ __device__ constexpr int hist_wide_off(int p) { return p ? (p + 1) * RADIX : 0; }
-// bits of the first digit: *w0 (device, nullable) when it is 9, else 8
-__device__ __forceinline__ u32 first_digit_bits(const u32* w0) { return (w0 && *w0 == RADIX_BITS + 1) ? RADIX_BITS + 1 : RADIX_BITS; }
 
 // Tile shapes (threads per block x keys per thread) compiled into the library.
 // The sort launches the selected one; workspaces are sized for the smallest
@@ -55,12 +53,11 @@ bool sort_wide_first();
 // Host launchers (defined in cv_radix.hip).
 //   radix_hist : digit histograms of `passes` passes (limited on device by
 //                ceil(*bits_dev / 8) when bits_dev is given) added into hist.
-//   radix_passes: (hist: the digit counts, each pass scans its own) up to `passes` stable scatter passes, ping-pong k0 -> k1 -> k0
-//                ...; pass p is skipped on device when 8p >= *bits_dev.  vals of
+//   radix_passes: up to `passes` stable scatter passes (hist: the digit counts,
+//                each pass scans its own), ping-pong k0 -> k1 -> k0 ...; pass p
+//                is skipped on device when 8p >= *bits_dev.  vals of
 //                pass 0 come from v_first (nullptr = identity).  After p passes
 //                the data sits in (k1, v1) when p is odd, in (k0, v0) when even.
-void radix_hist(const u64* keys, u32 n_max, const u32* n_dev, int passes, const u32* bits_dev, u32* hist,
-                int grid, hipStream_t s);
 //                Few keys take all passes in one launch (k_radix_all).
 //                When `timed`, pass p is bracketed as timing family "sort_pass<p>"
 //                (a launch of all passes as "sort_pass0").
@@ -72,6 +69,8 @@ void radix_hist(const u64* keys, u32 n_max, const u32* n_dev, int passes, const 
 //                9; 9 only with p0 = 0), the word after pack's two; hist then
 //                use the wide layout and status holds 512 words per tile.
 //                count: what n_max says of the number at n_dev.
+void radix_hist(const u64* keys, u32 n_max, const u32* n_dev, int passes, const u32* bits_dev, u32* hist,
+                int grid, hipStream_t s);
 void radix_passes(u64* k0, u64* k1, const u32* v_first, u32* v0, u32* v1, u32 n_max, const u32* n_dev,
                   const u32* bits_dev, int passes, const u32* hist, u64* status, u32* tickets, hipStream_t s,
                   bool timed = false, const u32* pack = nullptr, const u32* w0_dev = nullptr,

@@ -48,7 +48,6 @@ constexpr u64 SIGN = 0x8000000000000000ull;
 struct SortMeta {
     u64 tmin_ord;
     u64 tmax_ord;
-    u32 n_distinct;
     u32 has_min;
     u32 overflow;
     u32 J;

@@ -139,7 +139,6 @@ __global__ void __launch_bounds__(256) k_st_begin(StreamMeta* m, u64* __restrict
     }
 }
 
-// journey starts per tile of the sorted batch
 // The batch's journeys in one pass over the sorted ids: boff[j] = position of batch
 // journey j's first record, boff[Jb] = n, Jb.  Tiles are taken by ticket; a tile's
 // starts are numbered by ballots per row of 64 records and follow the tiles before

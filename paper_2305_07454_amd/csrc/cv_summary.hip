@@ -1,11 +1,14 @@
 // cv_summary.hip -- cv_journey_summary: one row per journey of sorted records.
 //
-// Journeys are maximal runs of equal journey id.  Tiles of ST records:
-//   k_sum_count   journey starts per wave chunk (a tile holds NW chunks);
+// Journeys are maximal runs of equal journey id.  Tiles of NW waves' chunks:
+//   k_sum_count   journey starts per wave chunk (k_sum_count_flags: from the
+//                 features' flags);
 //   k_tile_scan   exclusive scan of the tile totals (one block) -> journey index
-//                 of each tile's first start, J;
+//                 of each tile's first start, J (calls of more than N_S records; in
+//                 shorter ones every block sums the counts that it needs);
 //   k_sum_init    identity values in the accumulator rows of the J journeys;
-//   k_sum_reduce  segmented reduction over journey boundaries: every wave walks
+//   k_sum_reduce  (up to N_S records k_sum_both: box and sums in one launch)
+//                 segmented reduction over journey boundaries: every wave walks
 //                 its records in coalesced windows of 64, folding them in exact
 //                 fixed point; a journey that starts and ends inside one wave's
 //                 records is written out directly, the pieces of one that
