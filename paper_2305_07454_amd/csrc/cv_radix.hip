@@ -454,14 +454,15 @@ constexpr u64 DEVICE_COUNT_MAX_TILES = 1ull << 17;
 // at a time, and at 2 M keys and four passes that takes what the launches saved
 // (126, 128 us; 4 M 157, 211).  A count known on the device alone may be far below
 // its bound or come near it, so the kernel picks the tile, and the line lies where
-// one launch costs the second no more than launches per pass ever did:
+// one launch costs the second little more than launches per pass and the first less:
 //   few   distinct ids, a flush's rows (the record sort whole, one launch / per pass):
 //         3 M ids allowed, 5 000 there 498 / 508 us, all there 1575 / 1466 (1680 when
 //         each pass read its offsets from a scan's launch); 4.1 M 603 / 615, 2008 / 1871
 //         (2022);
 //   rows  the grid's partial rows (the whole call; every record one of its own: random
 //         places): 1.2 M records at 0.001 deg x 1 min 101 / 109, random 306 / 304; 2 M 115 /
-//         123, 378 / 369; 3 M 140 / 149, 616 / 584 (567 with the scan);
+//         123, 378 / 369; 3 M 140 / 149, 616 / 584 (567 with the scan); 4.1 M 161 / 169, 749 /
+//         712 (722);
 //   many  the same with directions: a row for every two or three records.
 // Tiles of 512 x 8 alone took 452 us for 2 M random records, 2375 for 4.1 M distinct ids.
 constexpr int ALL_B = 512;
@@ -472,8 +473,8 @@ AllForm all_form(u64 n_max, RadixCount count)
     if (n_max <= ALL_SMALL) return AllForm::small;
     switch (count) {
     case RadixCount::exact: return n_max <= (1u << 21) ? AllForm::large : AllForm::none;
-    case RadixCount::few: return n_max <= (1u << 22) ? AllForm::counted : AllForm::none;
-    case RadixCount::rows: return n_max <= (1u << 21) ? AllForm::counted : AllForm::none;
+    case RadixCount::few:
+    case RadixCount::rows: return n_max <= (1u << 22) ? AllForm::counted : AllForm::none;
     default: return AllForm::none;
     }
 }

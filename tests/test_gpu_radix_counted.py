@@ -1,7 +1,7 @@
 """Sorts of all passes in one launch whose number of keys is known on the device
-alone: counts on both sides of 2^19, where the launch changes its tiles, and bounds on
-both sides of 2^21 (the grid's partial rows) and 2^22 (the record sort's distinct ids),
-where launches per pass take over.  Compared with numpy."""
+alone (the grid's partial rows, the record sort's distinct ids): counts on both sides
+of 2^19, where the launch changes its tiles, and bounds on both sides of 2^22, where
+launches per pass take over.  Compared with numpy."""
 import numpy as np
 import pytest
 
@@ -22,7 +22,7 @@ def cv():
     return cvetl
 
 
-@pytest.mark.parametrize("n", [1 << 21, (1 << 21) + 1])
+@pytest.mark.parametrize("n", [1 << 21, (1 << 21) + 1, 1 << 22, (1 << 22) + 1])
 @pytest.mark.parametrize("rows", [1, 4_097, (1 << 19) - 1, 1 << 19, (1 << 19) + 1, 1 << 21])
 def test_grid_rows(cv, n, rows):
     """`rows` runs of one cell each, none across a tile's or a wave's edge (512 records): a row per run."""
