@@ -219,7 +219,14 @@ def bench_batched(args, steps):
     st = step_stats(per_step)
     ms_batched = st["median"]
     rs_b = bp.results()[0]
-    roof_b, pass_ms_b = radix_roofline(cvetl, n, rs_b)
+    # counted traffic of the default batch's passes, while the kernels and the shape are those profiled
+    traffic_b = None
+    if args.shards == 115 and args.total == 400_000_000:
+        seen = read_traffic(os.path.join(ROOT, "profiles", "radix_pass_c2_traffic.md"))
+        if seen.get("kernel_source_sha") == _kernel_sha("cv_radix.hip", "cv_radix.h", "cv_device.h") and \
+                seen.get("sort_shape") == str(cvetl.cv_tuning_get("sort_shape")):
+            traffic_b = float(seen["traffic_bytes_per_launch"])
+    roof_b, pass_ms_b = radix_roofline(cvetl, n, rs_b, traffic=traffic_b)
     stages_b = {}
     for fam in ("sort_prep", "gather", "features", "gather_features", "summary", "grid_agg", "grid_tail"):
         ms, c = cvetl.cv_timing_read(fam)
@@ -467,10 +474,9 @@ def bench_plain(args, workload):
         lattice["csv_extract"] = bench_csv(r, dev)
 
     traffic = None
-    tfile = os.path.join(ROOT, "profiles", "gather_c1_traffic.md")
-    if not sorts and workload == "c1" and args.n_journeys is None and os.path.exists(tfile):
-        t = read_traffic(tfile)
-        if t.get("kernel_source_sha") == _kernel_sha():
+    if not sorts and workload == "c1" and args.n_journeys is None:
+        t = read_traffic(os.path.join(ROOT, "profiles", "gather_c1_traffic.md"))
+        if t.get("kernel_source_sha") == _kernel_sha("cv_sort.hip", "cv_kin.h", "cv_device.h"):
             traffic = float(t["traffic_bytes_per_launch"])
 
     del pipe, rec
@@ -815,9 +821,12 @@ def pass_bytes(p, p0):
 
 
 def read_traffic(path):
-    """`key: value` lines of a traffic summary (HBM bytes per launch of the gather
-    from the FETCH_SIZE / WRITE_SIZE counters, scaled by a copy of known size)."""
+    """`key: value` lines of a traffic summary (HBM bytes per launch of a kernel
+    from the FETCH_SIZE / WRITE_SIZE counters, scaled by a copy of known size);
+    none without the file."""
     out = {}
+    if not os.path.exists(path):
+        return out
     for line in open(path):
         if ":" in line and not line.startswith(("#", "|", " ", "`")):
             k, v = line.split(":", 1)
@@ -825,10 +834,10 @@ def read_traffic(path):
     return out
 
 
-def _kernel_sha():
+def _kernel_sha(*files):
     import hashlib
     h = hashlib.sha256()
-    for f in ("cv_sort.hip", "cv_kin.h", "cv_device.h"):
+    for f in files:
         with open(os.path.join(ROOT, "paper_2305_07454_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]
