@@ -80,9 +80,9 @@ def test_csv_rows_at_the_length_limit(cv, eol):
 
 @pytest.mark.parametrize("fill", [b"x", b"\r", b","])
 def test_csv_line_without_end(cv, fill):
-    """64 MB without a newline after a row: refused from its first 2^20 bytes.  One
-    thread read it to the end, 0.2 us per byte; 100 ms is a fiftieth of that for
-    2^25 bytes, and a hundred times what reading 2^20 bytes takes."""
+    """64 MB without a newline after a row: refused from its first 2^20 bytes, which a
+    block reads in about a millisecond.  One thread read it to the end, some 0.2 us
+    per byte, 13 s."""
     import torch
     row = np.frombuffer(BODY % (7, 7, b"65536") + b"\n", dtype=np.uint8)
     text = torch.full(((64 << 20) + len(row),), fill[0], dtype=torch.uint8, device="cuda")

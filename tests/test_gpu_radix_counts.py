@@ -1,7 +1,6 @@
-"""Sorts whose number of keys is known on the device alone, on both sides of the
-bounds up to which their passes run in one launch: the grid's partial rows (2^20
-records, nearly every one with a row of its own, or few) and the record sort's
-distinct ids (2^21 of them allowed, all there or few).  Compared with numpy."""
+"""Sorts whose number of keys is known on the device alone, around 2^20 and 2^21 keys
+allowed: the grid's partial rows (nearly every record with a row of its own, or few) and
+the record sort's distinct ids (all there or few).  Compared with numpy."""
 import numpy as np
 import pytest
 
